@@ -418,16 +418,42 @@ __device__ __forceinline__ int64_t tile_key(int32_t I, int32_t J, int tile, int6
     return (int64_t)(I / tile) * ntj + J / tile;
 }
 
+// The tile of this lane's run (-1: none, or a class that is not scheduled).
+__device__ __forceinline__ int64_t run_tile(int64_t r, int64_t nruns, const int64_t *run_cblk,
+                                            const int32_t *run_class, const char *elig, const int32_t *c_row,
+                                            const int32_t *c_ci, int tile, int64_t ntj, int32_t *I, int32_t *J) {
+    if (r >= nruns || !elig[run_class[r]]) return -1;
+    const int64_t c = run_cblk[r];
+    *I = c_row[c];
+    *J = c_ci[c];
+    return tile_key(*I, *J, tile, ntj);
+}
+
+// Consecutive runs follow a C block row, so neighbouring lanes mostly share
+// their tile: the first lane of every stretch of equal tiles (`head`) adds
+// the stretch's length at once.  One atomic per run put thousands of them
+// on each tile's counter (23-blocks at 20 %, 121,000 runs on 121 tiles:
+// 208 + 247 us for the two kernels, 6 + 7 us so).
+__device__ __forceinline__ int stretch(int64_t key, int *head) {
+    const int l = lane_id();
+    const int64_t prev = __shfl_up(key, 1, kWave);
+    const uint64_t heads = __ballot(l == 0 || prev != key);
+    const uint64_t below = heads & (lanemask_lt() | (1ull << l)), above = heads & ~(lanemask_lt() | (1ull << l));
+    *head = 63 - __builtin_clzll(below);
+    return (above ? __ffsll((unsigned long long)above) - 1 : kWave) - l;
+}
+
 // Runs per tile (runs of eligible classes only).
 __global__ __launch_bounds__(256) void k_sched_hist(int64_t nruns, const int64_t *run_cblk,
                                                     const int32_t *run_class, const char *elig,
                                                     const int32_t *c_row, const int32_t *c_ci,
                                                     int tile, int64_t ntj, int64_t *hist) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nruns;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        if (!elig[run_class[r]]) continue;
-        const int64_t c = run_cblk[r];
-        atomicAdd((unsigned long long *)&hist[tile_key(c_row[c], c_ci[c], tile, ntj)], 1ull);
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nruns; base += (int64_t)gridDim.x * blockDim.x) {
+        int32_t I, J;
+        const int64_t key = run_tile(base + threadIdx.x, nruns, run_cblk, run_class, elig, c_row, c_ci, tile, ntj, &I, &J);
+        int head;
+        const int len = stretch(key, &head);
+        if (key >= 0 && head == lane_id()) atomicAdd((unsigned long long *)&hist[key], (unsigned long long)len);
     }
 }
 
@@ -439,15 +465,19 @@ __global__ __launch_bounds__(256) void k_sched_scatter(int64_t nruns, const int6
                                                        const int32_t *rbs, const int32_t *cbs,
                                                        int tile, int64_t ntj, int64_t *cursor,
                                                        unsigned long long *sched) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nruns;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        if (!elig[run_class[r]]) continue;
-        const int64_t c = run_cblk[r];
-        const int32_t I = c_row[c], J = c_ci[c];
-        const int64_t pos =
-            (int64_t)atomicAdd((unsigned long long *)&cursor[tile_key(I, J, tile, ntj)], 1ull);
-        sched[pos] = ((unsigned long long)r << 16) | ((unsigned long long)rbs[I] << 8) |
-                     (unsigned long long)cbs[J];
+    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nruns; base += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t r = base + threadIdx.x;
+        int32_t I, J;
+        const int64_t key = run_tile(r, nruns, run_cblk, run_class, elig, c_row, c_ci, tile, ntj, &I, &J);
+        int head;
+        const int len = stretch(key, &head);
+        unsigned long long pos = 0;
+        if (key >= 0 && head == lane_id())
+            pos = atomicAdd((unsigned long long *)&cursor[key], (unsigned long long)len);
+        pos = __shfl(pos, head, kWave) + (unsigned)(lane_id() - head);
+        if (key >= 0)
+            sched[pos] = ((unsigned long long)r << 16) | ((unsigned long long)rbs[I] << 8) |
+                         (unsigned long long)cbs[J];
     }
 }
 
