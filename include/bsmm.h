@@ -243,10 +243,11 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
                  always fail the filter, so C is the same as with "0",
                  which forms every block of the product pattern first
    "stack_at"    scheduled launch: "1" reads A's blocks from row-major
-                 copies made for the multiply (one vector load per four k
-                 values), "0" reads them in place, "auto" (default) copies
-                 for FP32 matrices only; the same bits either way (not in
-                 bsmm_multiply_noalloc, which makes no copies)
+                 copies made for the multiply, "0" and "auto" (default) read
+                 them in place; the same bits either way (not in
+                 bsmm_multiply_noalloc, which makes no copies).  Unless "1",
+                 an FP64 launch with many products per block of B reads B's
+                 blocks from such copies
    "stack_sched" order in which the scheduled launch's waves take runs:
                  "dynamic" (default; a run counter, several short runs per
                  update) or "static" (fixed strides, numbered XCD by XCD)

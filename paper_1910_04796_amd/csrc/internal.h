@@ -63,7 +63,7 @@ struct Options {
     int stack_tile = 32;   // tuned path: > 0 runs MFMA classes in one launch, tiles of this many blocks
     int stack_sched = 1;   // scheduled kernel: 0 static XCD-aware striding, 1 dynamic run counter
     int prescreen = 1;     // stack path with eps > 0: leave out C blocks whose norm bound is below eps
-    int stack_at = -1;     // scheduled launch reads A's blocks transposed: 1 on, 0 off, -1 FP32 only
+    int stack_at = -1;     // scheduled launch reads A's blocks transposed: 1 on, 0 and -1 (auto) off
 };
 Options &options();
 
@@ -295,7 +295,9 @@ struct Stacks {
     DevBuf d_rsi, d_csi, missing;     // size-class index of rows / columns; pattern flag
     bool screened = false;            // C's pattern came from the screen: products of left-out blocks are skipped
     DevBuf a_t;                       // A's blocks transposed, for the scheduled launch (option stack_at)
+    DevBuf b_t;                       // B's blocks transposed, for the scheduled launch
     bool a_t_fresh = false;           // a_t holds this multiply's A (later row panels reuse it)
+    bool b_t_fresh = false;           // b_t holds this multiply's B
     int kparts = 1;                   // parts per A block row in count and fill
     DevBuf pcount;                    // int64[C.nnzb * kparts]: first position of each part (kparts > 1)
     int nwin = 0;                     // column windows of a C wider than kMaxStackCols (else 0)
@@ -389,6 +391,7 @@ struct SmmArgs {
     // Scheduled kernel reading A's blocks transposed (row-major copies at
     // the same offsets), or null.
     const void *A_t;
+    const void *B_t;        // the same for B
 };
 // Squared block norms the scheduled kernel writes for the filter during the
 // current multiply on this thread (nullptr: none); set around the numeric
@@ -421,6 +424,7 @@ struct StackExec {
     LaunchList launches;
     std::vector<DevBuf> parts;  // partial blocks of split launches
     bool reads_a_t = false;     // a launch reads the stacks' transposed copy of A
+    bool reads_b_t = false;     // ... of B
     hipGraphExec_t exec = nullptr;
     hipEvent_t done = nullptr;  // recorded after every launch of exec
     StackExec() = default;
@@ -460,7 +464,7 @@ int build_graph(const LaunchList &launches, const bsmm_matrix_s *A, const bsmm_m
                 bsmm_matrix_s *C, const Stacks &st, double alpha, double beta,
                 hipGraphExec_t *out);
 int replay_stacks(const StackExec &ex, const bsmm_matrix_s *A, const bsmm_matrix_s *B,
-                  bsmm_matrix_s *C, const Stacks &st, double alpha, double beta, hipStream_t s);
+                  bsmm_matrix_s *C, Stacks &st, double alpha, double beta, hipStream_t s);
 
 // ----------------------------------------------------------------- dense
 int dense_multiply(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,

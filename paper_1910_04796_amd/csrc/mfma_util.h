@@ -8,6 +8,7 @@ namespace bsmm {
 
 typedef double v4d_t __attribute__((ext_vector_type(4)));
 typedef double v2d_t __attribute__((ext_vector_type(2)));
+typedef float v2f_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 
 // Both instructions take lane l's operands at row (or column) l % 16 and
@@ -21,16 +22,17 @@ template <> struct Mfma<double> {
     }
     // Result element e of lane l: row 4 e + l / 16, column l % 16.
     static __device__ __forceinline__ int row(int e, int lk) { return 4 * e + lk; }
-    // Four consecutive values (16-byte loads at 8-byte alignment: dword
-    // alignment is all the vector loads need).
-    static __device__ __forceinline__ void load4(const double *p, double (&v)[4]) {
-        v2d_t lo, hi;
-        __builtin_memcpy(&lo, p, sizeof lo);
-        __builtin_memcpy(&hi, p + 2, sizeof hi);
-        v[0] = lo[0];
-        v[1] = lo[1];
-        v[2] = hi[0];
-        v[3] = hi[1];
+    // Two consecutive values (one 16-byte load at 8-byte alignment: dword
+    // alignment is all the vector loads need), and their store.
+    static __device__ __forceinline__ void load2(const double *p, double &x, double &y) {
+        v2d_t v;
+        __builtin_memcpy(&v, p, sizeof v);
+        x = v[0];
+        y = v[1];
+    }
+    static __device__ __forceinline__ void store2(double *p, double x, double y) {
+        const v2d_t v = {x, y};
+        __builtin_memcpy(p, &v, sizeof v);
     }
 };
 template <> struct Mfma<float> {
@@ -41,13 +43,15 @@ template <> struct Mfma<float> {
     }
     // Result element e of lane l: row 4 (l / 16) + e, column l % 16.
     static __device__ __forceinline__ int row(int e, int lk) { return 4 * lk + e; }
-    static __device__ __forceinline__ void load4(const float *p, float (&v)[4]) {
-        v4f_t x;
-        __builtin_memcpy(&x, p, sizeof x);
-        v[0] = x[0];
-        v[1] = x[1];
-        v[2] = x[2];
-        v[3] = x[3];
+    static __device__ __forceinline__ void load2(const float *p, float &x, float &y) {
+        v2f_t v;
+        __builtin_memcpy(&v, p, sizeof v);
+        x = v[0];
+        y = v[1];
+    }
+    static __device__ __forceinline__ void store2(float *p, float x, float y) {
+        const v2f_t v = {x, y};
+        __builtin_memcpy(p, &v, sizeof v);
     }
 };
 

@@ -371,7 +371,7 @@ int numeric(int path, bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, doub
     case 2:
         return dense_multiply(A, B, C, alpha, beta, s);
     default:
-        st.a_t_fresh = false;  // A's transposed copy, if any, is made anew
+        st.a_t_fresh = st.b_t_fresh = false;  // transposed copies, if any, are made anew
         if (replay) {
             BSMM_TRY(replay_stacks(ex, A, B, C, st, alpha, beta, s));
             *n_panels = 1;

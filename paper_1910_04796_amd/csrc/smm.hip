@@ -142,13 +142,71 @@ __global__ __launch_bounds__(256) void k_smm_valu(SmmArgs p) {
 // tm = tn = 16): one wave owns one run at a time and keeps the C block as
 // MT x NT tiles of 16 x 16 x 4 MFMA accumulators (m <= 16 MT, n <= 16 NT):
 // v_mfma_f64_16x16x4 for FP64, v_mfma_f32_16x16x4 for FP32.  Operands come
-// straight from the contiguous A and B blocks (each product's blocks are a
-// few KB and stay in L1/L2), zero outside the block, so 23- or 13-sized
-// blocks are padded in registers only.  Both instructions take lane l's
-// operands at row (or column) l % 16 and k = l / 16 of the step.
+// straight from the contiguous A and B blocks; rows and columns past the
+// block repeat its last one (they only reach results that are not stored),
+// and k past the block is zero on both sides.  Both instructions take lane
+// l's operands at row (or column) l % 16 and k = l / 16 of the step.
+
+// Where an operand's values lie.
+enum OperandLayout {
+    kAlongTile,  // consecutive values run along the tile's rows (columns):
+                 // A in place (column-major), B from row-major copies
+    kAlongK      // consecutive values run along k: B in place, A from
+                 // row-major copies
+};
+
+// Row (column) of a block that lane index r = 0..15 of tile t stands for.
+// Two neighbouring tiles interleave their 32 rows, so that one load of two
+// consecutive values serves both.
+template <int NTILE> __device__ __forceinline__ int tile_row(int t, int r) {
+    return (t | 1) < NTILE ? 32 * (t >> 1) + 2 * r + (t & 1) : 16 * t + r;
+}
+
+// The operands of MFMA steps s = 0, 1 of the 8 values of k from k0: lane
+// group lk supplies k = k0 + 2 lk + s.  ext: rows (columns) of the block.
+template <class T, int NTILE, OperandLayout LAY>
+__device__ __forceinline__ void load_operand(const T *x, int ext, int k, int k0, int lr, int lk,
+                                             T (&f)[2][NTILE]) {
+    const int kb = k0 + 2 * lk;
+    if (LAY == kAlongTile) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const T *xk = x + min(kb + s, k - 1) * ext;
+#pragma unroll
+            for (int t = 0; t + 1 < NTILE; t += 2) {
+                // The pair may end one past the block: every data buffer
+                // holds one element more than its blocks.
+                Mfma<T>::load2(xk + min(16 * t + 2 * lr, ext - 1), f[s][t], f[s][t + 1]);
+            }
+            if (NTILE & 1) f[s][NTILE - 1] = xk[min(16 * (NTILE - 1) + lr, ext - 1)];
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < NTILE; ++t)
+            Mfma<T>::load2(x + min(tile_row<NTILE>(t, lr), ext - 1) * k + min(kb, k - 1), f[0][t], f[1][t]);
+    }
+    if (k0 + 8 > k) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int t = 0; t < NTILE; ++t) f[s][t] = kb + s < k ? f[s][t] : T(0);
+    }
+}
+
+template <class T, int MT, int NT>
+__device__ __forceinline__ void mfma_chunk(const T (&af)[2][MT], const T (&bf)[2][NT],
+                                           typename Mfma<T>::acc_t (&acc)[MT][NT]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::step(af[s][i], bf[s][j], acc[i][j]);
+}
+
 // Products [q0, q1) of one run into the MT x NT accumulator tiles of an
 // m x n C block.
-template <class T, int MT, int NT, bool AT = false>
+template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, int64_t q0, int64_t q1,
                                               typename Mfma<T>::acc_t (&acc)[MT][NT]) {
     const int lane = lane_id();
@@ -157,8 +215,8 @@ __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, in
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::zero();
-    const T *A = static_cast<const T *>(AT ? p.A_t : p.A);
-    const T *B = static_cast<const T *>(p.B);
+    const T *A = static_cast<const T *>(LA == kAlongK ? p.A_t : p.A);
+    const T *B = static_cast<const T *>(LB == kAlongTile ? p.B_t : p.B);
     // The next product's descriptor is loaded one product ahead.
     ulonglong2 nxt = q0 < q1 ? p.prods[q0] : make_ulonglong2(0ull, 0ull);
     for (int64_t q = q0; q < q1; ++q) {
@@ -168,110 +226,54 @@ __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, in
         const int k = (int)(pr.x >> 48);
         const T *b = B + (int64_t)pr.y;
         for (int k0 = 0; k0 < k; k0 += 16) {
-            // Four k steps of fragments, then their MFMAs.  Lane group
-            // g = l / 16 supplies k = k0 + 4 g + s to step s (any
-            // assignment of k to steps is valid when A and B agree), so a
-            // lane's B operands are four consecutive values of a column.
-            T af[4][MT], bf[4][NT];
-            const int kb = k0 + 4 * lk;
-#pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                const int row = 16 * i + lr;
-                if (AT) {
-                    // Row-major copy: the four k values of a row are adjacent.
-                    const T *ar = a + (int64_t)row * k + kb;
-                    if (row < m && kb + 3 < k) {
-                        T v[4];
-                        Mfma<T>::load4(ar, v);
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) af[s][i] = v[s];
-                    } else {
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) af[s][i] = (row < m && kb + s < k) ? ar[s] : T(0);
-                    }
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        af[s][i] = (row < m && kb + s < k) ? a[(int64_t)(kb + s) * m + row] : T(0);
-                }
+            T a0[2][MT], b0[2][NT], a1[2][MT], b1[2][NT];
+            const bool two = k0 + 8 < k;
+            load_operand<T, MT, LA>(a, m, k, k0, lr, lk, a0);
+            load_operand<T, NT, LB>(b, n, k, k0, lr, lk, b0);
+            if (two) {
+                load_operand<T, MT, LA>(a, m, k, k0 + 8, lr, lk, a1);
+                load_operand<T, NT, LB>(b, n, k, k0 + 8, lr, lk, b1);
             }
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int col = 16 * j + lr;
-                const T *bc = b + (int64_t)col * k + kb;
-                if (col < n && kb + 3 < k) {
-                    T v[4];
-                    Mfma<T>::load4(bc, v);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) bf[s][j] = v[s];
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) bf[s][j] = (col < n && kb + s < k) ? bc[s] : T(0);
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::step(af[s][i], bf[s][j], acc[i][j]);
+            mfma_chunk<T, MT, NT>(a0, b0, acc);
+            if (two) mfma_chunk<T, MT, NT>(a1, b1, acc);
         }
     }
 }
 
 // C block (column-major, ld = m) <- beta C + alpha acc, or the unscaled
-// accumulators into a partial block when alpha is not applied here.
-template <class T, int MT, int NT>
-__device__ __forceinline__ void mfma_store(T *c, int m, int n,
-                                           const typename Mfma<T>::acc_t (&acc)[MT][NT],
-                                           bool partial, T alpha, T beta) {
-    const int lane = lane_id();
-    const int lr = lane & 15, lk = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = 16 * i + Mfma<T>::row(e, lk), col = 16 * j + lr;
-                if (row < m && col < n) {
-                    T *dst = c + (int64_t)col * m + row;
-                    if (partial) {
-                        *dst = acc[i][j][e];
-                    } else {
-                        const T prod = alpha * acc[i][j][e];
-                        *dst = (beta == T(0)) ? prod : fma(beta, *dst, prod);
-                    }
-                }
-            }
-}
-
-// mfma_store (C = beta C + alpha acc) that also returns, on every lane,
-// the squared Frobenius norm of the stored block (summed in FP64: each
-// lane's elements in order, then across the wave in a fixed order).
-template <class T, int MT, int NT>
-__device__ __forceinline__ double mfma_store_sumsq(T *c, int m, int n,
-                                                   const typename Mfma<T>::acc_t (&acc)[MT][NT],
-                                                   T alpha, T beta) {
+// accumulators into a partial block when alpha is not applied here.  With
+// SUMSQ, returns on every lane the squared Frobenius norm of the stored
+// block (summed in FP64: each lane's elements in order, then across the
+// wave in a fixed order).
+template <class T, int MT, int NT, bool SUMSQ>
+__device__ __forceinline__ double mfma_store(T *c, int m, int n,
+                                             const typename Mfma<T>::acc_t (&acc)[MT][NT],
+                                             bool partial, T alpha, T beta) {
     const int lane = lane_id();
     const int lr = lane & 15, lk = lane >> 4;
     double ss = 0.0;
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int j = 0; j < NT; ++j) {
+        const int col = tile_row<NT>(j, lr);
+        if (col >= n) continue;
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int row = 16 * i + Mfma<T>::row(e, lk), col = 16 * j + lr;
-                if (row < m && col < n) {
+                const int row = tile_row<MT>(i, Mfma<T>::row(e, lk));
+                if (row < m) {
                     T *dst = c + (int64_t)col * m + row;
-                    const T prod = alpha * acc[i][j][e];
-                    const T v = (beta == T(0)) ? prod : fma(beta, *dst, prod);
+                    T v = acc[i][j][e];
+                    if (!partial) {
+                        const T prod = alpha * v;
+                        v = (beta == T(0)) ? prod : fma(beta, *dst, prod);
+                    }
                     *dst = v;
-                    ss = fma((double)v, (double)v, ss);
+                    if (SUMSQ) ss = fma((double)v, (double)v, ss);
                 }
             }
-    return wave_sum(ss);
+    }
+    return SUMSQ ? wave_sum(ss) : 0.0;
 }
 
 template <class T, int MT, int NT>
@@ -289,13 +291,13 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
         const int64_t rq0 = p.run_ptr[r], len = p.run_ptr[r + 1] - rq0;
         const int64_t q0 = rq0 + len * sg / S, q1 = rq0 + len * (sg + 1) / S;
         typename Mfma<T>::acc_t acc[MT][NT];
-        mfma_products<T, MT, NT>(p, m, n, q0, q1, acc);
+        mfma_products<T, MT, NT, kAlongTile, kAlongK>(p, m, n, q0, q1, acc);
         if (S > 1)
-            mfma_store<T, MT, NT>(static_cast<T *>(p.part) + it * (int64_t)m * n, m, n, acc, true, T(0),
-                                  T(0));
+            mfma_store<T, MT, NT, false>(static_cast<T *>(p.part) + it * (int64_t)m * n, m, n, acc, true,
+                                         T(0), T(0));
         else
-            mfma_store<T, MT, NT>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc, false, (T)p.alpha,
-                                  (T)p.beta);
+            mfma_store<T, MT, NT, false>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc, false,
+                                         (T)p.alpha, (T)p.beta);
     }
 }
 
@@ -306,12 +308,12 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
 // m << 8 | n.  Static mode: wave slots are numbered XCD by XCD (workgroup g
 // runs on XCD g % 8), so each XCD takes a contiguous part of every window
 // of in-flight runs; dynamic mode: waves take the next run from a counter.
-template <class T, int MT, int NT, bool AT>
+template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, int n) {
     typename Mfma<T>::acc_t acc[MT][NT];
-    mfma_products<T, MT, NT, AT>(p, m, n, p.run_ptr[r], p.run_ptr[r + 1], acc);
+    mfma_products<T, MT, NT, LA, LB>(p, m, n, p.run_ptr[r], p.run_ptr[r + 1], acc);
     // One store path: the norm is summed whether or not the filter wants it.
-    const double ss = mfma_store_sumsq<T, MT, NT>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc,
+    const double ss = mfma_store<T, MT, NT, true>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc, false,
                                                   (T)p.alpha, (T)p.beta);
     if (p.norm2 && lane_id() == 0) p.norm2[p.run_cblk[r]] = ss;
 }
@@ -320,7 +322,7 @@ constexpr int kXcds = 8;
 // Fewest runs for which the MFMA classes go through the scheduled launch.
 constexpr int64_t kSchedMinRuns = 4096;
 
-template <class T, bool AT>
+template <class T, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     const int wpw = blockDim.x / kWave;
     const int64_t waves = (int64_t)gridDim.x * wpw;
@@ -344,11 +346,11 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
             const int64_t r = (int64_t)(e >> 16);
             const int m = (int)((e >> 8) & 255), n = (int)(e & 255);
             if (m > 16) {
-                if (n > 16) sched_run<T, 2, 2, AT>(p, r, m, n);
-                else sched_run<T, 2, 1, AT>(p, r, m, n);
+                if (n > 16) sched_run<T, 2, 2, LA, LB>(p, r, m, n);
+                else sched_run<T, 2, 1, LA, LB>(p, r, m, n);
             } else {
-                if (n > 16) sched_run<T, 1, 2, AT>(p, r, m, n);
-                else sched_run<T, 1, 1, AT>(p, r, m, n);
+                if (n > 16) sched_run<T, 1, 2, LA, LB>(p, r, m, n);
+                else sched_run<T, 1, 1, LA, LB>(p, r, m, n);
             }
         }
         if (p.sched_mode == 0) {
@@ -361,32 +363,50 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     }
 }
 
-template <class T>
+template <class T, OperandLayout LA, OperandLayout LB>
 __global__ __launch_bounds__(256, 4) void k_smm_mfma_sched(SmmArgs p) {
-    sched_loop<T, false>(p);
+    sched_loop<T, LA, LB>(p);
 }
 
-// The scheduled launch reading A's blocks from their row-major copies.
-template <class T>
-__global__ __launch_bounds__(256, 4) void k_smm_mfma_sched_at(SmmArgs p) {
-    sched_loop<T, true>(p);
-}
-
-// Row-major copies of A's blocks at the blocks' own offsets: one workgroup
-// per block row, consecutive lanes write consecutive elements of a row.
+// Row-major copies of a matrix's blocks at the blocks' own offsets: a wave
+// takes whole blocks of one block row and turns them through LDS (blocks of
+// up to kTurnElems elements), so that reads and writes are both contiguous.
+constexpr int kTurnElems = 1024;
 template <class T>
 __global__ __launch_bounds__(256) void k_transpose_blocks(int32_t nbr, const int64_t *rp, const int32_t *ci,
                                                           const int32_t *rbs, const int32_t *cbs,
                                                           const int64_t *blk_off, const T *src, T *dst) {
+    __shared__ T lds[4][kTurnElems + 64];
+    T *buf = lds[wave_id()];
+    const int lane = lane_id();
     for (int32_t r = blockIdx.x; r < nbr; r += gridDim.x) {
         const int m = rbs[r];
-        for (int64_t p = rp[r]; p < rp[r + 1]; ++p) {
+        const int ld = m | 1;  // odd: the column reads spread over the banks
+        const float rm = 1.0f / (float)m;
+        for (int64_t p = rp[r] + wave_id() + 4 * (int64_t)blockIdx.y; p < rp[r + 1]; p += 4 * (int64_t)gridDim.y) {
             const int k = cbs[ci[p]];
             const T *sb = src + blk_off[p];
             T *db = dst + blk_off[p];
-            for (int e = threadIdx.x; e < m * k; e += blockDim.x) {
-                const int i = e / k, j = e - i * k;
-                db[e] = sb[(int64_t)j * m + i];
+            const int64_t len = (int64_t)m * k;
+            if ((int64_t)ld * k <= kTurnElems + 64) {
+                for (int e = lane; e < (int)len; e += kWave) {
+                    int i;
+                    const int j = divmod_small(e, m, rm, &i);
+                    buf[j * ld + i] = sb[e];
+                }
+                wave_lds_sync();
+                const float rk = 1.0f / (float)k;
+                for (int e = lane; e < (int)len; e += kWave) {
+                    int j;
+                    const int i = divmod_small(e, k, rk, &j);
+                    db[e] = buf[j * ld + i];
+                }
+                wave_lds_sync();
+            } else {
+                for (int64_t e = lane; e < len; e += kWave) {
+                    const int64_t i = e / k, j = e - i * k;
+                    db[e] = sb[j * m + i];
+                }
             }
         }
     }
@@ -467,10 +487,32 @@ template <class T> SmmKernel kernel_for(int tm, int tn) {
 
 thread_local double *t_norm_sink = nullptr;
 
-bool is_sched_kernel(const void *fn) {
-    return fn == (const void *)k_smm_mfma_sched<double> || fn == (const void *)k_smm_mfma_sched<float> ||
-           fn == (const void *)k_smm_mfma_sched_at<double> || fn == (const void *)k_smm_mfma_sched_at<float>;
+// The scheduled kernel reading A (or B) from row-major copies.
+SmmKernel sched_kernel(int dtype, bool a_rows, bool b_rows) {
+    if (dtype == BSMM_F32)
+        return a_rows ? k_smm_mfma_sched<float, kAlongK, kAlongK> : k_smm_mfma_sched<float, kAlongTile, kAlongK>;
+    if (a_rows) return k_smm_mfma_sched<double, kAlongK, kAlongK>;
+    return b_rows ? k_smm_mfma_sched<double, kAlongTile, kAlongTile> : k_smm_mfma_sched<double, kAlongTile, kAlongK>;
 }
+
+bool is_sched_kernel(const void *fn) {
+    return fn == (const void *)sched_kernel(BSMM_F64, false, false) ||
+           fn == (const void *)sched_kernel(BSMM_F64, false, true) ||
+           fn == (const void *)sched_kernel(BSMM_F64, true, false) ||
+           fn == (const void *)sched_kernel(BSMM_F32, false, false) ||
+           fn == (const void *)sched_kernel(BSMM_F32, true, false);
+}
+
+// Fewest products per block of B for which the scheduled launch reads B
+// from row-major copies.  A fragment of B in place touches one 64-byte
+// piece of 16 columns, from a copy one 128-byte piece of 4 rows of k: a
+// third fewer cache lines, which the launch feels once each B block is read
+// many times, while the copy costs one read and one write of B.  Measured
+// (kernel plus copy, FP64): banded 30 % (about 800 products per B block)
+// 680 -> 647 ms, 10 % (270) 75.8 -> 73.0 ms, 23-blocks at 20 % (70) 2.23 ->
+// 2.15 ms, banded 1 % (18) 1.46 -> 1.61 ms.  FP32, whose fragments are half
+// as long, gains nothing (10 %, 130 products: 11.9 -> 12.1 ms).
+constexpr int64_t kCopyBMinUses = 48;
 
 constexpr int kLdsBudget = 64 * 1024;  // bytes of LDS per workgroup
 
@@ -660,19 +702,22 @@ static int split_for(int64_t runs, int64_t prods, int m, int n, size_t esize) {
     return (int)std::max<int64_t>(S, 1);
 }
 
-// Row-major copies of A's blocks into st.a_t (the A data of this call: a
-// replayed plan copies again, since A's values may have changed).
-static int transpose_a(const bsmm_matrix_s *A, const Stacks &st, hipStream_t s) {
-    BSMM_TRY(const_cast<DevBuf &>(st.a_t).reserve(A->esize() * (size_t)(A->storage + 1), s));
-    if (A->nnzb == 0) return BSMM_OK;
-    if (A->dtype == BSMM_F32)
-        hipLaunchKernelGGL(k_transpose_blocks<float>, dim3(grid_rows(A->nbr)), dim3(256), 0, s, A->nbr,
-                           A->d_row_ptr(), A->d_col_ind(), A->d_rbs(), A->d_cbs(), A->d_blk_off(),
-                           (const float *)A->d_raw(), st.a_t.as<float>());
+// Row-major copies of M's blocks into buf (the data of this call: a
+// replayed plan copies again, since the values may have changed).
+static int copy_rows(const bsmm_matrix_s *M, DevBuf &buf, hipStream_t s) {
+    BSMM_TRY(buf.reserve(M->esize() * (size_t)(M->storage + 1), s));
+    if (M->nnzb == 0) return BSMM_OK;
+    // About 4,096 workgroups, also where there are few block rows.
+    const unsigned gy = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(4096, M->nbr), 1024));
+    const dim3 grid(grid_rows(M->nbr), gy);
+    if (M->dtype == BSMM_F32)
+        hipLaunchKernelGGL(k_transpose_blocks<float>, grid, dim3(256), 0, s, M->nbr, M->d_row_ptr(),
+                           M->d_col_ind(), M->d_rbs(), M->d_cbs(), M->d_blk_off(),
+                           (const float *)M->d_raw(), buf.as<float>());
     else
-        hipLaunchKernelGGL(k_transpose_blocks<double>, dim3(grid_rows(A->nbr)), dim3(256), 0, s, A->nbr,
-                           A->d_row_ptr(), A->d_col_ind(), A->d_rbs(), A->d_cbs(), A->d_blk_off(),
-                           (const double *)A->d_raw(), st.a_t.as<double>());
+        hipLaunchKernelGGL(k_transpose_blocks<double>, grid, dim3(256), 0, s, M->nbr, M->d_row_ptr(),
+                           M->d_col_ind(), M->d_rbs(), M->d_cbs(), M->d_blk_off(),
+                           (const double *)M->d_raw(), buf.as<double>());
     return launch_check("transpose_blocks");
 }
 
@@ -720,8 +765,10 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         SmmLaunch L;
         BSMM_TRY(plan_smm(prm, m, n, kmax, C->dtype, &L));
         if (chunk <= 0 && prm.tm == kMfmaTile && (int)st.class_prod_begin.size() == st.n_classes + 1) {
-            const int S = split_for(re - rb, st.class_prod_begin[cl + 1] - st.class_prod_begin[cl], m, n,
-                                    C->esize());
+            // The plain path never splits a run: its sums keep one order.
+            const int S = !tuned ? 1
+                                 : split_for(re - rb, st.class_prod_begin[cl + 1] - st.class_prod_begin[cl],
+                                             m, n, C->esize());
             if (tuned && options().jit && S == 1 && uniform_k > 0) {
                 // One product depth: a kernel compiled for this (m, n, k).
                 if (hipFunction_t f = jit_smm_kernel(C->dtype, m, n, uniform_k)) {
@@ -778,24 +825,17 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     if (sched_on && sched_runs > 0) {
         BSMM_TRY(build_schedule(C, st, eligible, options().stack_tile, s));
         SmmLaunch L;
-        // FP32 loads are instruction-bound: A's blocks are read from
-        // row-major copies (one 16-byte load for four k values instead of
-        // four 4-byte loads; banded 10 % FP32 kernel 54.5 -> 51.8 ms).  FP64
-        // is bound by the fabric, where the copies' strided rows coalesce
-        // worse (headline kernel 669 -> 718 ms), so it reads A in place.
-        const int at_opt = options().stack_at;
-        // (Not with a scratch arena: the copy is as large as A.)
-        const bool at = (at_opt == 1 || (at_opt < 0 && C->dtype == BSMM_F32)) && !scratch_arena();
-        if (at && !st.a_t_fresh) {
-            BSMM_TRY(transpose_a(A, st, s));
-            st.a_t_fresh = true;
-        }
+        // No copies with a scratch arena (they are as large as the operands).
+        const bool at = options().stack_at == 1 && !scratch_arena();
+        const bool bt = !at && C->dtype == BSMM_F64 && !scratch_arena() && B->nnzb > 0 &&
+                        st.n_prod / B->nnzb >= kCopyBMinUses;
         ex->reads_a_t = at;
-        if (C->dtype == BSMM_F32)
-            L.fn = at ? (void *)k_smm_mfma_sched_at<float> : (void *)k_smm_mfma_sched<float>;
-        else
-            L.fn = at ? (void *)k_smm_mfma_sched_at<double> : (void *)k_smm_mfma_sched<double>;
+        ex->reads_b_t = bt;
+        if (at) BSMM_TRY(st.a_t.reserve(A->esize() * (size_t)(A->storage + 1), s));
+        if (bt) BSMM_TRY(st.b_t.reserve(B->esize() * (size_t)(B->storage + 1), s));
+        L.fn = (void *)sched_kernel(C->dtype, at, bt);
         L.args.A_t = at ? st.a_t.p : nullptr;
+        L.args.B_t = bt ? st.b_t.p : nullptr;
         L.dtype = C->dtype;
         L.args.L = kWave;
         L.args.G = 1;
@@ -858,9 +898,13 @@ void retire_graph(hipGraphExec_t exec, hipEvent_t done) {
 }
 
 int replay_stacks(const StackExec &ex, const bsmm_matrix_s *A, const bsmm_matrix_s *B,
-                  bsmm_matrix_s *C, const Stacks &st, double alpha, double beta, hipStream_t s) {
-    // Same buffer (the launches hold its address), this call's A values.
-    if (ex.reads_a_t) BSMM_TRY(transpose_a(A, st, s));
+                  bsmm_matrix_s *C, Stacks &st, double alpha, double beta, hipStream_t s) {
+    // Same buffers (the launches hold their addresses), this call's values;
+    // later row panels of one multiply find them there.
+    if (ex.reads_a_t && !st.a_t_fresh) BSMM_TRY(copy_rows(A, st.a_t, s));
+    if (ex.reads_b_t && !st.b_t_fresh) BSMM_TRY(copy_rows(B, st.b_t, s));
+    if (ex.reads_a_t) st.a_t_fresh = true;
+    if (ex.reads_b_t) st.b_t_fresh = true;
     if (ex.exec) {
         {
             KernelTimer kt(1, s);

@@ -1,0 +1,130 @@
+"""Edges of the small-block MFMA kernel's tiles and of the passes around it:
+block sides on both sides of the 8-, 16- and 32-wide tiles, products one
+deep to beyond two chunks, B read in place and from row-major copies, blocks
+moved between layouts in pieces, norms of neighbouring blocks of very
+different magnitude."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from synth import BlockCSR, make_matrix, rng_of
+
+from tests.helpers import check_against_oracle, gpu_multiply, lib, set_path
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrices(seed, rs, ks, ns, occ, values="uniform"):
+    rng = rng_of(seed)
+    return make_matrix(rng, rs, ks, occ, values), make_matrix(rng, ks, ns, occ, values)
+
+
+@pytest.mark.parametrize("kernel", ["plain", "tuned"])
+@pytest.mark.parametrize("sizes", [[7, 8, 9], [15, 16, 17], [1, 31, 32, 33], [47, 48, 49], [63, 64, 2]])
+def test_tile_edges(sizes, kernel):
+    """Integer values: exact whatever the order of the sums."""
+    rng = rng_of(len(sizes) + sizes[0])
+    rs, ks, ns = (rng.choice(sizes, size=9).astype(np.int32) for _ in range(3))
+    A, B = _matrices(sizes[0], rs, ks, ns, 0.6, "int")
+    Cin = make_matrix(rng, rs, ns, 0.3, "int")
+    X, _ = gpu_multiply(2.0, A, B, -1.0, Cin, path="stack", kernel=kernel)
+    check_against_oracle(X, orc.multiply(2.0, A, B, -1.0, Cin), 0.0)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 7, 8, 9, 15, 16, 17, 24, 25, 40])
+def test_product_depths(k):
+    """Uniform 13- and 23-sided blocks, every product k deep."""
+    rng = rng_of(k)
+    rs = rng.choice([13, 23], size=10).astype(np.int32)
+    A, B = _matrices(k + 100, rs, np.full(12, k, np.int32), rs, 0.7, "int")
+    X, _ = gpu_multiply(1.0, A, B, 0.0, path="stack", kernel="tuned")
+    check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
+
+
+def test_copied_b_same_bits():
+    """Enough products per B block for row-major copies of B: the same bits
+    as reading both operands in place (stack_at "1" keeps B in place), and a
+    replayed plan copies B's new values."""
+    rng = rng_of(5)
+    # Two sizes, so that every shape class holds more runs than are split.
+    rs, ks = (np.repeat([13, 23], 70).astype(np.int32), rng.choice([5, 17, 32], size=110).astype(np.int32))
+    A, B = _matrices(6, rs, ks, rs, 0.6)
+    b = lib()
+    out = {}
+    try:
+        for at in ("0", "1"):
+            b.bsmm_set_option("stack_at", at)
+            out[at] = gpu_multiply(1.5, A, B, 0.0, path="stack", kernel="tuned")
+    finally:
+        b.bsmm_set_option("stack_at", "auto")
+    assert out["0"][1]["n_sched_runs"] > 4096
+    assert out["0"][1]["n_products"] >= 48 * len(B.col_ind)
+    check_against_oracle(out["0"][0], out["1"][0], 0.0)
+    check_against_oracle(out["0"][0], orc.multiply(1.5, A, B, 0.0), 1e-13)
+    b.bsmm_set_option("plan_cache", "1")
+    set_path("stack", "tuned")
+    try:
+        MA, MB, MC = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B), b.Matrix.empty(A.rbs, B.cbs)
+        b.multiply(1.0, MA, MB, 0.0, MC)
+        E1, E2 = b.Matrix.empty(B.rbs, B.rbs), b.Matrix.empty(B.rbs, B.cbs)
+        b.multiply(1.0, E1, E2, 2.0, MB)  # B <- 2 B in place
+        b.multiply(1.0, MA, MB, 0.0, MC)
+        X = MC.to_host()
+        for M in (MA, MB, MC, E1, E2):
+            M.close()
+    finally:
+        b.bsmm_set_option("plan_cache", "0")
+        set_path()
+    check_against_oracle(X, orc.multiply(2.0, A, B, 0.0), 1e-13)
+
+
+@pytest.mark.parametrize("sizes", [[1], [1, 2, 3], [5, 13], [23, 32, 64]])
+def test_moved_blocks(sizes):
+    """A filter that drops single blocks and stretches of them, the packed
+    read-out, and old blocks moved into a grown pattern."""
+    rng = rng_of(sum(sizes))
+    rs = rng.choice(sizes, size=40).astype(np.int32)
+    one = np.ones(40, np.int32)
+    A = make_matrix(rng, rs, one, 0.5)
+    B = make_matrix(rng, one, rs, 0.5)
+    # Columns of small values: their blocks of C fall below the filter.
+    scale = np.where(rng.random(40) < 0.5, 1e-12, 1.0)
+    ne = np.repeat(B.col_ind, np.asarray(rs)[B.col_ind])
+    B = BlockCSR(B.rbs, B.cbs, B.row_ptr, B.col_ind, B.data * scale[ne])
+    b = lib()
+    set_path("stack", "tuned")
+    try:
+        MA, MB, MC = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B), b.Matrix.empty(rs, rs)
+        b.multiply(1.0, MA, MB, 0.0, MC, 1e-9)
+        X = MC.to_host()
+        R = orc.multiply(1.0, A, B, 0.0, filter_eps=1e-9)
+        check_against_oracle(X, R, 1e-13)
+        b.multiply(1.0, MA, MB, 1.0, MC)
+        Y = MC.to_host()
+        for M in (MA, MB, MC):
+            M.close()
+    finally:
+        set_path()
+    check_against_oracle(Y, orc.multiply(1.0, A, B, 1.0, R), 1e-13)
+
+
+def test_screen_norms_of_mixed_neighbours():
+    """Blocks whose squares overflow, underflow or are ordinary side by side
+    (also zero and NaN ones): the screened multiply gives the unscreened
+    one's blocks bit for bit."""
+    rng = rng_of(77)
+    sizes = rng.choice([1, 5, 13, 23], size=24).astype(np.int32)
+    A, B = _matrices(78, sizes, sizes, sizes, 0.5)
+    per_block = np.asarray(sizes, np.int64)[np.repeat(np.arange(24), np.diff(A.row_ptr))] * sizes[A.col_ind]
+    mag = rng.choice([1e-200, 1e-160, 1e-12, 1.0, 0.0, 1e170], size=len(per_block))
+    A = BlockCSR(A.rbs, A.cbs, A.row_ptr, A.col_ind, A.data * np.repeat(mag, per_block))
+    A.data[int(per_block[:7].sum())] = np.nan
+    b = lib()
+    out = []
+    try:
+        for on in ("1", "0"):
+            b.bsmm_set_option("prescreen", on)
+            out.append(gpu_multiply(1.0, A, B, 0.0, eps=1e-9, path="stack", kernel="tuned")[0])
+    finally:
+        b.bsmm_set_option("prescreen", "1")
+    check_against_oracle(out[0], out[1], 0.0)
