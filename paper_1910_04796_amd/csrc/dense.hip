@@ -11,9 +11,10 @@
 // epilogue, which writes C = beta*C + alpha*(Ap Bp) straight into C's
 // blocks through per-row and per-column (block, offset) maps.
 //
-// GEMM: 128 x 128 output tile per 256-thread workgroup, k step 16 (or 32),
-// LDS double buffered; each wave owns a 64 x 64 sub-tile as 4 x 4 MFMA tiles of
-// v_mfma_f64_16x16x4 (FP64 in, FP64 accumulate).  Workgroup ids are remapped
+// GEMM: 128 x 128 output tile per 512-thread workgroup, k step 16, LDS double
+// buffered; each wave owns a 64 x 32 sub-tile as 4 x 2 MFMA tiles of
+// v_mfma_f64_16x16x4 (FP64 in, FP64 accumulate); with k step 32, 256 threads
+// and 64 x 64 sub-tiles.  Workgroup ids are remapped
 // so that the tiles dispatched to one XCD form a contiguous band of
 // 8 tile-rows (shared A panels stay in that XCD's L2).  When the output
 // has too few tiles to fill the GPU (M = N = 1408 with K in the millions:
@@ -34,22 +35,33 @@ template <class T> struct Vec2;
 template <> struct Vec2<double> { typedef double __attribute__((ext_vector_type(2))) t; };
 template <> struct Vec2<float> { typedef float __attribute__((ext_vector_type(2))) t; };
 
+// Zeros in the padding of a column-major panel of ld x ncols whose merge
+// fills rows x cols: the rows below in the first columns, then whole
+// columns (one workgroup per column).
+template <class T>
+__global__ __launch_bounds__(256) void k_zero_padding(T *panel, int64_t ld, int64_t ncols, int64_t rows, int64_t cols) {
+    for (int64_t c = blockIdx.x; c < ncols; c += gridDim.x)
+        for (int64_t r = (c < cols ? rows : 0) + threadIdx.x; r < ld; r += blockDim.x) panel[c * ld + r] = T(0);
+}
+
 constexpr int BM = 128, BN = 128;
 constexpr int kGroupM = 8;
 
 // Merge of blocks of 64 elements or more: one wave per block (block row
-// found by binary search in the row pointer), copying the column-major
+// found by binary search in the row pointer, or by division when every
+// block is stored), copying the column-major
 // block into the column-major panel (ld = panel rows); consecutive lanes
 // write consecutive rows of a column.
 template <class T>
-__global__ __launch_bounds__(256) void k_merge_block(int32_t nbr, int64_t nnzb, const int32_t *rbs,
+__global__ __launch_bounds__(256) void k_merge_block(int32_t nbr, int32_t full_nbc, int64_t nnzb, const int32_t *rbs,
                                                      const int32_t *cbs, const int64_t *row_off,
                                                      const int64_t *col_off, const int64_t *rp,
                                                      const int32_t *ci, const int64_t *blk_off,
                                                      const T *data, T *panel, int64_t ld) {
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
     for (int64_t p = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id(); p < nnzb; p += waves) {
-        int32_t lo = 0, hi = nbr;  // row = last lo with rp[lo] <= p
+        int32_t lo = full_nbc ? (int32_t)((uint32_t)p / (uint32_t)full_nbc) : 0;
+        int32_t hi = full_nbc ? lo : nbr;  // row = last lo with rp[lo] <= p
         while (hi - lo > 1) {
             const int32_t mid = (lo + hi) >> 1;
             if (rp[mid] <= p) lo = mid;
@@ -157,29 +169,30 @@ struct GemmArgs {
     const int32_t *c_rbs;
     const int2 *rmap, *cmap;
     // Split k (few output tiles): workgroup (tile, split) sums k tiles
-    // [split * kt_per, (split + 1) * kt_per) into part[split] (row-major
-    // M_pad x N_pad, unscaled); k_splitk_reduce applies the epilogue.
+    // [split * kt_per, (split + 1) * kt_per) into part[split] (unscaled, per
+    // tile in the waves' accumulator order); k_splitk_reduce applies the
+    // epilogue.
     int splits, kt_per;
     void *part;
 };
 
 // Global -> register loads of one k step of KB: A tile (128 rows x KB k) as
 // KB * 64 double2 along the rows, B tile (KB k x 128 cols) along k.
-template <class T, int KB>
-__device__ __forceinline__ void gemm_gload(typename Vec2<T>::t (&ra)[KB / 4],
-                                           typename Vec2<T>::t (&rb)[KB / 4], const T *Ablk,
+template <class T, int KB, int NTH>
+__device__ __forceinline__ void gemm_gload(typename Vec2<T>::t (&ra)[KB * 64 / NTH],
+                                           typename Vec2<T>::t (&rb)[KB * 64 / NTH], const T *Ablk,
                                            const T *Bblk, int64_t lda, int64_t ldb, int kt, int tid) {
     typedef typename Vec2<T>::t V2;
     const int64_t k0 = (int64_t)kt * KB;
 #pragma unroll
-    for (int i = 0; i < KB / 4; ++i) {
-        const int e = tid + 256 * i;
+    for (int i = 0; i < KB * 64 / NTH; ++i) {
+        const int e = tid + NTH * i;
         const int kk = e >> 6, r2 = e & 63;
         ra[i] = *reinterpret_cast<const V2 *>(Ablk + (k0 + kk) * lda + 2 * r2);
     }
 #pragma unroll
-    for (int i = 0; i < KB / 4; ++i) {
-        const int e = tid + 256 * i;
+    for (int i = 0; i < KB * 64 / NTH; ++i) {
+        const int e = tid + NTH * i;
         const int col = e / (KB / 2), k2 = e % (KB / 2);
         rb[i] = *reinterpret_cast<const V2 *>(Bblk + (int64_t)col * ldb + k0 + 2 * k2);
     }
@@ -187,20 +200,20 @@ __device__ __forceinline__ void gemm_gload(typename Vec2<T>::t (&ra)[KB / 4],
 
 // Register -> LDS stores: As[k][m]; Bs[n][k ^ (n & 15)] (XOR swizzle keeps
 // the 16 lanes that read one k of 16 consecutive columns on distinct banks).
-template <class T, int KB>
-__device__ __forceinline__ void gemm_lstore(const typename Vec2<T>::t (&ra)[KB / 4],
-                                            const typename Vec2<T>::t (&rb)[KB / 4], T *As, T *Bs,
+template <class T, int KB, int NTH>
+__device__ __forceinline__ void gemm_lstore(const typename Vec2<T>::t (&ra)[KB * 64 / NTH],
+                                            const typename Vec2<T>::t (&rb)[KB * 64 / NTH], T *As, T *Bs,
                                             int tid) {
     typedef typename Vec2<T>::t V2;
 #pragma unroll
-    for (int i = 0; i < KB / 4; ++i) {
-        const int e = tid + 256 * i;
+    for (int i = 0; i < KB * 64 / NTH; ++i) {
+        const int e = tid + NTH * i;
         const int kk = e >> 6, r2 = e & 63;
         *reinterpret_cast<V2 *>(&As[kk * BM + 2 * r2]) = ra[i];
     }
 #pragma unroll
-    for (int i = 0; i < KB / 4; ++i) {
-        const int e = tid + 256 * i;
+    for (int i = 0; i < KB * 64 / NTH; ++i) {
+        const int e = tid + NTH * i;
         const int col = e / (KB / 2), k2 = e % (KB / 2);
         const int sw = col & 15;
         const int base = (2 * k2) ^ (sw & ~1);
@@ -211,8 +224,13 @@ __device__ __forceinline__ void gemm_lstore(const typename Vec2<T>::t (&ra)[KB /
 
 // KB = 16: 64 KB of LDS, two workgroups per CU; KB = 32: 128 KB, one
 // workgroup per CU with twice the prefetch distance and half the barriers.
-template <class T, int KB, int MINB, bool SPLIT>
-__global__ __launch_bounds__(256, MINB) void k_dgemm_mfma(GemmArgs g) {
+// NT: 16-column tiles per wave.  Bound by the matrix cores; what is left is
+// the waves' common stop at the barrier and LDS stores of a k step, which
+// four waves per SIMD (NT = 2, 122 registers) cover better than two (NT = 4,
+// 224 registers): N = 8192 16.82 -> 16.40 ms (67 TFLOP/s).
+template <class T, int KB, int NT, int MINW, bool SPLIT>
+__global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
+    constexpr int NTH = 1024 / NT;
     __shared__ T As[2][KB * BM];  // [k][m]
     __shared__ T Bs[2][BN * KB];  // [n][k ^ swizzle(n)]
 
@@ -220,7 +238,10 @@ __global__ __launch_bounds__(256, MINB) void k_dgemm_mfma(GemmArgs g) {
     // (split k: consecutive logical ids walk the tiles of one split).
     const int nwg = gridDim.x;
     int logical = blockIdx.x;
-    if ((nwg & 7) == 0) logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+    {
+        const int xcd = blockIdx.x & 7, rest = nwg & 7;
+        logical = xcd * (nwg >> 3) + min(xcd, rest) + (blockIdx.x >> 3);
+    }
     int split = 0, kt0 = 0, kt1 = g.ktiles;
     if (SPLIT) {
         const int tiles = g.tiles_m * g.tiles_n;
@@ -246,37 +267,37 @@ __global__ __launch_bounds__(256, MINB) void k_dgemm_mfma(GemmArgs g) {
     const T *Ablk = static_cast<const T *>(g.Ap) + (int64_t)tm * BM;
     const T *Bblk = static_cast<const T *>(g.Bp) + (int64_t)tn * BN * g.ldb;
 
-    typename Vec2<T>::t ra[KB / 4], rb[KB / 4];
-    typename Mfma<T>::acc_t acc[4][4];
+    typename Vec2<T>::t ra[KB * 64 / NTH], rb[KB * 64 / NTH];
+    typename Mfma<T>::acc_t acc[4][NT];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = Mfma<T>::zero();
+        for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::zero();
 
-    gemm_gload<T, KB>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt0, tid);
-    gemm_lstore<T, KB>(ra, rb, As[0], Bs[0], tid);
+    gemm_gload<T, KB, NTH>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt0, tid);
+    gemm_lstore<T, KB, NTH>(ra, rb, As[0], Bs[0], tid);
     __syncthreads();
     for (int kt = kt0; kt < kt1; ++kt) {
         const int cur = (kt - kt0) & 1;
-        if (kt + 1 < kt1) gemm_gload<T, KB>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt + 1, tid);
+        if (kt + 1 < kt1) gemm_gload<T, KB, NTH>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt + 1, tid);
 #pragma unroll
         for (int ks = 0; ks < KB / 4; ++ks) {
             const int k = ks * 4 + lk;
-            T a[4], b[4];
+            T a[4], b[NT];
 #pragma unroll
             for (int t = 0; t < 4; ++t) a[t] = As[cur][k * BM + wm * 64 + t * 16 + l16];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int col = wn * 64 + t * 16 + l16;
+            for (int t = 0; t < NT; ++t) {
+                const int col = wn * 16 * NT + t * 16 + l16;
                 b[t] = Bs[cur][col * KB + (k ^ (col & 15))];
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < NT; ++j)
                     acc[i][j] = Mfma<T>::step(a[i], b[j], acc[i][j]);
         }
-        if (kt + 1 < kt1) gemm_lstore<T, KB>(ra, rb, As[cur ^ 1], Bs[cur ^ 1], tid);
+        if (kt + 1 < kt1) gemm_lstore<T, KB, NTH>(ra, rb, As[cur ^ 1], Bs[cur ^ 1], tid);
         __syncthreads();
     }
 
@@ -284,27 +305,21 @@ __global__ __launch_bounds__(256, MINB) void k_dgemm_mfma(GemmArgs g) {
     // column l % 16 of its 16 x 16 tile.
     const T alpha = (T)g.alpha, beta = (T)g.beta;
     if (SPLIT) {
-        // Partial sums, row-major: 16 lanes store 16 consecutive columns.
-        const int64_t ldp = (int64_t)g.tiles_n * BN;
-        T *P = static_cast<T *>(g.part) + (int64_t)split * g.tiles_m * BM * ldp;
+        // Partial sums in the accumulators' own order: per 16 columns and
+        // 64 rows, four consecutive 64-lane vectors.
+        typename Mfma<T>::acc_t *P = static_cast<typename Mfma<T>::acc_t *>(g.part) +
+                                     (((int64_t)split * g.tiles_m + tm) * g.tiles_n + tn) * 4096 + lane;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t col = (int64_t)tn * BN + wn * 64 + j * 16 + l16;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int64_t row = (int64_t)tm * BM + wm * 64 + i * 16 + Mfma<T>::row(e, lk);
-                    P[row * ldp + col] = acc[i][j][e];
-                }
-            }
+            for (int j = 0; j < NT; ++j) P[(((wn * NT + j) * 2 + wm) * 4 + i) * 64] = acc[i][j];
         return;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t col = (int64_t)tn * BN + wn * 64 + j * 16 + l16;
+        for (int j = 0; j < NT; ++j) {
+            const int64_t col = (int64_t)tn * BN + wn * 16 * NT + j * 16 + l16;
             if (col >= g.N) continue;
             const int2 cm = g.cmap[col];
 #pragma unroll
@@ -324,27 +339,53 @@ __global__ __launch_bounds__(256, MINB) void k_dgemm_mfma(GemmArgs g) {
 }
 
 // Split-k epilogue: C(row, col) = beta C + alpha * (sum of the partials in
-// split order), written into C's blocks like the GEMM epilogue; one thread
-// per element, consecutive threads on consecutive columns.
+// split order), written into C's blocks.  One wave per 64 x 16 strip of a
+// tile: it adds the strip's partials as the GEMM's lanes
+// held them (32 bytes per lane, contiguous), turns the sums through LDS and
+// writes C with consecutive lanes on consecutive rows of a column, the order
+// of C's blocks.  Bound by HBM (the partials are read once).
 template <class T>
-__global__ __launch_bounds__(256) void k_splitk_reduce(GemmArgs g) {
+__global__ __launch_bounds__(64) void k_splitk_reduce(GemmArgs g) {
+    typedef typename Mfma<T>::acc_t V;
+    __shared__ T s_out[16][65];
     const T alpha = (T)g.alpha, beta = (T)g.beta;
-    const int64_t ldp = (int64_t)g.tiles_n * BN;
-    const int64_t plane = (int64_t)g.tiles_m * BM * ldp;
-    const int64_t n = g.M * g.N;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t row = t / g.N, col = t - row * g.N;
-        const T *p = static_cast<const T *>(g.part) + row * ldp + col;
-        T v = p[0];
-        for (int sp = 1; sp < g.splits; ++sp) v += p[sp * plane];
-        const int2 rm = g.rmap[row], cm = g.cmap[col];
-        const int64_t bidx = (int64_t)rm.x * g.c_nbc + cm.x;
-        const int32_t blk = g.c_map ? g.c_map[bidx] : (int32_t)bidx;
-        if (blk < 0) continue;
-        T *dst = static_cast<T *>(g.C) + g.c_blk_off[blk] + rm.y + (int64_t)g.c_rbs[rm.x] * cm.y;
-        const T prod = alpha * v;
-        *dst = (beta == T(0)) ? prod : fma(beta, *dst, prod);
+    const int lane = threadIdx.x, l16 = lane & 15, lk = lane >> 4;
+    const int64_t strips = (int64_t)g.tiles_m * g.tiles_n * 16;
+    const int64_t plane = (int64_t)g.tiles_m * g.tiles_n * 4096;
+    for (int64_t st = blockIdx.x; st < strips; st += gridDim.x) {
+        const int64_t tile = st >> 4;
+        const int part = (int)st & 15;  // 16 columns (part / 2) of one half of the rows (part % 2)
+        const int64_t row0 = tile / g.tiles_n * BM + (part & 1) * 64;
+        const int64_t col0 = tile % g.tiles_n * BN + (part >> 1) * 16;
+        if (row0 >= g.M || col0 >= g.N) continue;
+        const V *p = static_cast<const V *>(g.part) + tile * 4096 + part * 256 + lane;
+        V v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = p[i * 64];
+        for (int sp = 1; sp < g.splits; ++sp) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] += p[sp * plane + i * 64];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s_out[l16][16 * i + Mfma<T>::row(e, lk)] = v[i][e];
+        __syncthreads();
+        const int64_t row = row0 + lane;
+        const bool in = row < g.M;
+        const int2 rm = in ? g.rmap[row] : make_int2(0, 0);
+        const int ld = in ? g.c_rbs[rm.x] : 0;
+        const int ncol = (int)min((int64_t)16, g.N - col0);
+        for (int c = 0; c < ncol; ++c) {
+            const int2 cm = g.cmap[col0 + c];
+            const int64_t bidx = (int64_t)rm.x * g.c_nbc + cm.x;
+            const int32_t blk = !in ? -1 : g.c_map ? g.c_map[bidx] : (int32_t)bidx;
+            if (blk < 0) continue;
+            T *dst = static_cast<T *>(g.C) + g.c_blk_off[blk] + rm.y + (int64_t)ld * cm.y;
+            const T prod = alpha * s_out[c][lane];
+            *dst = (beta == T(0)) ? prod : fma(beta, *dst, prod);
+        }
+        __syncthreads();  // the strip has been written before s_out is reused
     }
 }
 
@@ -394,10 +435,49 @@ int merge_panel(const bsmm_matrix_s *M, T *panel, int64_t ld, const char *what, 
                            M->d_row_off(), M->d_col_off(), M->d_row_ptr(), M->d_col_ind(), M->d_blk_off(),
                            (const T *)M->d_raw(), panel, ld);
     else
-        hipLaunchKernelGGL(k_merge_block<T>, dim3(grid_of(M->nnzb, 4)), dim3(256), 0, s, M->nbr, M->nnzb,
-                           M->d_rbs(), M->d_cbs(), M->d_row_off(), M->d_col_off(), M->d_row_ptr(),
+        hipLaunchKernelGGL(k_merge_block<T>, dim3(grid_of(M->nnzb, 4)), dim3(256), 0, s, M->nbr,
+                           M->full() ? M->nbc : 0, M->nnzb, M->d_rbs(), M->d_cbs(), M->d_row_off(), M->d_col_off(), M->d_row_ptr(),
                            M->d_col_ind(), M->d_blk_off(), (const T *)M->d_raw(), panel, ld);
     return launch_check(what);
+}
+
+// Zeros in a panel of ld x ncols ahead of M's merge: the padding when M
+// stores every block, else everything.
+template <class T>
+int zero_panel(const bsmm_matrix_s *M, T *panel, int64_t ld, int64_t ncols, hipStream_t s) {
+    if (!M->full()) return fill_zero_bytes(panel, sizeof(T) * ld * ncols, s);
+    if (ld == M->rows() && ncols == M->cols()) return BSMM_OK;
+    const int64_t first = ld == M->rows() ? M->cols() : 0;  // no rows to pad: only the last columns
+    hipLaunchKernelGGL(k_zero_padding<T>, dim3(grid_of(ncols - first, 1)), dim3(256), 0, s, panel + first * ld, ld,
+                       ncols - first, M->rows(), M->cols() - first);
+    return launch_check("zero_padding");
+}
+
+// Parts of k for an output of `tiles` tiles of `ktiles` k steps on `slots`
+// resident workgroups: the count with the lowest estimated time, in units of
+// one k step of a resident workgroup (4 us in FP64).  All workgroups take
+// ceil(tiles * S / slots) rounds of ceil(ktiles / S) k steps, plus about
+// three for a workgroup's start and end; S > 1 also writes and reads S
+// partial outputs (part_bytes each, 4.5 TB/s).  Each part holds at least
+// eight k steps, the partials at most max_bytes.  Aiming at two rounds whatever
+// the tile count left the last one nearly empty: 1408 x 1408 (121 tiles)
+// with k = 247,808 took 19.0 ms in 9 parts (2.13 rounds, three in effect)
+// and takes 15.0 ms in 21; 210 tiles of k = 2300 took 346 + 86 us in 5
+// parts and 329 + 28 us in 2.
+int64_t gemm_splits(int64_t tiles, int64_t ktiles, int64_t slots, int64_t part_bytes, int64_t max_bytes) {
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>({ktiles / 8, 64, max_bytes / part_bytes}));
+    int64_t best = 1;
+    double best_cost = 0.0;
+    for (int64_t S = 1; S <= most; ++S) {
+        const double rounds = (double)ceil_div(tiles * S, slots);
+        double cost = rounds * (double)(ceil_div(ktiles, S) + 3);
+        if (S > 1) cost += 2.0 * (double)(S * part_bytes) / 4.5e12 / 4e-6 + 2.0;
+        if (S == 1 || cost < 0.98 * best_cost) {
+            best = S;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 template <class T>
@@ -417,8 +497,8 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
     BSMM_TRY(ap.reserve(sizeof(T) * Mp * Kp, s));
     BSMM_TRY(bp.reserve(sizeof(T) * Kp * Np, s));
     // Panels need zeros where blocks are absent and in the padding.
-    if (!A->full() || Mp != M || Kp != K) BSMM_TRY(fill_zero_bytes(ap.p, sizeof(T) * Mp * Kp, s));
-    if (!B->full() || Kp != K || Np != N) BSMM_TRY(fill_zero_bytes(bp.p, sizeof(T) * Kp * Np, s));
+    BSMM_TRY(zero_panel<T>(A, ap.as<T>(), Mp, Kp, s));
+    BSMM_TRY(zero_panel<T>(B, bp.as<T>(), Kp, Np, s));
     if (A->nnzb > 0) BSMM_TRY(merge_panel<T>(A, ap.as<T>(), Mp, "merge_A", s));
     if (B->nnzb > 0) BSMM_TRY(merge_panel<T>(B, bp.as<T>(), Kp, "merge_B", s));
     const int32_t *d_cmap = nullptr;
@@ -453,16 +533,14 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
     g.c_rbs = C->d_rbs();
     g.rmap = C->d_row_map();
     g.cmap = C->d_col_map();
-    // Split k when the output tiles cannot fill the GPU (tall-and-skinny
-    // products): about two rounds of resident workgroups, each split at
-    // least 16 k tiles deep, partials at most 2 GiB.
     const int64_t slots = (int64_t)cu_count() * (KB == 32 ? 1 : 2);
-    int64_t splits = 1;
-    if (tiles < slots) {
-        splits = std::min<int64_t>(ceil_div(2 * slots, tiles), g.ktiles / 16);
-        splits = std::min<int64_t>(splits, (int64_t(1) << 31) / (int64_t)(sizeof(T) * Mp * Np));
-        splits = std::max<int64_t>(splits, 1);
+    int64_t part_cap = int64_t(1) << 31;
+    if (const ScratchArena *ar = scratch_arena()) {
+        // Allocation-free: the partials take what the panels have left.
+        part_cap = std::min<int64_t>(part_cap, (int64_t)(ar->cap - ar->used) - 512);
+        part_cap = std::max<int64_t>(part_cap, 0);
     }
+    int64_t splits = gemm_splits(tiles, g.ktiles, slots, (int64_t)sizeof(T) * Mp * Np, part_cap);
     DevBuf part;
     if (splits > 1) {
         g.kt_per = (int)ceil_div(g.ktiles, splits);
@@ -475,16 +553,16 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
         KernelTimer kt(0, s);
         const dim3 grid((unsigned)(tiles * splits));
         if (splits > 1) {
-            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 1, true>), grid, dim3(256), 0, s, g);
-            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, true>), grid, dim3(256), 0, s, g);
+            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 4, 1, true>), grid, dim3(256), 0, s, g);
+            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, 4, true>), grid, dim3(512), 0, s, g);
         } else {
-            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 1, false>), grid, dim3(256), 0, s, g);
-            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, false>), grid, dim3(256), 0, s, g);
+            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 4, 1, false>), grid, dim3(256), 0, s, g);
+            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, 4, false>), grid, dim3(512), 0, s, g);
         }
     }
     BSMM_TRY(launch_check("dgemm_mfma"));
     if (splits == 1) return BSMM_OK;
-    hipLaunchKernelGGL(k_splitk_reduce<T>, dim3(grid_of(M * N, 256, 8192)), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_splitk_reduce<T>, dim3(grid_of(tiles * 16, 1)), dim3(64), 0, s, g);
     return launch_check("splitk_reduce");
 }
 

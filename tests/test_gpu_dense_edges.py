@@ -1,0 +1,74 @@
+"""Edges of the dense path: outputs and depths around the 128-wide tiles,
+padding zeros, one part of k or several (a few output tiles with a long k),
+accumulation into C, sparse C patterns, FP64 and FP32."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from synth import make_matrix, rng_of
+
+from tests.helpers import check_against_oracle, gpu_multiply
+
+pytestmark = pytest.mark.gpu
+
+
+def _cover(total, sizes, rng):
+    out = []
+    while sum(out) < total:
+        out.append(min(int(rng.choice(sizes)), total - sum(out)))
+    return np.asarray(out, np.int32)
+
+
+@pytest.mark.parametrize("beta", [0.0, -2.0])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (127, 129, 15), (128, 128, 16), (129, 127, 17), (130, 250, 300),
+                                   (64, 40, 2100), (257, 1, 513)])
+def test_tile_edges_exact(m, n, k, beta):
+    """Integer values: exact for any split of k."""
+    rng = rng_of(m + n + k)
+    rs, ks, ns = (_cover(x, [9, 22, 32], rng) for x in (m, k, n))
+    A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, ns, 1.0, "int")
+    C = make_matrix(rng, rs, ns, 1.0, "int")
+    X, st = gpu_multiply(3.0, A, B, beta, C, path="dense")
+    assert st["path"] == 2
+    check_against_oracle(X, orc.multiply(3.0, A, B, beta, C), 0.0)
+
+
+@pytest.mark.parametrize("occ", [0.4, 1.0])
+def test_split_k_into_blocks(occ):
+    """Nine tiles with a long k (split), absent blocks of A and B read as
+    zero and a C that stores only the product's blocks."""
+    rng = rng_of(int(10 * occ))
+    rs, ks, ns = _cover(300, [5, 13, 23], rng), _cover(5000, [23, 32], rng), _cover(333, [5, 13, 23], rng)
+    A, B = make_matrix(rng, rs, ks, occ * 0.05, "int"), make_matrix(rng, ks, ns, occ, "int")
+    X, _ = gpu_multiply(1.0, A, B, 0.0, path="dense")
+    check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
+
+
+def test_split_k_f32():
+    from tests.test_gpu_f32 import _as_f32, _f32_multiply
+    rng = rng_of(9)
+    rs, ks = _cover(200, [22], rng), _cover(4000, [22], rng)
+    A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
+    X, _ = _f32_multiply(1.0, _as_f32(A), _as_f32(B), 0.0, path="dense")
+    check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)  # sums below 2^24: exact in FP32
+
+
+def test_split_k_within_the_scratch_region():
+    """The allocation-free multiply of a long k: the parts of k shrink to
+    what the scratch region holds beside the panels."""
+    from tests.helpers import lib, set_path
+    rng = rng_of(12)
+    rs, ks = _cover(640, [32], rng), _cover(6000, [32], rng)
+    A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
+    b = lib()
+    set_path("dense")
+    try:
+        MA, MB = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B)
+        MC = b.Matrix.from_blocks(make_matrix(rng, rs, rs, 1.0, "zeros"))
+        b.bsmm_multiply_noalloc(1.0, MA.handle, MB.handle, 0.0, MC.handle)
+        X = MC.to_host()
+        for M in (MA, MB, MC):
+            M.close()
+    finally:
+        set_path()
+    check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
