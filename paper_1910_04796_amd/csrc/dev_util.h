@@ -16,6 +16,18 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
     return l == 0 ? 0ull : (~0ull >> (64 - l));
 }
 
+// A value that is the same on every lane, for the scalar unit.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+}
+// x[i] on the scalar unit: i is the same on every lane, and nothing writes
+// the array while the kernel runs.
+template <class T> __device__ __forceinline__ T scalar_at(const T *x, int64_t i) {
+    return reinterpret_cast<const __attribute__((address_space(4))) T *>(reinterpret_cast<uintptr_t>(x))[i];
+}
+
 // Orders the LDS traffic of one wavefront: every LDS access issued before it
 // has completed, and the compiler moves no memory access across it.  Lanes
 // of a wave execute in lockstep, so this is all a wave-private exchange

@@ -275,6 +275,7 @@ constexpr int kMaxStackK = 0xFFFF;
 // block row's share of every window found once per multiply.
 constexpr int kMaxStackCols = 8192;
 constexpr int kStackWin = 4096;
+constexpr size_t kSchedCounterBytes = 4 * 256;  // four counters, a line each
 // Product stacks of C += A*B, grouped by shape class (m, n).
 struct Stacks {
     int64_t n_runs = 0, n_prod = 0;
@@ -304,7 +305,7 @@ struct Stacks {
     DevBuf b_split;                   // int64[B.nbr * (nwin + 1)]: first entry of each B row in each window
     DevBuf sched;                     // uint64[n_sched]: scheduled runs (run << 16 | m << 8 | n)
     int64_t n_sched = 0;
-    DevBuf sched_next;                // uint64 run counter of the dynamic schedule
+    DevBuf sched_next;                // uint64 run counters of the dynamic schedule
     int n_jit = 0;                    // classes on run-time compiled kernels
     std::vector<char> class_active;   // class holds runs (any panel so far)
     std::vector<int> run_len_hint;    // mean run length per class over every panel (else empty)
@@ -378,7 +379,7 @@ struct SmmArgs {
     void *part;
     // Scheduled MFMA kernel (one launch for every class with blocks up to
     // 32 x 32): entries run << 16 | m << 8 | n in tile order; mode 0 static
-    // XCD-aware striding, 1 a run counter (*next, zeroed before the launch).
+    // XCD-aware striding, 1 run counters (next, zeroed before the launch).
     const unsigned long long *sched;
     int64_t n_sched;
     unsigned long long *next;

@@ -162,82 +162,141 @@ template <int NTILE> __device__ __forceinline__ int tile_row(int t, int r) {
     return (t | 1) < NTILE ? 32 * (t >> 1) + 2 * r + (t & 1) : 16 * t + r;
 }
 
-// The operands of MFMA steps s = 0, 1 of the 8 values of k from k0: lane
-// group lk supplies k = k0 + 2 lk + s.  ext: rows (columns) of the block.
-template <class T, int NTILE, OperandLayout LAY>
-__device__ __forceinline__ void load_operand(const T *x, int ext, int k, int k0, int lr, int lk,
-                                             T (&f)[2][NTILE]) {
-    const int kb = k0 + 2 * lk;
-    if (LAY == kAlongTile) {
+// Byte offsets of one operand's loads from its chunk of 8 values of k; ext
+// is the block's row (column) count, k the product's depth.  Lane group lk
+// supplies k = 2 lk + s of the chunk to MFMA step s.  (Past the last value
+// of k the offsets repeat it; mfma_chunk zeroes those values.)
+template <class T, int NTILE, OperandLayout LAY> struct OperandOffsets {
+    // kAlongTile: rows of value s = 0; kAlongK: see of_depth.
+    uint32_t at[NTILE];
+    uint32_t step;  // bytes from one value of k to the next
+    __device__ __forceinline__ void init(int ext, int lr, int lk) {
+        if (LAY == kAlongTile) {
+            step = (uint32_t)ext * sizeof(T);
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const T *xk = x + min(kb + s, k - 1) * ext;
+            for (int t = 0; t < NTILE; ++t) at[t] = 2 * lk * step + row(t, ext, lr) * (uint32_t)sizeof(T);
+        } else {
+            step = sizeof(T);
 #pragma unroll
-            for (int t = 0; t + 1 < NTILE; t += 2) {
-                // The pair may end one past the block: every data buffer
-                // holds one element more than its blocks.
-                Mfma<T>::load2(xk + min(16 * t + 2 * lr, ext - 1), f[s][t], f[s][t + 1]);
-            }
-            if (NTILE & 1) f[s][NTILE - 1] = xk[min(16 * (NTILE - 1) + lr, ext - 1)];
+            for (int t = 0; t < NTILE; ++t) at[t] = row(t, ext, lr);  // times the depth, per product
         }
-    } else {
-#pragma unroll
-        for (int t = 0; t < NTILE; ++t)
-            Mfma<T>::load2(x + min(tile_row<NTILE>(t, lr), ext - 1) * k + min(kb, k - 1), f[0][t], f[1][t]);
     }
-    if (k0 + 8 > k) {
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int t = 0; t < NTILE; ++t) f[s][t] = kb + s < k ? f[s][t] : T(0);
+    // The row that lane index lr of tile t loads (a pair's first row for
+    // tiles that share their loads), inside the block.
+    static __device__ __forceinline__ uint32_t row(int t, int ext, int lr) {
+        if (LAY == kAlongTile) return min((t | 1) < NTILE ? 16 * (t & ~1) + 2 * lr : 16 * t + lr, ext - 1);
+        return min(tile_row<NTILE>(t, lr), ext - 1);
     }
-}
+    // base: the block's chunk; left: values of k from the chunk's first one.
+    __device__ __forceinline__ void load(const char *base, int k, int left, int lk, T (&f)[2][NTILE]) const {
+        if (LAY == kAlongTile) {
+            uint32_t back0 = 0, back1 = 0;
+            if (left < 8) {
+                // Steps back from a value past the block to its last one.
+                back0 = (uint32_t)max(2 * lk + 1 - left, 0) * step;
+                back1 = (uint32_t)max(2 * lk + 2 - left, 0) * step;
+            }
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const uint32_t add = s * step - (s ? back1 : back0);
+#pragma unroll
+                for (int t = 0; t + 1 < NTILE; t += 2) {
+                    // The pair may end one past the block: every data buffer
+                    // holds one element more than its blocks.
+                    Mfma<T>::load2(reinterpret_cast<const T *>(base + (at[t] + add)), f[s][t], f[s][t + 1]);
+                }
+                if (NTILE & 1) f[s][NTILE - 1] = *reinterpret_cast<const T *>(base + (at[NTILE - 1] + add));
+            }
+        } else {
+            const uint32_t kk = left < 8 ? min(2 * lk, left - 1) : 2 * lk;
+#pragma unroll
+            for (int t = 0; t < NTILE; ++t)
+                Mfma<T>::load2(reinterpret_cast<const T *>(base + (at[t] * (uint32_t)k + kk) * (uint32_t)sizeof(T)),
+                               f[0][t], f[1][t]);
+        }
+    }
+};
+
+// One chunk of 8 values of k of a product: its operands, and how many values
+// from the chunk's first one lie inside the block.
+template <class T, int MT, int NT> struct Chunk {
+    T a[2][MT], b[2][NT];
+    int left;
+};
 
 template <class T, int MT, int NT>
-__device__ __forceinline__ void mfma_chunk(const T (&af)[2][MT], const T (&bf)[2][NT],
-                                           typename Mfma<T>::acc_t (&acc)[MT][NT]) {
+__device__ __forceinline__ void mfma_chunk(Chunk<T, MT, NT> &c, int lk, typename Mfma<T>::acc_t (&acc)[MT][NT]) {
+    if (c.left < 8) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const bool in = 2 * lk + s < c.left;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) c.a[s][i] = in ? c.a[s][i] : T(0);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) c.b[s][j] = in ? c.b[s][j] : T(0);
+        }
+    }
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::step(af[s][i], bf[s][j], acc[i][j]);
+            for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::step(c.a[s][i], c.b[s][j], acc[i][j]);
 }
 
 // Products [q0, q1) of one run into the MT x NT accumulator tiles of an
-// m x n C block.
+// m x n C block (q0, q1, m and n the same on every lane: descriptors, depths
+// and block addresses stay on the scalar unit, a lane adds its offset).  The
+// products' chunks follow one another without a break: the operands of the
+// next chunk (of the next product where one ends) are on their way while a
+// chunk is multiplied, the descriptor of the product after it one product
+// earlier.
 template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, int64_t q0, int64_t q1,
                                               typename Mfma<T>::acc_t (&acc)[MT][NT]) {
+    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2 *prods = reinterpret_cast<const u64x2 *>(p.prods);
     const int lane = lane_id();
     const int lr = lane & 15, lk = lane >> 4;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::zero();
-    const T *A = static_cast<const T *>(LA == kAlongK ? p.A_t : p.A);
-    const T *B = static_cast<const T *>(LB == kAlongTile ? p.B_t : p.B);
-    // The next product's descriptor is loaded one product ahead.
-    ulonglong2 nxt = q0 < q1 ? p.prods[q0] : make_ulonglong2(0ull, 0ull);
-    for (int64_t q = q0; q < q1; ++q) {
-        const ulonglong2 pr = nxt;
-        if (q + 1 < q1) nxt = p.prods[q + 1];
-        const T *a = A + (int64_t)(pr.x & ((1ull << 48) - 1));
-        const int k = (int)(pr.x >> 48);
-        const T *b = B + (int64_t)pr.y;
-        for (int k0 = 0; k0 < k; k0 += 16) {
-            T a0[2][MT], b0[2][NT], a1[2][MT], b1[2][NT];
-            const bool two = k0 + 8 < k;
-            load_operand<T, MT, LA>(a, m, k, k0, lr, lk, a0);
-            load_operand<T, NT, LB>(b, n, k, k0, lr, lk, b0);
-            if (two) {
-                load_operand<T, MT, LA>(a, m, k, k0 + 8, lr, lk, a1);
-                load_operand<T, NT, LB>(b, n, k, k0 + 8, lr, lk, b1);
-            }
-            mfma_chunk<T, MT, NT>(a0, b0, acc);
-            if (two) mfma_chunk<T, MT, NT>(a1, b1, acc);
+    if (q0 >= q1) return;
+    const char *A = static_cast<const char *>(LA == kAlongK ? p.A_t : p.A);
+    const char *B = static_cast<const char *>(LB == kAlongTile ? p.B_t : p.B);
+    OperandOffsets<T, MT, LA> oa;
+    OperandOffsets<T, NT, LB> ob;
+    oa.init(m, lr, lk);
+    ob.init(n, lr, lk);
+    u64x2 pr = scalar_at(prods, q0), nxt = scalar_at(prods, min(q0 + 1, q1 - 1));
+    const char *a = A + (pr.x & ((1ull << 48) - 1)) * sizeof(T), *b = B + pr.y * sizeof(T);
+    int k = (int)(pr.x >> 48), left = k;
+    int64_t q = q0;
+    auto load = [&](Chunk<T, MT, NT> &c) {
+        oa.load(a, k, left, lk, c.a);
+        ob.load(b, k, left, lk, c.b);
+        c.left = left;
+        left -= 8;
+        a += 8 * oa.step;
+        b += 8 * ob.step;
+        if (left <= 0) {
+            ++q;
+            a = A + (nxt.x & ((1ull << 48) - 1)) * sizeof(T);
+            b = B + nxt.y * sizeof(T);
+            k = left = (int)(nxt.x >> 48);
+            nxt = scalar_at(prods, min(q + 1, q1 - 1));
         }
-    }
+    };
+    Chunk<T, MT, NT> cur, next;
+    load(cur);
+    bool more;
+    do {
+        more = q < q1;
+        if (more) load(next);
+        mfma_chunk(cur, lk, acc);
+        cur = next;
+    } while (more);
 }
 
 // C block (column-major, ld = m) <- beta C + alpha acc, or the unscaled
@@ -279,7 +338,7 @@ __device__ __forceinline__ double mfma_store(T *c, int m, int n,
 template <class T, int MT, int NT>
 __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + wave_id();
+    const int64_t wid = (int64_t)blockIdx.x * (blockDim.x / kWave) + uniform(wave_id());
     const int m = p.m, n = p.n;
     const int S = p.split > 1 ? p.split : 1;
     const int64_t items = (p.run_end - p.run_begin) * S;
@@ -288,7 +347,7 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
         // [len sg / S, len (sg + 1) / S) of the run.
         const int64_t r = p.run_begin + it / S;
         const int sg = (int)(it % S);
-        const int64_t rq0 = p.run_ptr[r], len = p.run_ptr[r + 1] - rq0;
+        const int64_t rq0 = scalar_at(p.run_ptr, r), len = scalar_at(p.run_ptr, r + 1) - rq0;
         const int64_t q0 = rq0 + len * sg / S, q1 = rq0 + len * (sg + 1) / S;
         typename Mfma<T>::acc_t acc[MT][NT];
         mfma_products<T, MT, NT, kAlongTile, kAlongK>(p, m, n, q0, q1, acc);
@@ -296,7 +355,7 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
             mfma_store<T, MT, NT, false>(static_cast<T *>(p.part) + it * (int64_t)m * n, m, n, acc, true,
                                          T(0), T(0));
         else
-            mfma_store<T, MT, NT, false>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc, false,
+            mfma_store<T, MT, NT, false>(static_cast<T *>(p.C) + scalar_at(p.run_coff, r), m, n, acc, false,
                                          (T)p.alpha, (T)p.beta);
     }
 }
@@ -311,14 +370,25 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
 template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, int n) {
     typename Mfma<T>::acc_t acc[MT][NT];
-    mfma_products<T, MT, NT, LA, LB>(p, m, n, p.run_ptr[r], p.run_ptr[r + 1], acc);
+    mfma_products<T, MT, NT, LA, LB>(p, m, n, scalar_at(p.run_ptr, r), scalar_at(p.run_ptr, r + 1), acc);
     // One store path: the norm is summed whether or not the filter wants it.
-    const double ss = mfma_store<T, MT, NT, true>(static_cast<T *>(p.C) + p.run_coff[r], m, n, acc, false,
+    const double ss = mfma_store<T, MT, NT, true>(static_cast<T *>(p.C) + scalar_at(p.run_coff, r), m, n, acc, false,
                                                   (T)p.alpha, (T)p.beta);
     if (p.norm2 && lane_id() == 0) p.norm2[p.run_cblk[r]] = ss;
 }
 
 constexpr int kXcds = 8;
+// Counters of the dynamic order: counter c hands out every kSchedCounters-th
+// chunk.  Updates of one address follow one another about 15 ns apart, so a
+// single counter bounded launches of many short runs: {5,13,23}-blocks at
+// 25 % (48,000 runs) 505 us with two runs per update, 310 us with four
+// counters and one run; FP32 banded 10 % (1.4 M runs) 11.9 -> 9.4 ms, banded
+// 10 % 69.8 -> 68.0 ms.  Every counter serves workgroups of all XCDs: with a
+// counter per XCD the XCDs drifted apart and the 30 % product lost 5 % (639
+// -> 671 ms); more counters gain nothing (8: the same, 32: 30 % 674 ms).
+constexpr int kSchedCounters = 4;
+constexpr int kSchedCounterStride = 32;  // in 8-byte words: a line each
+static_assert(kSchedCounters * kSchedCounterStride * 8 == kSchedCounterBytes, "counter buffer");
 // Fewest runs for which the MFMA classes go through the scheduled launch.
 constexpr int64_t kSchedMinRuns = 4096;
 
@@ -327,22 +397,22 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     const int wpw = blockDim.x / kWave;
     const int64_t waves = (int64_t)gridDim.x * wpw;
     // A wave takes `chunk` consecutive entries at a time (short runs: fewer
-    // counter updates).
+    // counter updates), the first ones by its number.
     const int64_t chunk = p.sched_chunk > 1 ? p.sched_chunk : 1;
+    const int w = uniform(wave_id());
     int64_t it;
     if (p.sched_mode == 0) {
         const int G = gridDim.x, xcd = blockIdx.x % kXcds, loc = blockIdx.x / kXcds;
         const int before = xcd * (G / kXcds) + min(xcd, G % kXcds);
-        it = ((int64_t)(before + loc) * wpw + wave_id()) * chunk;
+        it = ((int64_t)(before + loc) * wpw + w) * chunk;
     } else {
-        unsigned long long t = 0;
-        if (lane_id() == 0) t = atomicAdd(p.next, (unsigned long long)chunk);
-        it = (int64_t)__shfl(t, 0, kWave);
+        it = ((int64_t)blockIdx.x * wpw + w) * chunk;
     }
+    const int c = blockIdx.x / kXcds % kSchedCounters;
     while (it < p.n_sched) {
         const int64_t end = min(it + chunk, p.n_sched);
         for (int64_t i = it; i < end; ++i) {
-            const unsigned long long e = p.sched[i];
+            const unsigned long long e = scalar_at(p.sched, i);
             const int64_t r = (int64_t)(e >> 16);
             const int m = (int)((e >> 8) & 255), n = (int)(e & 255);
             if (m > 16) {
@@ -357,8 +427,8 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
             it += waves * chunk;
         } else {
             unsigned long long t = 0;
-            if (lane_id() == 0) t = atomicAdd(p.next, (unsigned long long)chunk);
-            it = (int64_t)__shfl(t, 0, kWave);
+            if (lane_id() == 0) t = atomicAdd(&p.next[c * kSchedCounterStride], 1ull);
+            it = (waves + uniform((int64_t)t) * kSchedCounters + c) * chunk;
         }
     }
 }
@@ -412,7 +482,7 @@ __global__ __launch_bounds__(256) void k_transpose_blocks(int32_t nbr, const int
     }
 }
 
-__global__ void k_zero_u64(unsigned long long *p) { *p = 0ull; }
+__global__ void k_zero_counters(unsigned long long *p) { p[threadIdx.x * kSchedCounterStride] = 0ull; }
 
 // Epilogue of split runs: C block of run r = beta C + alpha * (sum of its
 // segments' partial blocks in segment order); one thread per element.
@@ -536,14 +606,15 @@ SmmParams plain_params(int m, int n) {
     return SmmParams{t, t, 0, 0};
 }
 
-// The plain path's launch: the MFMA kernel for blocks of up to 64 x 64 with
-// at least 64 elements and 8-deep products, the register-tile rule else.
-// Over the 1,992 timed shapes and run lengths of the tuning database the
-// MFMA kernel takes 0.36 of the register tiles' time (geometric mean); it
-// loses where a 16 x 16 tile holds few elements (5 x 5 x 5: 1.2 to 1.7
-// times slower) and on 4- to 7-deep products (23 x 23 x 5: 1.3 to 1.8).
+// The plain path's launch: the MFMA kernel for blocks of up to 64 x 64 whose
+// tiles are worth a wave (at least 25 elements and 200 multiply-adds per
+// product), the register-tile rule else.  MFMA over register tiles, 15,000
+// and more runs of 1 / 8 / 32 products: 13 x 13 x 5 0.68 / 0.55 / 0.50,
+// 6 x 6 x 6 0.80 / 0.84 / 0.79, 5 x 5 x 23 1.03 / 0.73 / 0.70, but 5 x 5 x 5
+// 1.52 / 1.22 / 1.24, 4 x 4 x 32 1.38 / 1.07 / 1.09, 4 x 4 x 4 2.9 / 2.0 / 2.3.
 static SmmParams plain_launch(int m, int n, int k) {
-    if (m <= 64 && n <= 64 && m * n >= 64 && k >= 8) return SmmParams{kMfmaTile, kMfmaTile, 0, 4};
+    if (m <= 64 && n <= 64 && m * n >= 25 && (int64_t)m * n * k >= 200)
+        return SmmParams{kMfmaTile, kMfmaTile, 0, 4};
     return plain_params(m, n);
 }
 
@@ -624,7 +695,17 @@ unsigned smm_grid(const SmmLaunch &L, int64_t nruns) {
     const int64_t waves_needed = ceil_div(nruns * std::max(L.args.split, 1), L.args.G);
     // At most 32 waves per CU (256 CUs) in the grid, whatever the waves per
     // workgroup; the kernels stride over the remaining runs.
-    const int64_t wg_cap = 256 * 32 / std::max(L.waves, 1);
+    int64_t wg_cap = 256 * 32 / std::max(L.waves, 1);
+    if (is_sched_kernel(L.fn)) {
+        // Only resident workgroups: later ones would begin with the runs
+        // that their numbers stand for when the others are far ahead.
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, L.fn, 64 * L.waves, 0) != hipSuccess || per_cu < 1) {
+            (void)hipGetLastError();
+            per_cu = 5;
+        }
+        wg_cap = (int64_t)cu_count() * per_cu;
+    }
     return grid_of(waves_needed, L.waves, wg_cap);
 }
 
@@ -646,8 +727,8 @@ int launch_smm(SmmLaunch L, const void *A, const void *B, void *C, const int64_t
         return launch_jit_smm(L.jit_fn, smm_grid(L, re - rb), L.waves, A, B, C, run_coff, run_ptr, prods,
                               rb, re, alpha, beta, s);
     if (is_sched_kernel(L.fn) && a.sched_mode == 1) {
-        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, s, a.next);
-        BSMM_TRY(launch_check("zero_u64"));
+        hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(kSchedCounters), 0, s, a.next);
+        BSMM_TRY(launch_check("zero_counters"));
     }
     {
         KernelTimer kt(1, s);
@@ -765,7 +846,9 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     LaunchList &launches = ex->launches;
     // Tuned path with a tile size: the MFMA classes of blocks up to 32 x 32
     // whose runs need no splitting go to one scheduled launch.
-    const bool sched_on = tuned && chunk <= 0 && options().stack_tile > 0 &&
+    // (the plain path too, except in the scratch region, which the schedule
+    // would share with the products: its classes keep their own launches).
+    const bool sched_on = (tuned || !scratch_arena()) && chunk <= 0 && options().stack_tile > 0 &&
                           (int)st.class_prod_begin.size() == st.n_classes + 1;
     std::vector<char> eligible(st.n_classes, 0);
     for (int cl = 0; cl < st.n_classes; ++cl) {
@@ -827,7 +910,8 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
             if (!eligible[cl]) continue;
             const int m = st.row_sizes[cl / st.ncs], n = st.col_sizes[cl % st.ncs];
             SmmLaunch L;
-            BSMM_TRY(plan_smm(select_params(m, n, krep, rlen[cl]), m, n, kmax, C->dtype, &L));
+            BSMM_TRY(plan_smm(tuned ? select_params(m, n, krep, rlen[cl]) : plain_launch(m, n, krep), m, n, kmax,
+                              C->dtype, &L));
             launches.push_back({L, {st.class_begin[cl], st.class_begin[cl + 1]}});
             eligible[cl] = 0;
         }
@@ -857,10 +941,12 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         L.args.sched_mode = options().stack_sched;
         L.args.norm2 = norm_sink();
         L.args.run_cblk = st.run_cblk.as<int64_t>();
-        // About 32 products per counter update: runs of one product go
-        // 16 at a time, runs of 32 or more one at a time.
+        // About four products per counter update: runs of one product go
+        // four at a time, runs of four or more one at a time (banded 1 %,
+        // two products per run: 1.26 / 1.25 / 1.26 / 1.29 / 1.33 ms for 1 / 2
+        // / 4 / 8 / 16 runs per update).
         const int64_t mean_len = std::max<int64_t>(1, sched_prods / sched_runs);
-        L.args.sched_chunk = (int)std::min<int64_t>(16, std::max<int64_t>(1, 32 / mean_len));
+        L.args.sched_chunk = (int)std::max<int64_t>(1, 4 / mean_len);
         L.waves = 4;
         L.lds = 0;
         launches.push_back({L, {0, st.n_sched}});
@@ -969,9 +1055,9 @@ int build_graph(const LaunchList &launches, const bsmm_matrix_s *A, const bsmm_m
             // The dynamic schedule's run counter starts at zero every replay
             // (a kernel node: memset nodes are not used in the graph).
             hipKernelNodeParams zp{};
-            zp.func = (void *)k_zero_u64;
+            zp.func = (void *)k_zero_counters;
             zp.gridDim = dim3(1);
-            zp.blockDim = dim3(1);
+            zp.blockDim = dim3(kSchedCounters);
             zp.sharedMemBytes = 0;
             zp.kernelParams = &zargp;
             zp.extra = nullptr;

@@ -34,7 +34,12 @@ namespace bsmm {
 
 namespace {
 
-constexpr int kTile = 1024;         // C blocks per classification tile
+// C blocks per classification tile (one wave): smaller tiles put more waves
+// on a mid-size C (47,000 blocks: 47 waves with tiles of 1024 took 34 us in
+// the scatter, 188 waves 12 us), their histograms grow with the class count.
+constexpr int kTileFew = 256, kTileMany = 1024;
+constexpr int kSmallBlocks = 8192;  // C blocks classified by one workgroup ...
+constexpr int kSmallClasses = 64;   // ... when there are at most this many classes
 constexpr int kMaxClasses = 1024;   // distinct (m, n) shapes
 
 // A block range [pa0, pa1) of part `part` of P of A's block row `row`.
@@ -200,7 +205,7 @@ __device__ __forceinline__ int class_of(int64_t c, const int32_t *c_row, const i
 // One wave per tile of kTile C blocks: per-class counts of the blocks that
 // receive products and per-class sums of their products, written
 // class-major (hist[cl * ntiles + tile], hist_p likewise).
-__global__ __launch_bounds__(256) void k_class_hist(int64_t c_base, int64_t nnzb, int64_t ntiles,
+__global__ __launch_bounds__(256) void k_class_hist(int64_t c_base, int64_t nnzb, int64_t ntiles, int kTile,
                                                     const int64_t *c_count, const int32_t *c_row,
                                                     const int32_t *c_ci, const int32_t *rsi,
                                                     const int32_t *csi, int ncs, int ncl,
@@ -236,7 +241,7 @@ __global__ __launch_bounds__(256) void k_class_hist(int64_t c_base, int64_t nnzb
 
 // Stable scatter of the runs into class-major order.
 __global__ __launch_bounds__(256) void k_class_scatter(
-    int64_t c_base, int64_t nnzb, int64_t ntiles, const int64_t *c_count, const int32_t *c_row,
+    int64_t c_base, int64_t nnzb, int64_t ntiles, int kTile, const int64_t *c_count, const int32_t *c_row,
     const int32_t *c_ci, const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi,
     int ncs, int ncl, const int64_t *hoff, int64_t *run_cblk, int32_t *run_class,
     int64_t *run_coff, int64_t *run_cnt, int64_t *run_of_c) {
@@ -273,6 +278,83 @@ __global__ __launch_bounds__(256) void k_class_scatter(
                 wave_lds_sync();
                 pending &= ~mask;
             }
+        }
+    }
+}
+
+// Classification of at most kSmallBlocks C blocks and kSmallClasses classes
+// by one workgroup: what the per-tile histograms, their scans, the class
+// boundaries, the scatter and the scan of the product counts give (cb: first
+// run of every class, then its first product), in one launch instead of
+// eight; such multiplies are bound by the number of launches.  Wave w takes
+// the w-th sixteenth of the blocks; counts and product sums per (class, wave)
+// are scanned class by class, then every wave walks its blocks again.
+__global__ __launch_bounds__(1024) void k_classify_small(
+    int64_t c_base, int nblk, const int64_t *c_count, const int32_t *c_row, const int32_t *c_ci,
+    const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi, int ncs, int ncl, int64_t *cb,
+    int64_t *run_cblk, int32_t *run_class, int64_t *run_coff, int64_t *run_ptr, int64_t *run_of_c) {
+    constexpr int W = 16;
+    __shared__ unsigned long long s_run[kSmallClasses * W], s_prod[kSmallClasses * W];
+    __shared__ int64_t red[16];
+    const int t = threadIdx.x, w = wave_id(), lane = lane_id();
+    s_run[t] = s_prod[t] = 0;
+    __syncthreads();
+    const int per = (nblk + W - 1) / W;
+    const int64_t b0 = c_base + min(w * per, nblk), b1 = c_base + min((w + 1) * per, nblk);
+    for (int64_t c = b0 + lane; c < b1; c += kWave) {
+        const int64_t n = c_count[c];
+        if (n > 0) {
+            const int cl = class_of(c, c_row, c_ci, rsi, csi, ncs);
+            atomicAdd(&s_run[cl * W + w], 1ull);
+            atomicAdd(&s_prod[cl * W + w], (unsigned long long)n);
+        }
+    }
+    __syncthreads();
+    int64_t runs, prods;
+    const int64_t r0 = block_exclusive_scan((int64_t)s_run[t], red, &runs);
+    const int64_t p0 = block_exclusive_scan((int64_t)s_prod[t], red, &prods);
+    s_run[t] = (unsigned long long)r0;
+    s_prod[t] = (unsigned long long)p0;
+    if (t % W == 0 && t / W < ncl) {
+        cb[t / W] = r0;
+        cb[ncl + 1 + t / W] = p0;
+    }
+    if (t == 0) {
+        cb[ncl] = runs;
+        cb[2 * ncl + 1] = prods;
+        run_ptr[runs] = prods;
+    }
+    __syncthreads();
+    for (int64_t base = b0; base < b1; base += kWave) {
+        const int64_t c = base + lane;
+        const bool inb = c < b1;
+        const int64_t cnt = inb ? c_count[c] : 0;
+        const bool valid = cnt > 0;
+        const int cl = valid ? class_of(c, c_row, c_ci, rsi, csi, ncs) : -1;
+        if (inb && !valid) run_of_c[c] = -1;
+        uint64_t pending = __ballot(valid);
+        while (pending) {
+            const int lead = __shfl(cl, __ffsll((unsigned long long)pending) - 1, kWave);
+            const bool mine = valid && cl == lead;
+            const uint64_t mask = __ballot(mine);
+            const int64_t inc = wave_inclusive_scan(mine ? cnt : (int64_t)0);
+            const int64_t first_r = (int64_t)s_run[lead * W + w], first_p = (int64_t)s_prod[lead * W + w];
+            if (mine) {
+                const int64_t r = first_r + __popcll(mask & lanemask_lt());
+                run_cblk[r] = c;
+                run_class[r] = cl;
+                run_coff[r] = c_blk_off[c];
+                run_ptr[r] = first_p + inc - cnt;
+                run_of_c[c] = r;
+            }
+            const int64_t add = __shfl(inc, kWave - 1, kWave);
+            wave_lds_sync();
+            if (lane == 0) {
+                s_run[lead * W + w] = (unsigned long long)(first_r + __popcll(mask));
+                s_prod[lead * W + w] = (unsigned long long)(first_p + add);
+            }
+            wave_lds_sync();
+            pending &= ~mask;
         }
     }
 }
@@ -497,7 +579,7 @@ int build_schedule(const bsmm_matrix_s *C, Stacks &st, const std::vector<char> &
     BSMM_TRY(hist.reserve(sizeof(int64_t) * (ntiles + 1), s));
     BSMM_TRY(off.reserve(sizeof(int64_t) * (ntiles + 1), s));
     BSMM_TRY(st.sched.reserve(sizeof(unsigned long long) * st.n_sched, s));
-    BSMM_TRY(st.sched_next.reserve(sizeof(unsigned long long), s));
+    BSMM_TRY(st.sched_next.reserve(kSchedCounterBytes, s));
     BSMM_HIP(hipMemcpyAsync(elig.p, eligible.data(), eligible.size(), hipMemcpyHostToDevice, s));
     BSMM_TRY(fill_zero(hist.as<double>(), ntiles + 1, s));
     const unsigned grid = grid_of(st.n_runs, 256, 8192);
@@ -568,7 +650,13 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
     int64_t rows = nbr;
     if (cap > 0 && st.n_prod > cap)
         rows = std::max<int64_t>(1, (int64_t)((double)nbr * (double)cap / (double)st.n_prod));
-    if (rows < 256 && A->nnzb > 0) {
+    if (rows < 512 && A->nnzb > 0 && !scratch_arena()) {
+        // At least 16 A blocks per part: a part walks them one after another.
+        const int64_t per_row = A->nnzb / nbr;
+        int64_t P = std::min<int64_t>(ceil_div(1024, rows), std::max<int64_t>(1, per_row / 16));
+        P = std::min<int64_t>(P, std::max<int64_t>(1, (int64_t(1) << 28) / nnzb));
+        st.kparts = (int)P;
+    } else if (rows < 256 && A->nnzb > 0) {
         const int64_t per_row = A->nnzb / nbr;
         int64_t P = std::min<int64_t>(ceil_div(1024, rows), std::max<int64_t>(1, per_row / 64));
         P = std::min<int64_t>(P, std::max<int64_t>(1, (int64_t(1) << 28) / nnzb));
@@ -641,6 +729,7 @@ namespace {
 struct ClassHist {
     DevBuf hist, hoff, hist_p, hoff_p, cb;
     int64_t ntiles = 0;
+    int tile = kTileMany;
 };
 
 // Per-class histograms of the C blocks [c0, c0 + nblk) that receive products
@@ -650,7 +739,9 @@ struct ClassHist {
 int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t nblk, ClassHist &h,
                   hipStream_t s) {
     const int ncl = st.n_classes;
-    h.ntiles = ceil_div(nblk, kTile);
+    // (The scratch region is left as it was: the large tiles' histograms.)
+    h.tile = ncl <= kSmallClasses && !scratch_arena() ? kTileFew : kTileMany;
+    h.ntiles = ceil_div(nblk, h.tile);
     const int64_t n = ncl * h.ntiles + 1;
     BSMM_TRY(h.hist.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.hoff.reserve(sizeof(int64_t) * n, s));
@@ -658,7 +749,7 @@ int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t 
     BSMM_TRY(h.hoff_p.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
     hipLaunchKernelGGL(k_class_hist, dim3(grid_of(h.ntiles, 4)), dim3(256),
-                       (sizeof(int32_t) + sizeof(int64_t)) * 4 * ncl, s, c0, nblk, h.ntiles,
+                       (sizeof(int32_t) + sizeof(int64_t)) * 4 * ncl, s, c0, nblk, h.ntiles, h.tile,
                        (const int64_t *)st.c_count.as<int64_t>(),
                        (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(),
                        (const int32_t *)st.d_rsi.as<int32_t>(),
@@ -707,22 +798,35 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
 
     DevBuf run_cnt;
     ClassHist h;
-    BSMM_TRY(run_cnt.reserve(sizeof(int64_t) * (nblk + 1), s));
     BSMM_TRY(st.run_of_c.reserve(sizeof(int64_t) * C->nnzb, s));
     BSMM_TRY(st.run_cblk.reserve(sizeof(int64_t) * nblk, s));
     BSMM_TRY(st.run_coff.reserve(sizeof(int64_t) * nblk, s));
     BSMM_TRY(st.run_class.reserve(sizeof(int32_t) * nblk, s));
     BSMM_TRY(st.run_ptr.reserve(sizeof(int64_t) * (nblk + 1), s));
-    BSMM_TRY(class_offsets(C, st, c0, nblk, h, s));
-    hipLaunchKernelGGL(k_class_scatter, dim3(grid_of(h.ntiles, 4)), dim3(256), sizeof(int64_t) * 4 * ncl,
-                       s, c0, nblk, h.ntiles, (const int64_t *)st.c_count.as<int64_t>(),
-                       (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
-                       (const int32_t *)st.d_rsi.as<int32_t>(),
-                       (const int32_t *)st.d_csi.as<int32_t>(), st.ncs, ncl,
-                       (const int64_t *)h.hoff.as<int64_t>(), st.run_cblk.as<int64_t>(),
-                       st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(),
-                       run_cnt.as<int64_t>(), st.run_of_c.as<int64_t>());
-    BSMM_TRY(launch_check("class_scatter"));
+    const bool small = nblk <= kSmallBlocks && ncl <= kSmallClasses;
+    if (small) {
+        BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
+        hipLaunchKernelGGL(k_classify_small, dim3(1), dim3(1024), 0, s, c0, (int)nblk,
+                           (const int64_t *)st.c_count.as<int64_t>(),
+                           (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
+                           (const int32_t *)st.d_rsi.as<int32_t>(), (const int32_t *)st.d_csi.as<int32_t>(),
+                           st.ncs, ncl, h.cb.as<int64_t>(), st.run_cblk.as<int64_t>(),
+                           st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(), st.run_ptr.as<int64_t>(),
+                           st.run_of_c.as<int64_t>());
+        BSMM_TRY(launch_check("classify_small"));
+    } else {
+        BSMM_TRY(run_cnt.reserve(sizeof(int64_t) * (nblk + 1), s));
+        BSMM_TRY(class_offsets(C, st, c0, nblk, h, s));
+        hipLaunchKernelGGL(k_class_scatter, dim3(grid_of(h.ntiles, 4)), dim3(256), sizeof(int64_t) * 4 * ncl,
+                           s, c0, nblk, h.ntiles, h.tile, (const int64_t *)st.c_count.as<int64_t>(),
+                           (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
+                           (const int32_t *)st.d_rsi.as<int32_t>(),
+                           (const int32_t *)st.d_csi.as<int32_t>(), st.ncs, ncl,
+                           (const int64_t *)h.hoff.as<int64_t>(), st.run_cblk.as<int64_t>(),
+                           st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(),
+                           run_cnt.as<int64_t>(), st.run_of_c.as<int64_t>());
+        BSMM_TRY(launch_check("class_scatter"));
+    }
     int32_t miss = 0;
     std::vector<int64_t> both(2 * (ncl + 1));
     BSMM_HIP(hipMemcpyAsync(both.data(), h.cb.p, sizeof(int64_t) * 2 * (ncl + 1),
@@ -736,7 +840,7 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     st.n_prod = st.class_prod_begin[ncl];  // below nprod when the screen left blocks out
     for (int cl = 0; cl < ncl; ++cl)
         if (st.class_begin[cl + 1] > st.class_begin[cl]) st.class_active[cl] = 1;
-    BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), st.n_runs, s));
+    if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), st.n_runs, s));
     if (st.n_prod > 0 && nbc > kMaxStackCols) {
         BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * st.n_prod, s));
         hipLaunchKernelGGL(k_stack_fill_win, dim3(grid_rows(r1 - r0), st.kparts), dim3(256), 0, s, r0, r1,

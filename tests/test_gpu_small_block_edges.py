@@ -128,3 +128,41 @@ def test_screen_norms_of_mixed_neighbours():
     finally:
         b.bsmm_set_option("prescreen", "1")
     check_against_oracle(out[0], out[1], 0.0)
+
+
+@pytest.mark.parametrize("nb,sizes", [(1, [23]), (7, [5, 13, 23, 32]), (60, [3, 8, 17]), (90, [4, 9]),
+                                      (92, [4, 9]), (40, list(range(1, 9)))])
+def test_classified_stacks(nb, sizes):
+    """Stacks of a small C (classified by one workgroup, up to 8,192 blocks
+    and 64 classes) and of larger ones: every product once, runs by class and
+    C block, K ascending."""
+    rng = rng_of(nb)
+    rs, ks = rng.choice(sizes, size=nb).astype(np.int32), rng.choice([2, 7], size=nb + 1).astype(np.int32)
+    A, B = _matrices(nb + 1, rs, ks, rs, 0.5)
+    b = lib()
+    set_path("stack", "plain")
+    try:
+        MA, MB = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B)
+        MC = b.Matrix.from_blocks(make_matrix(rng, rs, rs, 0.2, "zeros"))  # also blocks without products
+        b.multiply(1.0, MA, MB, 1.0, MC)
+        X = MC.to_host()
+        st = b.bsmm_inspect_stacks(MA.handle, MB.handle, MC.handle)
+        for M in (MA, MB, MC):
+            M.close()
+    finally:
+        set_path()
+    a_rows = np.repeat(np.arange(nb), np.diff(A.row_ptr))
+    c_rows = np.repeat(np.arange(nb), np.diff(X.row_ptr))
+    b_rows = np.repeat(np.arange(nb + 1), np.diff(B.row_ptr))
+    want = {(I, K, J) for I, K in zip(a_rows, A.col_ind) for J in B.col_ind[B.row_ptr[K]:B.row_ptr[K + 1]]}
+    got = set()
+    for r, c in enumerate(st["run_cblk"]):
+        p = slice(st["run_ptr"][r], st["run_ptr"][r + 1])
+        K = A.col_ind[st["prod_ablk"][p]]
+        assert len(K) > 0 and np.all(np.diff(K) > 0)
+        assert np.all(a_rows[st["prod_ablk"][p]] == c_rows[c]) and np.all(b_rows[st["prod_bblk"][p]] == K)
+        assert np.all(B.col_ind[st["prod_bblk"][p]] == X.col_ind[c])
+        got |= {(c_rows[c], k, X.col_ind[c]) for k in K}
+    assert got == want and sum(np.diff(st["run_ptr"])) == len(want)
+    order = list(zip(st["run_class"], st["run_cblk"]))
+    assert order == sorted(order)
