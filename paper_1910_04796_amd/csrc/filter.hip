@@ -253,8 +253,8 @@ int filter_blocks(bsmm_matrix_s *C, double eps, int64_t *nnzb_after, hipStream_t
                            (const double *)C->d_raw(), pre_norm2, eps * eps, keep.as<int64_t>(),
                            kel.as<int64_t>());
     BSMM_TRY(launch_check("norm_keep"));
-    BSMM_TRY(scan_exclusive_i64(keep.as<int64_t>(), kpos.as<int64_t>(), nnzb, s));
-    BSMM_TRY(scan_exclusive_i64(kel.as<int64_t>(), epos.as<int64_t>(), nnzb, s));
+    BSMM_TRY(scan_exclusive_pair(keep.as<int64_t>(), kpos.as<int64_t>(), kel.as<int64_t>(), epos.as<int64_t>(),
+                                 nnzb, s));
     int64_t tot[2];
     BSMM_HIP(hipMemcpyAsync(&tot[0], kpos.as<int64_t>() + nnzb, sizeof(int64_t),
                             hipMemcpyDeviceToHost, s));

@@ -210,6 +210,9 @@ namespace bsmm {
 // Exclusive prefix sum of n int64 values: out[0..n] with out[n] = total.
 // in and out may alias.  Temporary storage comes from the pool.
 int scan_exclusive_i64(const int64_t *in, int64_t *out, int64_t n, hipStream_t s);
+// Two arrays of n values each, by the same launches.
+int scan_exclusive_pair(const int64_t *in0, int64_t *out0, const int64_t *in1, int64_t *out1, int64_t n,
+                        hipStream_t s);
 
 // ---------------------------------------------------------------- index
 // Builds d_blk_off (int64[nnzb+1]) of a pattern from per-row element totals

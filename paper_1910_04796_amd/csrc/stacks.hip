@@ -756,8 +756,8 @@ int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t 
                        (const int32_t *)st.d_csi.as<int32_t>(), st.ncs, ncl, h.hist.as<int64_t>(),
                        h.hist_p.as<int64_t>());
     BSMM_TRY(launch_check("class_hist"));
-    BSMM_TRY(scan_exclusive_i64(h.hist.as<int64_t>(), h.hoff.as<int64_t>(), ncl * h.ntiles, s));
-    BSMM_TRY(scan_exclusive_i64(h.hist_p.as<int64_t>(), h.hoff_p.as<int64_t>(), ncl * h.ntiles, s));
+    BSMM_TRY(scan_exclusive_pair(h.hist.as<int64_t>(), h.hoff.as<int64_t>(), h.hist_p.as<int64_t>(),
+                                 h.hoff_p.as<int64_t>(), ncl * h.ntiles, s));
     hipLaunchKernelGGL(k_gather_class_begin, dim3(1), dim3(256), 0, s,
                        (const int64_t *)h.hoff.as<int64_t>(), (const int64_t *)h.hoff_p.as<int64_t>(),
                        h.ntiles, ncl, h.cb.as<int64_t>());
