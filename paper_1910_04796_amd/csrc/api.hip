@@ -133,6 +133,100 @@ void dev_free(void *p, hipStream_t s) {
     g_free.emplace(b.bytes, b);
 }
 
+// ---------------------------------------------------------------- readback
+struct Readback::Slot {
+    void *p = nullptr;
+    hipEvent_t ev = nullptr;
+    int device = 0;
+    ~Slot() {
+        if (p) (void)hipHostFree(p);
+        if (ev) (void)hipEventDestroy(ev);
+    }
+};
+static std::mutex g_readback_mu;
+std::vector<Readback::Slot *> &Readback::idle_slots() {
+    static auto *v = new std::vector<Slot *>();  // outlives the runtime's own teardown
+    return *v;
+}
+
+void release_readback_slots() {
+    std::lock_guard<std::mutex> lk(g_readback_mu);
+    for (Readback::Slot *x : Readback::idle_slots()) delete x;
+    Readback::idle_slots().clear();
+}
+
+int Readback::reserve(size_t bytes, hipStream_t s) {
+    s_ = s;
+    bytes_ = bytes;
+    if (scratch_arena()) {
+        BSMM_TRY(tmp_.reserve(bytes, s));
+        dev_ = tmp_.p;
+        return BSMM_OK;
+    }
+    if (bytes > kMaxBytes) {
+        set_error(BSMM_ERANGE, "%zu bytes to read back at once", bytes);
+        return BSMM_ERANGE;
+    }
+    int device = 0;
+    BSMM_HIP(hipGetDevice(&device));
+    {
+        std::lock_guard<std::mutex> lk(g_readback_mu);
+        auto &idle = idle_slots();
+        for (size_t i = idle.size(); i-- > 0;)
+            if (idle[i]->device == device) {
+                slot_ = idle[i];
+                idle.erase(idle.begin() + (long)i);
+                break;
+            }
+    }
+    if (!slot_) {
+        auto *x = new (std::nothrow) Slot();
+        if (!x || hipHostMalloc(&x->p, kMaxBytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess ||
+            hipEventCreateWithFlags(&x->ev, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            delete x;
+            set_error(BSMM_ENOMEM, "page-locked host memory is not available");
+            return BSMM_ENOMEM;
+        }
+        x->device = device;
+        slot_ = x;
+    }
+    dev_ = slot_->p;
+    return BSMM_OK;
+}
+
+int Readback::record() {
+    if (!slot_) {
+        copy_.resize(bytes_);
+        BSMM_HIP(hipMemcpyAsync(copy_.data(), dev_, bytes_, hipMemcpyDeviceToHost, s_));
+        return BSMM_OK;
+    }
+    BSMM_HIP(hipEventRecord(slot_->ev, s_));
+    recorded_ = true;
+    return BSMM_OK;
+}
+
+int Readback::wait() {
+    if (!slot_) {
+        BSMM_HIP(hipStreamSynchronize(s_));
+        host_ = copy_.data();
+        return BSMM_OK;
+    }
+    BSMM_HIP(hipEventSynchronize(slot_->ev));
+    waited_ = true;
+    host_ = slot_->p;
+    return BSMM_OK;
+}
+
+Readback::~Readback() {
+    if (!slot_) return;
+    // Kernels may still write when the multiply ended early.
+    if (!waited_) (void)hipStreamSynchronize(s_);
+    std::lock_guard<std::mutex> lk(g_readback_mu);
+    if (idle_slots().size() < 16) idle_slots().push_back(slot_);
+    else delete slot_;
+}
+
 int pool_release_all() {
     std::lock_guard<std::mutex> lk(g_mu);
     release_free_locked();
@@ -140,6 +234,7 @@ int pool_release_all() {
 }
 
 static int set_provider(bsmm_alloc_fn a, bsmm_dealloc_fn d, void *ctx) {
+    if (!a) release_readback_slots();  // back to the built-in provider: nothing is kept
     std::lock_guard<std::mutex> lk(g_mu);
     release_free_locked();
     g_prov.alloc = a;
@@ -222,7 +317,8 @@ ScratchArena *&scratch_arena() { return t_arena; }
 // hands it out while that work may still run.
 int adopt_stream(bsmm_matrix_s *M, hipStream_t s) {
     DevBuf *bufs[] = {&M->b_rbs, &M->b_cbs, &M->b_row_off, &M->b_col_off, &M->b_row_map,
-                      &M->b_col_map, &M->b_row_ptr, &M->b_col_ind, &M->b_blk_off, &M->b_data};
+                      &M->b_col_map, &M->b_row_ptr, &M->b_col_ind, &M->b_blk_off, &M->b_data,
+                      &M->b_row_size, &M->b_col_size};
     std::vector<hipStream_t> waited;
     for (DevBuf *b : bufs) {
         if (!b->p || b->s == s) continue;

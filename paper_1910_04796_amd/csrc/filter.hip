@@ -76,6 +76,11 @@ __global__ __launch_bounds__(256) void k_new_row_ptr(int32_t nbr, int64_t nnzb, 
     }
 }
 
+__global__ void k_kept_totals(const int64_t *blocks, const int64_t *elems, int64_t *out) {
+    out[0] = *blocks;
+    out[1] = *elems;
+}
+
 // One thread per old block: the kept blocks' column indices and data
 // offsets move to their new index positions; the data stay in place.
 __global__ __launch_bounds__(256) void k_keep_index(int64_t nnzb, const int32_t *ci,
@@ -255,13 +260,14 @@ int filter_blocks(bsmm_matrix_s *C, double eps, int64_t *nnzb_after, hipStream_t
     BSMM_TRY(launch_check("norm_keep"));
     BSMM_TRY(scan_exclusive_pair(keep.as<int64_t>(), kpos.as<int64_t>(), kel.as<int64_t>(), epos.as<int64_t>(),
                                  nnzb, s));
-    int64_t tot[2];
-    BSMM_HIP(hipMemcpyAsync(&tot[0], kpos.as<int64_t>() + nnzb, sizeof(int64_t),
-                            hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipMemcpyAsync(&tot[1], epos.as<int64_t>() + nnzb, sizeof(int64_t),
-                            hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipStreamSynchronize(s));
-    const int64_t new_nnzb = tot[0], new_elems = tot[1];
+    Readback tot;
+    BSMM_TRY(tot.reserve(2 * sizeof(int64_t), s));
+    hipLaunchKernelGGL(k_kept_totals, dim3(1), dim3(1), 0, s, (const int64_t *)kpos.as<int64_t>() + nnzb,
+                       (const int64_t *)epos.as<int64_t>() + nnzb, tot.dev<int64_t>());
+    BSMM_TRY(launch_check("kept_totals"));
+    BSMM_TRY(tot.record());
+    BSMM_TRY(tot.wait());
+    const int64_t new_nnzb = tot.host<int64_t>()[0], new_elems = tot.host<int64_t>()[1];
     *nnzb_after = new_nnzb;
     if (new_nnzb == nnzb) return BSMM_OK;
 

@@ -154,6 +154,41 @@ struct DevBuf {
     template <class T> T *as() const { return static_cast<T *>(p); }
 };
 
+// A few values that kernels compute and the host waits for: kernels write
+// them straight into page-locked host memory, and the host waits for an
+// event behind them, so that work queued after record() runs on.  Buffers
+// and events come from a small pool (at most 16 idle) that
+// bsmm_set_allocator(NULL) gives back.
+// While a scratch arena is active (nothing may be allocated) the values go
+// through device memory and a copy instead.
+class Readback {
+  public:
+    Readback() = default;
+    Readback(const Readback &) = delete;
+    Readback &operator=(const Readback &) = delete;
+    ~Readback();
+    int reserve(size_t bytes, hipStream_t s);  // at most kMaxBytes
+    template <class T> T *dev() const { return static_cast<T *>(dev_); }
+    int record();                              // after the last kernel that writes
+    int wait();                                // values readable through host() after this
+    template <class T> const T *host() const { return static_cast<const T *>(host_); }
+    static constexpr size_t kMaxBytes = 32768;
+
+  private:
+    struct Slot;
+    friend void release_readback_slots();
+    static std::vector<Slot *> &idle_slots();
+    Slot *slot_ = nullptr;
+    void *dev_ = nullptr;
+    const void *host_ = nullptr;
+    hipStream_t s_ = nullptr;
+    bool recorded_ = false, waited_ = false;
+    size_t bytes_ = 0;
+    DevBuf tmp_;
+    std::vector<char> copy_;
+};
+void release_readback_slots();
+
 }  // namespace bsmm
 
 namespace bsmm {
@@ -202,6 +237,12 @@ struct bsmm_matrix_s {
     bool full() const { return nnzb == (int64_t)nbr * (int64_t)nbc; }
     bool holes = false;
     int64_t storage = 0;  // elements the data buffer holds (blk_off[nnzb])
+    // Distinct block-row and block-column sizes and every block row's and
+    // column's index among them (device), made when the matrix is first C of
+    // a stack multiply; the sizes of a matrix never change.
+    mutable bool has_size_index = false;
+    mutable std::vector<int32_t> row_sizes, col_sizes;
+    mutable bsmm::DevBuf b_row_size, b_col_size;
 };
 
 namespace bsmm {
@@ -296,7 +337,9 @@ struct Stacks {
     DevBuf c_count;    // int64[C.nnzb]   products per C block
     DevBuf c_row;      // int32[C.nnzb]   block row of every C block
     DevBuf run_of_c;   // int64[C.nnzb]   run of every C block in its panel, or -1
-    DevBuf d_rsi, d_csi, missing;     // size-class index of rows / columns; pattern flag
+    DevBuf d_rsi, d_csi;              // size-class index of rows / columns while a scratch arena is active
+    const int32_t *rsi = nullptr, *csi = nullptr;  // ... where it lies (there, or in C)
+    DevBuf missing;                   // pattern flag
     bool screened = false;            // C's pattern came from the screen: products of left-out blocks are skipped
     DevBuf a_t;                       // A's blocks transposed, for the scheduled launch (option stack_at)
     DevBuf b_t;                       // B's blocks transposed, for the scheduled launch

@@ -22,14 +22,16 @@ bsmm_multiply_stats &stats();
 
 namespace {
 
-// Sums of the per-row symbolic counts: out_i[0..4] (nnz, elems, products,
-// and with the screen the screened blocks and screened old blocks), out_d[0]
-// (flops).
+// Sums of the per-row symbolic counts (screened, old_screened: with the
+// screen).
+struct RowTotals {
+    int64_t nnz, elems, products, screened, old_screened;
+    double flops;
+};
 __global__ __launch_bounds__(256) void k_row_totals(int32_t nbr, const int64_t *nnz,
                                                     const int64_t *elems, const int64_t *prod,
                                                     const double *flops, const int64_t *scr,
-                                                    const int64_t *old_scr, int64_t *out_i,
-                                                    double *out_d) {
+                                                    const int64_t *old_scr, RowTotals *out) {
     __shared__ int64_t ri[16];
     __shared__ double rd[16];
     int64_t a = 0, b = 0, c = 0, e = 0, f = 0;
@@ -51,12 +53,7 @@ __global__ __launch_bounds__(256) void k_row_totals(int32_t nbr, const int64_t *
     f = block_sum(f, ri);
     d = block_sum(d, rd);
     if (threadIdx.x == 0) {
-        out_i[0] = a;
-        out_i[1] = b;
-        out_i[2] = c;
-        out_i[3] = e;
-        out_i[4] = f;
-        out_d[0] = d;
+        *out = RowTotals{a, b, c, e, f, d};
     }
 }
 
@@ -74,7 +71,8 @@ int symbolic_screened(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, cons
     const int32_t nbr = A->nbr, nbc = B->nbc;
     const int64_t nwords = (nbc + 31) / 32;
     ScreenNorms sn = req;
-    DevBuf an, bn, cn, bits, rnnz, rprod, rflops, rscr, rold, sums_i, sums_d;
+    DevBuf an, bn, cn, bits, rnnz, rprod, rflops, rscr, rold;
+    Readback sums;
     BSMM_TRY(an.reserve(sizeof(double) * (A->nnzb + 1), s));
     BSMM_TRY(bn.reserve(sizeof(double) * (B->nnzb + 1), s));
     BSMM_TRY(block_norms(A, an.as<double>(), s));
@@ -94,8 +92,7 @@ int symbolic_screened(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, cons
     BSMM_TRY(rflops.reserve(sizeof(double) * (nbr + 1), s));
     BSMM_TRY(rscr.reserve(sizeof(int64_t) * (nbr + 1), s));
     BSMM_TRY(rold.reserve(sizeof(int64_t) * (nbr + 1), s));
-    BSMM_TRY(sums_i.reserve(sizeof(int64_t) * 6, s));
-    BSMM_TRY(sums_d.reserve(sizeof(double) * 2, s));
+    BSMM_TRY(sums.reserve(sizeof(RowTotals), s));
     BSMM_TRY(symbolic_count_screen(A, B, C, sn, bits.as<uint32_t>(), rnnz.as<int64_t>(),
                                    row_elems.as<int64_t>(), rprod.as<int64_t>(), rflops.as<double>(),
                                    rscr.as<int64_t>(), rold.as<int64_t>(), s));
@@ -103,20 +100,18 @@ int symbolic_screened(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, cons
                        (const int64_t *)rnnz.as<int64_t>(), (const int64_t *)row_elems.as<int64_t>(),
                        (const int64_t *)rprod.as<int64_t>(), (const double *)rflops.as<double>(),
                        (const int64_t *)rscr.as<int64_t>(), (const int64_t *)rold.as<int64_t>(),
-                       sums_i.as<int64_t>(), sums_d.as<double>());
+                       sums.dev<RowTotals>());
     BSMM_TRY(launch_check("row_totals"));
-    int64_t hi[5];
-    double hd[1];
-    BSMM_HIP(hipMemcpyAsync(hi, sums_i.p, sizeof(hi), hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipMemcpyAsync(hd, sums_d.p, sizeof(hd), hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipStreamSynchronize(s));
-    tot->nnzb = hi[0];
-    tot->nelems = hi[1];
-    tot->nprod = hi[2];
-    tot->flops = hd[0];
+    BSMM_TRY(sums.record());
+    BSMM_TRY(sums.wait());
+    const RowTotals h = *sums.host<RowTotals>();
+    tot->nnzb = h.nnz;
+    tot->nelems = h.elems;
+    tot->nprod = h.products;
+    tot->flops = h.flops;
     tot->screen = true;
-    tot->screened = hi[3];
-    tot->old_screened = hi[4];
+    tot->screened = h.screened;
+    tot->old_screened = h.old_screened;
     if (tot->nnzb > (int64_t)INT32_MAX || tot->nelems >= (int64_t(1) << 47)) {
         set_error(BSMM_ERANGE, "result too large (%lld blocks, %lld elements)",
                   (long long)tot->nnzb, (long long)tot->nelems);
@@ -169,29 +164,26 @@ int symbolic(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, SymbolicTotal
                               row_elems.as<int64_t>(), C->d_rbs(), s));
         return BSMM_OK;
     }
-    DevBuf rnnz, rprod, rflops, sums_i, sums_d;
+    DevBuf rnnz, rprod, rflops;
+    Readback sums;
     BSMM_TRY(rnnz.reserve(sizeof(int64_t) * (nbr + 1), s));
     BSMM_TRY(rprod.reserve(sizeof(int64_t) * (nbr + 1), s));
     BSMM_TRY(rflops.reserve(sizeof(double) * (nbr + 1), s));
-    BSMM_TRY(sums_i.reserve(sizeof(int64_t) * 6, s));
-    BSMM_TRY(sums_d.reserve(sizeof(double) * 2, s));
+    BSMM_TRY(sums.reserve(sizeof(RowTotals), s));
     BSMM_TRY(symbolic_count(A, B, C, rnnz.as<int64_t>(), row_elems.as<int64_t>(),
                             rprod.as<int64_t>(), rflops.as<double>(), s));
     hipLaunchKernelGGL(k_row_totals, dim3(1), dim3(256), 0, s, nbr,
                        (const int64_t *)rnnz.as<int64_t>(), (const int64_t *)row_elems.as<int64_t>(),
                        (const int64_t *)rprod.as<int64_t>(), (const double *)rflops.as<double>(),
-                       (const int64_t *)nullptr, (const int64_t *)nullptr, sums_i.as<int64_t>(),
-                       sums_d.as<double>());
+                       (const int64_t *)nullptr, (const int64_t *)nullptr, sums.dev<RowTotals>());
     BSMM_TRY(launch_check("row_totals"));
-    int64_t hi[3];
-    double hd[1];
-    BSMM_HIP(hipMemcpyAsync(hi, sums_i.p, sizeof(hi), hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipMemcpyAsync(hd, sums_d.p, sizeof(hd), hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipStreamSynchronize(s));
-    tot->nnzb = hi[0];
-    tot->nelems = hi[1];
-    tot->nprod = hi[2];
-    tot->flops = hd[0];
+    BSMM_TRY(sums.record());
+    BSMM_TRY(sums.wait());
+    const RowTotals h = *sums.host<RowTotals>();
+    tot->nnzb = h.nnz;
+    tot->nelems = h.elems;
+    tot->nprod = h.products;
+    tot->flops = h.flops;
     if (tot->nnzb > (int64_t)INT32_MAX || tot->nelems >= (int64_t(1) << 47)) {
         set_error(BSMM_ERANGE, "result too large (%lld blocks, %lld elements)",
                   (long long)tot->nnzb, (long long)tot->nelems);

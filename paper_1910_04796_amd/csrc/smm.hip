@@ -444,7 +444,7 @@ __global__ __launch_bounds__(256, 4) void k_smm_mfma_sched(SmmArgs p) {
 // kTurnElems elements), so that reads and writes are both contiguous; the
 // next block's elements are read while this one is written.  Bound by HBM
 // (16 bytes per FP64 element); 1.44 GB of 5-to-32-sided blocks 1,146 us with
-// one lookup per block and no read ahead, @X@ us so.
+// one lookup per block and no read ahead, 642 us so (4.5 TB/s).
 constexpr int kTurnElems = 1024;
 constexpr int kTurnBlocks = 8;
 template <class T>
@@ -988,8 +988,11 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     // Instantiating a graph may allocate device memory: a multiply running
     // on a scratch arena launches its classes one by one instead, and so
     // does one with run-time compiled kernels (module functions, which a
-    // graph kernel node does not take).
-    if (tuned && chunk <= 0 && launches.size() > 1 && !scratch_arena() && st.n_jit == 0) {
+    // graph kernel node does not take).  Up to three launches that are not
+    // kept for a replay go one by one too: instantiating their graph takes
+    // longer than they gain from running side by side.
+    if (tuned && chunk <= 0 && launches.size() > (options().plan_cache ? 1u : 3u) && !scratch_arena() &&
+        st.n_jit == 0) {
         BSMM_TRY(build_graph(launches, A, B, C, st, alpha, beta, &ex->exec));
         BSMM_HIP(hipEventCreateWithFlags(&ex->done, hipEventDisableTiming));
     }

@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256) void k_class_scatter(
 // are scanned class by class, then every wave walks its blocks again.
 __global__ __launch_bounds__(1024) void k_classify_small(
     int64_t c_base, int nblk, const int64_t *c_count, const int32_t *c_row, const int32_t *c_ci,
-    const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi, int ncs, int ncl, int64_t *cb,
+    const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi, int ncs, int ncl, const int32_t *missing, int64_t *cb,
     int64_t *run_cblk, int32_t *run_class, int64_t *run_coff, int64_t *run_ptr, int64_t *run_of_c) {
     constexpr int W = 16;
     __shared__ unsigned long long s_run[kSmallClasses * W], s_prod[kSmallClasses * W];
@@ -322,6 +322,7 @@ __global__ __launch_bounds__(1024) void k_classify_small(
     if (t == 0) {
         cb[ncl] = runs;
         cb[2 * ncl + 1] = prods;
+        cb[2 * (ncl + 1)] = *missing;
         run_ptr[runs] = prods;
     }
     __syncthreads();
@@ -370,7 +371,8 @@ __global__ void k_gather_rows(const int64_t *scan, const int64_t *rp, int32_t nb
 
 // out[0..ncl]: first run of every class; out[ncl+1..2 ncl+1]: its first product.
 __global__ void k_gather_class_begin(const int64_t *hoff, const int64_t *hoff_p, int64_t ntiles,
-                                     int ncl, int64_t *out) {
+                                     int ncl, const int32_t *missing, int64_t *out) {
+    if (threadIdx.x == 0) out[2 * (ncl + 1)] = *missing;
     for (int cl = threadIdx.x; cl <= ncl; cl += blockDim.x) {
         out[cl] = hoff[(int64_t)cl * ntiles];
         out[ncl + 1 + cl] = hoff_p[(int64_t)cl * ntiles];
@@ -500,11 +502,19 @@ __device__ __forceinline__ int64_t tile_key(int32_t I, int32_t J, int tile, int6
     return (int64_t)(I / tile) * ntj + J / tile;
 }
 
+// The classes whose runs are scheduled: one bit each in the argument while
+// they fit, else one byte each in device memory.
+struct Eligible {
+    uint64_t bits;
+    const char *flags;
+    __device__ __forceinline__ bool has(int cl) const { return flags ? flags[cl] != 0 : (bits >> cl & 1) != 0; }
+};
+
 // The tile of this lane's run (-1: none, or a class that is not scheduled).
 __device__ __forceinline__ int64_t run_tile(int64_t r, int64_t nruns, const int64_t *run_cblk,
-                                            const int32_t *run_class, const char *elig, const int32_t *c_row,
+                                            const int32_t *run_class, Eligible elig, const int32_t *c_row,
                                             const int32_t *c_ci, int tile, int64_t ntj, int32_t *I, int32_t *J) {
-    if (r >= nruns || !elig[run_class[r]]) return -1;
+    if (r >= nruns || !elig.has(run_class[r])) return -1;
     const int64_t c = run_cblk[r];
     *I = c_row[c];
     *J = c_ci[c];
@@ -527,7 +537,7 @@ __device__ __forceinline__ int stretch(int64_t key, int *head) {
 
 // Runs per tile (runs of eligible classes only).
 __global__ __launch_bounds__(256) void k_sched_hist(int64_t nruns, const int64_t *run_cblk,
-                                                    const int32_t *run_class, const char *elig,
+                                                    const int32_t *run_class, Eligible elig,
                                                     const int32_t *c_row, const int32_t *c_ci,
                                                     int tile, int64_t ntj, int64_t *hist) {
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nruns; base += (int64_t)gridDim.x * blockDim.x) {
@@ -542,7 +552,7 @@ __global__ __launch_bounds__(256) void k_sched_hist(int64_t nruns, const int64_t
 // Every eligible run into its tile's range of the schedule (the order of
 // the runs inside a tile is not fixed; it does not change any result).
 __global__ __launch_bounds__(256) void k_sched_scatter(int64_t nruns, const int64_t *run_cblk,
-                                                       const int32_t *run_class, const char *elig,
+                                                       const int32_t *run_class, Eligible elig,
                                                        const int32_t *c_row, const int32_t *c_ci,
                                                        const int32_t *rbs, const int32_t *cbs,
                                                        int tile, int64_t ntj, int64_t *cursor,
@@ -574,25 +584,31 @@ int build_schedule(const bsmm_matrix_s *C, Stacks &st, const std::vector<char> &
     tile = std::max(tile, 1);
     const int64_t nti = ceil_div(C->nbr, tile), ntj = ceil_div(C->nbc, tile);
     const int64_t ntiles = nti * ntj;
-    DevBuf elig, hist, off;
-    BSMM_TRY(elig.reserve(eligible.size(), s));
+    DevBuf flags, hist, off;
+    Eligible elig{0, nullptr};
+    if (eligible.size() <= 64) {
+        for (size_t cl = 0; cl < eligible.size(); ++cl) elig.bits |= (uint64_t)(eligible[cl] != 0) << cl;
+    } else {
+        BSMM_TRY(flags.reserve(eligible.size(), s));
+        BSMM_HIP(hipMemcpyAsync(flags.p, eligible.data(), eligible.size(), hipMemcpyHostToDevice, s));
+        elig.flags = flags.as<char>();
+    }
     BSMM_TRY(hist.reserve(sizeof(int64_t) * (ntiles + 1), s));
     BSMM_TRY(off.reserve(sizeof(int64_t) * (ntiles + 1), s));
     BSMM_TRY(st.sched.reserve(sizeof(unsigned long long) * st.n_sched, s));
     BSMM_TRY(st.sched_next.reserve(kSchedCounterBytes, s));
-    BSMM_HIP(hipMemcpyAsync(elig.p, eligible.data(), eligible.size(), hipMemcpyHostToDevice, s));
     BSMM_TRY(fill_zero(hist.as<double>(), ntiles + 1, s));
     const unsigned grid = grid_of(st.n_runs, 256, 8192);
     hipLaunchKernelGGL(k_sched_hist, dim3(grid), dim3(256), 0, s, st.n_runs,
                        (const int64_t *)st.run_cblk.as<int64_t>(),
-                       (const int32_t *)st.run_class.as<int32_t>(), (const char *)elig.as<char>(),
+                       (const int32_t *)st.run_class.as<int32_t>(), elig,
                        (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), tile, ntj,
                        hist.as<int64_t>());
     BSMM_TRY(launch_check("sched_hist"));
     BSMM_TRY(scan_exclusive_i64(hist.as<int64_t>(), off.as<int64_t>(), ntiles, s));
     hipLaunchKernelGGL(k_sched_scatter, dim3(grid), dim3(256), 0, s, st.n_runs,
                        (const int64_t *)st.run_cblk.as<int64_t>(),
-                       (const int32_t *)st.run_class.as<int32_t>(), (const char *)elig.as<char>(),
+                       (const int32_t *)st.run_class.as<int32_t>(), elig,
                        (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_rbs(),
                        C->d_cbs(), tile, ntj, off.as<int64_t>(),
                        st.sched.as<unsigned long long>());
@@ -617,9 +633,16 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
                 Stacks &st, hipStream_t s) {
     const int32_t nbr = C->nbr, nbc = C->nbc;
     const int64_t nnzb = C->nnzb;
+    // The size index is kept with C, except in the scratch region.
     std::vector<int32_t> rsi, csi;
-    size_classes(C->rbs, st.row_sizes, rsi);
-    size_classes(C->cbs, st.col_sizes, csi);
+    const bool keep = !scratch_arena(), made = keep && C->has_size_index;
+    if (!made) {
+        size_classes(C->rbs, st.row_sizes, rsi);
+        size_classes(C->cbs, st.col_sizes, csi);
+    } else {
+        st.row_sizes = C->row_sizes;
+        st.col_sizes = C->col_sizes;
+    }
     st.nrs = (int32_t)st.row_sizes.size();
     st.ncs = (int32_t)st.col_sizes.size();
     const int ncl = st.nrs * st.ncs;
@@ -635,8 +658,20 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
     st.n_runs = 0;
     if (nbr == 0 || nnzb == 0) return BSMM_OK;
 
-    BSMM_TRY(st.d_rsi.reserve(sizeof(int32_t) * nbr, s));
-    BSMM_TRY(st.d_csi.reserve(sizeof(int32_t) * nbc, s));
+    if (!made) {
+        DevBuf &dr = keep ? C->b_row_size : st.d_rsi, &dc = keep ? C->b_col_size : st.d_csi;
+        BSMM_TRY(dr.reserve(sizeof(int32_t) * nbr, s));
+        BSMM_TRY(dc.reserve(sizeof(int32_t) * nbc, s));
+        BSMM_HIP(hipMemcpyAsync(dr.p, rsi.data(), sizeof(int32_t) * nbr, hipMemcpyHostToDevice, s));
+        BSMM_HIP(hipMemcpyAsync(dc.p, csi.data(), sizeof(int32_t) * nbc, hipMemcpyHostToDevice, s));
+        if (keep) {
+            C->row_sizes = st.row_sizes;
+            C->col_sizes = st.col_sizes;
+            C->has_size_index = true;
+        }
+    }
+    st.rsi = keep ? C->b_row_size.as<int32_t>() : st.d_rsi.as<int32_t>();
+    st.csi = keep ? C->b_col_size.as<int32_t>() : st.d_csi.as<int32_t>();
     BSMM_TRY(st.c_row.reserve(sizeof(int32_t) * nnzb, s));
     BSMM_TRY(st.c_count.reserve(sizeof(int64_t) * nnzb, s));
     BSMM_TRY(st.missing.reserve(sizeof(int32_t), s));
@@ -663,8 +698,6 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
         st.kparts = (int)P;
     }
     if (st.kparts > 1) BSMM_TRY(st.pcount.reserve(sizeof(int64_t) * nnzb * st.kparts, s));
-    BSMM_HIP(hipMemcpyAsync(st.d_rsi.p, rsi.data(), sizeof(int32_t) * nbr, hipMemcpyHostToDevice, s));
-    BSMM_HIP(hipMemcpyAsync(st.d_csi.p, csi.data(), sizeof(int32_t) * nbc, hipMemcpyHostToDevice, s));
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, s, st.missing.as<int32_t>());
     BSMM_TRY(launch_check("zero_i32"));
     st.nwin = 0;
@@ -727,7 +760,8 @@ int stack_row_bounds(const bsmm_matrix_s *C, const Stacks &st, std::vector<int64
 
 namespace {
 struct ClassHist {
-    DevBuf hist, hoff, hist_p, hoff_p, cb;
+    DevBuf hist, hoff, hist_p, hoff_p;
+    Readback cb;
     int64_t ntiles = 0;
     int tile = kTileMany;
 };
@@ -735,7 +769,7 @@ struct ClassHist {
 // Per-class histograms of the C blocks [c0, c0 + nblk) that receive products
 // (blocks and products, per tile), their scans, and the class boundaries
 // gathered into h.cb: first run of every class, then its first product
-// (2 (ncl + 1) values).  Everything is queued on s.
+// (2 (ncl + 1) values), then the pattern flag.  Everything is queued on s.
 int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t nblk, ClassHist &h,
                   hipStream_t s) {
     const int ncl = st.n_classes;
@@ -747,20 +781,20 @@ int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t 
     BSMM_TRY(h.hoff.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.hist_p.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.hoff_p.reserve(sizeof(int64_t) * n, s));
-    BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
+    BSMM_TRY(h.cb.reserve(sizeof(int64_t) * (2 * (ncl + 1) + 1), s));
     hipLaunchKernelGGL(k_class_hist, dim3(grid_of(h.ntiles, 4)), dim3(256),
                        (sizeof(int32_t) + sizeof(int64_t)) * 4 * ncl, s, c0, nblk, h.ntiles, h.tile,
                        (const int64_t *)st.c_count.as<int64_t>(),
                        (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(),
-                       (const int32_t *)st.d_rsi.as<int32_t>(),
-                       (const int32_t *)st.d_csi.as<int32_t>(), st.ncs, ncl, h.hist.as<int64_t>(),
+                       st.rsi,
+                       st.csi, st.ncs, ncl, h.hist.as<int64_t>(),
                        h.hist_p.as<int64_t>());
     BSMM_TRY(launch_check("class_hist"));
     BSMM_TRY(scan_exclusive_pair(h.hist.as<int64_t>(), h.hoff.as<int64_t>(), h.hist_p.as<int64_t>(),
                                  h.hoff_p.as<int64_t>(), ncl * h.ntiles, s));
     hipLaunchKernelGGL(k_gather_class_begin, dim3(1), dim3(256), 0, s,
                        (const int64_t *)h.hoff.as<int64_t>(), (const int64_t *)h.hoff_p.as<int64_t>(),
-                       h.ntiles, ncl, h.cb.as<int64_t>());
+                       h.ntiles, ncl, (const int32_t *)st.missing.as<int32_t>(), h.cb.dev<int64_t>());
     return launch_check("gather_class_begin");
 }
 }  // namespace
@@ -772,10 +806,9 @@ int stack_class_run_lengths(const bsmm_matrix_s *C, const Stacks &st, std::vecto
     if (C->nnzb == 0 || ncl == 0) return BSMM_OK;
     ClassHist h;
     BSMM_TRY(class_offsets(C, st, 0, C->nnzb, h, s));
-    std::vector<int64_t> both(2 * (ncl + 1));
-    BSMM_HIP(hipMemcpyAsync(both.data(), h.cb.p, sizeof(int64_t) * 2 * (ncl + 1),
-                            hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipStreamSynchronize(s));
+    BSMM_TRY(h.cb.record());
+    BSMM_TRY(h.cb.wait());
+    const int64_t *both = h.cb.host<int64_t>();
     for (int cl = 0; cl < ncl; ++cl) {
         const int64_t runs = both[cl + 1] - both[cl];
         const int64_t prods = both[ncl + 2 + cl] - both[ncl + 1 + cl];
@@ -805,12 +838,12 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     BSMM_TRY(st.run_ptr.reserve(sizeof(int64_t) * (nblk + 1), s));
     const bool small = nblk <= kSmallBlocks && ncl <= kSmallClasses;
     if (small) {
-        BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
+        BSMM_TRY(h.cb.reserve(sizeof(int64_t) * (2 * (ncl + 1) + 1), s));
         hipLaunchKernelGGL(k_classify_small, dim3(1), dim3(1024), 0, s, c0, (int)nblk,
                            (const int64_t *)st.c_count.as<int64_t>(),
                            (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
-                           (const int32_t *)st.d_rsi.as<int32_t>(), (const int32_t *)st.d_csi.as<int32_t>(),
-                           st.ncs, ncl, h.cb.as<int64_t>(), st.run_cblk.as<int64_t>(),
+                           st.rsi, st.csi,
+                           st.ncs, ncl, (const int32_t *)st.missing.as<int32_t>(), h.cb.dev<int64_t>(), st.run_cblk.as<int64_t>(),
                            st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(), st.run_ptr.as<int64_t>(),
                            st.run_of_c.as<int64_t>());
         BSMM_TRY(launch_check("classify_small"));
@@ -820,29 +853,20 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
         hipLaunchKernelGGL(k_class_scatter, dim3(grid_of(h.ntiles, 4)), dim3(256), sizeof(int64_t) * 4 * ncl,
                            s, c0, nblk, h.ntiles, h.tile, (const int64_t *)st.c_count.as<int64_t>(),
                            (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
-                           (const int32_t *)st.d_rsi.as<int32_t>(),
-                           (const int32_t *)st.d_csi.as<int32_t>(), st.ncs, ncl,
+                           st.rsi,
+                           st.csi, st.ncs, ncl,
                            (const int64_t *)h.hoff.as<int64_t>(), st.run_cblk.as<int64_t>(),
                            st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(),
                            run_cnt.as<int64_t>(), st.run_of_c.as<int64_t>());
         BSMM_TRY(launch_check("class_scatter"));
     }
-    int32_t miss = 0;
-    std::vector<int64_t> both(2 * (ncl + 1));
-    BSMM_HIP(hipMemcpyAsync(both.data(), h.cb.p, sizeof(int64_t) * 2 * (ncl + 1),
-                            hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipMemcpyAsync(&miss, st.missing.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    BSMM_HIP(hipStreamSynchronize(s));
-    BSMM_TRY(check_missing(miss));
-    st.class_begin.assign(both.begin(), both.begin() + ncl + 1);
-    st.class_prod_begin.assign(both.begin() + ncl + 1, both.end());
-    st.n_runs = st.class_begin[ncl];
-    st.n_prod = st.class_prod_begin[ncl];  // below nprod when the screen left blocks out
-    for (int cl = 0; cl < ncl; ++cl)
-        if (st.class_begin[cl + 1] > st.class_begin[cl]) st.class_active[cl] = 1;
-    if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), st.n_runs, s));
-    if (st.n_prod > 0 && nbc > kMaxStackCols) {
-        BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * st.n_prod, s));
+    BSMM_TRY(h.cb.record());
+    // The rest is queued ahead of the host's wait, by what is known before
+    // it: at most nblk runs (the scan's values past the runs are not used)
+    // and nprod products.
+    if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), nblk, s));
+    if (nprod > 0 && nbc > kMaxStackCols) {
+        BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * nprod, s));
         hipLaunchKernelGGL(k_stack_fill_win, dim3(grid_rows(r1 - r0), st.kparts), dim3(256), 0, s, r0, r1,
                            st.kparts, (const int64_t *)st.pcount.as<int64_t>(), st.nwin, A->d_row_ptr(),
                            A->d_col_ind(), A->d_blk_off(), (const int64_t *)st.b_split.as<int64_t>(),
@@ -850,8 +874,8 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
                            (const int64_t *)st.run_of_c.as<int64_t>(),
                            (const int64_t *)st.run_ptr.as<int64_t>(), st.prods.as<ulonglong2>());
         BSMM_TRY(launch_check("stack_fill_win"));
-    } else if (st.n_prod > 0) {
-        BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * st.n_prod, s));
+    } else if (nprod > 0) {
+        BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * nprod, s));
         // LDS: the column map, then per slot a 64-bit next position (rows of
         // at most cap slots) or a 32-bit count; at most 64 KB.
         const int64_t nbc_pad = (nbc + 1) & ~1;
@@ -865,6 +889,15 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
                            (const int64_t *)st.run_ptr.as<int64_t>(), st.prods.as<ulonglong2>());
         BSMM_TRY(launch_check("stack_fill"));
     }
+    BSMM_TRY(h.cb.wait());
+    const int64_t *both = h.cb.host<int64_t>();
+    BSMM_TRY(check_missing((int32_t)both[2 * (ncl + 1)]));
+    st.class_begin.assign(both, both + ncl + 1);
+    st.class_prod_begin.assign(both + ncl + 1, both + 2 * (ncl + 1));
+    st.n_runs = st.class_begin[ncl];
+    st.n_prod = st.class_prod_begin[ncl];  // below nprod when the screen left blocks out
+    for (int cl = 0; cl < ncl; ++cl)
+        if (st.class_begin[cl + 1] > st.class_begin[cl]) st.class_active[cl] = 1;
     return BSMM_OK;
 }
 

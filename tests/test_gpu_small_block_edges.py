@@ -166,3 +166,45 @@ def test_classified_stacks(nb, sizes):
     assert got == want and sum(np.diff(st["run_ptr"])) == len(want)
     order = list(zip(st["run_class"], st["run_cblk"]))
     assert order == sorted(order)
+
+
+def test_threads_and_streams_read_back_their_own_counts():
+    """Four host threads, each with its own handles and stream: every
+    multiply sees the pattern sizes and class counts of its own product."""
+    import threading
+
+    import torch
+    b = lib()
+    set_path("stack", "plain")
+    jobs = []
+    for t in range(4):
+        rng = rng_of(500 + t)
+        rs, ks = rng.choice([5, 13, 23][: t % 3 + 1], size=10 + 7 * t).astype(np.int32), np.full(9 + t, 8, np.int32)
+        A, B = _matrices(600 + t, rs, ks, rs, 0.3 + 0.1 * t)
+        jobs.append((A, B, orc.multiply(1.0, A, B, 0.0, filter_eps=1e-3 if t == 3 else 0.0), 1e-3 if t == 3 else 0.0))
+    failed = []
+
+    def work(A, B, R, eps):
+        try:
+            stream = torch.cuda.Stream()
+            MA, MB = b.Matrix.from_blocks(A, stream=stream), b.Matrix.from_blocks(B, stream=stream)
+            for _ in range(8):
+                MC = b.Matrix.empty(A.rbs, B.cbs, stream=stream)
+                for _ in range(3):
+                    b.multiply(1.0, MA, MB, 0.0, MC, eps, stream=stream)
+                check_against_oracle(MC.to_host(stream=stream), R, 1e-13)
+                MC.close()
+            MA.close()
+            MB.close()
+        except Exception as e:  # noqa: BLE001 - reported by the main thread
+            failed.append(repr(e))
+
+    try:
+        threads = [threading.Thread(target=work, args=j) for j in jobs]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+    finally:
+        set_path()
+    assert not failed, failed
