@@ -12,9 +12,10 @@
 // blocks through per-row and per-column (block, offset) maps.
 //
 // GEMM: 128 x 128 output tile per 512-thread workgroup, k step 16, LDS double
-// buffered; each wave owns a 64 x 32 sub-tile as 4 x 2 MFMA tiles of
-// v_mfma_f64_16x16x4 (FP64 in, FP64 accumulate); with k step 32, 256 threads
-// and 64 x 64 sub-tiles.  Workgroup ids are remapped
+// buffered and filled straight from memory; each wave owns 64 rows x 32
+// columns as 4 x 2 MFMA tiles of v_mfma_f64_16x16x4 (FP64 in, FP64
+// accumulate); with k step 32, 256 threads and 64 x 64 outputs per wave.
+// Workgroup ids are remapped
 // so that the tiles dispatched to one XCD form a contiguous band of
 // 8 tile-rows (shared A panels stay in that XCD's L2).  When the output
 // has too few tiles to fill the GPU (M = N = 1408 with K in the millions:
@@ -22,6 +23,7 @@
 // are summed in a fixed order by a second kernel that applies the epilogue.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "dev_util.h"
 #include "internal.h"
@@ -30,10 +32,6 @@
 namespace bsmm {
 
 namespace {
-
-template <class T> struct Vec2;
-template <> struct Vec2<double> { typedef double __attribute__((ext_vector_type(2))) t; };
-template <> struct Vec2<float> { typedef float __attribute__((ext_vector_type(2))) t; };
 
 // Zeros in the padding of a column-major panel of ld x ncols whose merge
 // fills rows x cols: the rows below in the first columns, then whole
@@ -176,63 +174,111 @@ struct GemmArgs {
     void *part;
 };
 
-// Global -> register loads of one k step of KB: A tile (128 rows x KB k) as
-// KB * 64 double2 along the rows, B tile (KB k x 128 cols) along k.
-template <class T, int KB, int NTH>
-__device__ __forceinline__ void gemm_gload(typename Vec2<T>::t (&ra)[KB * 64 / NTH],
-                                           typename Vec2<T>::t (&rb)[KB * 64 / NTH], const T *Ablk,
-                                           const T *Bblk, int64_t lda, int64_t ldb, int kt, int tid) {
-    typedef typename Vec2<T>::t V2;
-    const int64_t k0 = (int64_t)kt * KB;
-#pragma unroll
-    for (int i = 0; i < KB * 64 / NTH; ++i) {
-        const int e = tid + NTH * i;
-        const int kk = e >> 6, r2 = e & 63;
-        ra[i] = *reinterpret_cast<const V2 *>(Ablk + (k0 + kk) * lda + 2 * r2);
-    }
-#pragma unroll
-    for (int i = 0; i < KB * 64 / NTH; ++i) {
-        const int e = tid + NTH * i;
-        const int col = e / (KB / 2), k2 = e % (KB / 2);
-        rb[i] = *reinterpret_cast<const V2 *>(Bblk + (int64_t)col * ldb + k0 + 2 * k2);
-    }
+// The place in LDS of the g-th 16 bytes of a column of the B tile is
+// g ^ b_swizzle(col): the columns whose first bytes share a bank take
+// different places, so the 16 columns that are read together at one k lie on
+// distinct banks.
+template <class T, int KB>
+__device__ __forceinline__ int b_swizzle(int col) {
+    constexpr int kGran = KB * (int)sizeof(T) / 16, kShare = 16 / kGran;  // columns per 256 bytes of banks
+    return (kShare > 1 ? col / kShare : col) & (kGran - 1);
 }
 
-// Register -> LDS stores: As[k][m]; Bs[n][k ^ (n & 15)] (XOR swizzle keeps
-// the 16 lanes that read one k of 16 consecutive columns on distinct banks).
+// Copy of one k step of KB from the panels straight into LDS, 16 bytes per
+// lane and 1 KB per wave and instruction: A as [k][row], B as [col][place].
+// A wave's KBs start at scalar addresses and its lanes add a fixed offset to
+// them, so a step costs the vector unit next to nothing: FP64 MFMAs and
+// vector instructions of a SIMD exclude each other here, and the 60 vector
+// instructions that each 32 MFMAs carried for addresses, bank swizzles and
+// LDS stores were most of what the matrix cores lost (86 % busy; 93 % now).
+// FP64 offsets have 32 bits (the widest is that of B's last column in a KB:
+// dense_multiply_t picks the k step by it), FP32 ones 64.
 template <class T, int KB, int NTH>
-__device__ __forceinline__ void gemm_lstore(const typename Vec2<T>::t (&ra)[KB * 64 / NTH],
-                                            const typename Vec2<T>::t (&rb)[KB * 64 / NTH], T *As, T *Bs,
-                                            int tid) {
-    typedef typename Vec2<T>::t V2;
+struct StepCopy {
+    static constexpr int kGran = KB * (int)sizeof(T) / 16;                // 16-byte places of a column
+    static constexpr int kVec = 16 / (int)sizeof(T);                      // elements per lane
+    static constexpr int kPer = KB * (int)sizeof(T) / 8 / (NTH / kWave);  // KBs of each tile per wave
+    typedef typename std::conditional<sizeof(T) == 8, uint32_t, int64_t>::type Off;
+    typedef __attribute__((address_space(1))) const void *Src;
+    typedef __attribute__((address_space(3))) void *Dst;
+    const char *a, *b[kPer];  // of the wave, at k = 0
+    Off a_off, b_off[kPer];   // of the lane, bytes
+    int64_t lda;
+    int lds;  // the wave's first element in a tile
+
+    __device__ __forceinline__ StepCopy(const T *Ablk, const T *Bblk, int64_t lda_, int64_t ldb, int w, int lane)
+        : lda(lda_ * (int64_t)sizeof(T)) {
+        lds = w * kPer * 64 * kVec;
+        a = reinterpret_cast<const char *>(Ablk + (int64_t)(lds / BM) * lda_);
+        a_off = (Off)(lane * kVec / BM) * (Off)lda + (lane * kVec % BM) * (int)sizeof(T);
 #pragma unroll
-    for (int i = 0; i < KB * 64 / NTH; ++i) {
-        const int e = tid + NTH * i;
-        const int kk = e >> 6, r2 = e & 63;
-        *reinterpret_cast<V2 *>(&As[kk * BM + 2 * r2]) = ra[i];
+        for (int i = 0; i < kPer; ++i) {
+            const int p0 = w * kPer * 64 + i * 64, c0 = p0 / kGran, col = (p0 + lane) / kGran;
+            b[i] = reinterpret_cast<const char *>(Bblk + (int64_t)c0 * ldb);
+            b_off[i] = (Off)(col - c0) * (Off)(ldb * (int64_t)sizeof(T)) +
+                       (((p0 + lane) % kGran) ^ b_swizzle<T, KB>(col)) * 16;
+        }
     }
+    __device__ __forceinline__ void operator()(int kt, T *As, T *Bs) const {
+        const int64_t k0 = (int64_t)kt * KB;
 #pragma unroll
-    for (int i = 0; i < KB * 64 / NTH; ++i) {
-        const int e = tid + NTH * i;
-        const int col = e / (KB / 2), k2 = e % (KB / 2);
-        const int sw = col & 15;
-        const int base = (2 * k2) ^ (sw & ~1);
-        const V2 v = (sw & 1) ? rb[i].yx : rb[i];
-        *reinterpret_cast<V2 *>(&Bs[col * KB + base]) = v;
+        for (int i = 0; i < kPer; ++i)
+            __builtin_amdgcn_global_load_lds((Src)(a + (k0 + i * (64 * kVec / BM)) * lda + a_off),
+                                             (Dst)(As + lds + i * 64 * kVec), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            __builtin_amdgcn_global_load_lds((Src)(b[i] + k0 * (int)sizeof(T) + b_off[i]),
+                                             (Dst)(Bs + lds + i * 64 * kVec), 16, 0, 0);
+    }
+};
+
+// This wave's copies to LDS have landed, then every wave of the workgroup is here.
+__device__ __forceinline__ void step_sync() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// One k step: wave (wm, wn) multiplies rows (2 t + wm) * 16 .. + 15 (t < 4)
+// with columns wn * 16 NT ...  The rows of a wave alternate with the other's
+// so that the four reads of a k lie 512 bytes apart in pairs: one address
+// register serves all k of the step through the instructions' offsets.
+template <class T, int KB, int NT>
+__device__ __forceinline__ void gemm_step(const T *As, const T *Bs, int w, int lane,
+                                          typename Mfma<T>::acc_t (&acc)[4][NT]) {
+    constexpr int kVec = 16 / (int)sizeof(T);
+    const int wm = w & 1, wn = w >> 1, l16 = lane & 15, lk = lane >> 4;
+#pragma unroll
+    for (int ks = 0; ks < KB / 4; ++ks) {
+        const int k = ks * 4 + lk;
+        T a[4], b[NT];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = As[k * BM + (t * 2 + wm) * 16 + l16];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int col = wn * 16 * NT + t * 16 + l16;
+            b[t] = Bs[col * KB + ((k / kVec) ^ b_swizzle<T, KB>(col)) * kVec + k % kVec];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::step(a[i], b[j], acc[i][j]);
     }
 }
 
 // KB = 16: 64 KB of LDS, two workgroups per CU; KB = 32: 128 KB, one
 // workgroup per CU with twice the prefetch distance and half the barriers.
-// NT: 16-column tiles per wave.  Bound by the matrix cores; what is left is
-// the waves' common stop at the barrier and LDS stores of a k step, which
-// four waves per SIMD (NT = 2, 122 registers) cover better than two (NT = 4,
-// 224 registers): N = 8192 16.82 -> 16.40 ms (67 TFLOP/s).
+// NT: 16-column tiles per wave.  Bound by the matrix cores.  N = 8192 in
+// FP64: 16.82 ms with two waves per SIMD (NT = 4), 16.40 with four (NT = 2,
+// which cover each other's barriers), 15.15 with copies straight to LDS and
+// no address arithmetic in the loop (72.6 of 77.8 TFLOP/s); the same copies
+// with 59 vector instructions per step for addresses: 16.37.
 template <class T, int KB, int NT, int MINW, bool SPLIT>
 __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
     constexpr int NTH = 1024 / NT;
-    __shared__ T As[2][KB * BM];  // [k][m]
-    __shared__ T Bs[2][BN * KB];  // [n][k ^ swizzle(n)]
+    // Two buffers of one k step, as objects of their own: the compiler sees
+    // then that the copies into one do not touch what is read from the other
+    // and does not end them before every LDS read.
+    __shared__ __attribute__((aligned(16))) T As0[KB * BM], As1[KB * BM], Bs0[BN * KB], Bs1[BN * KB];
 
     // XCD-aware remap, then grouped row-major order inside the XCD's band
     // (split k: consecutive logical ids walk the tiles of one split).
@@ -267,38 +313,24 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
     const T *Ablk = static_cast<const T *>(g.Ap) + (int64_t)tm * BM;
     const T *Bblk = static_cast<const T *>(g.Bp) + (int64_t)tn * BN * g.ldb;
 
-    typename Vec2<T>::t ra[KB * 64 / NTH], rb[KB * 64 / NTH];
     typename Mfma<T>::acc_t acc[4][NT];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::zero();
 
-    gemm_gload<T, KB, NTH>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt0, tid);
-    gemm_lstore<T, KB, NTH>(ra, rb, As[0], Bs[0], tid);
-    __syncthreads();
-    for (int kt = kt0; kt < kt1; ++kt) {
-        const int cur = (kt - kt0) & 1;
-        if (kt + 1 < kt1) gemm_gload<T, KB, NTH>(ra, rb, Ablk, Bblk, g.lda, g.ldb, kt + 1, tid);
-#pragma unroll
-        for (int ks = 0; ks < KB / 4; ++ks) {
-            const int k = ks * 4 + lk;
-            T a[4], b[NT];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) a[t] = As[cur][k * BM + wm * 64 + t * 16 + l16];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int col = wn * 16 * NT + t * 16 + l16;
-                b[t] = Bs[cur][col * KB + (k ^ (col & 15))];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    acc[i][j] = Mfma<T>::step(a[i], b[j], acc[i][j]);
-        }
-        if (kt + 1 < kt1) gemm_lstore<T, KB, NTH>(ra, rb, As[cur ^ 1], Bs[cur ^ 1], tid);
-        __syncthreads();
+    const StepCopy<T, KB, NTH> copy(Ablk, Bblk, g.lda, g.ldb, __builtin_amdgcn_readfirstlane(w), lane);
+    copy(kt0, As0, Bs0);
+    step_sync();
+    for (int kt = kt0;;) {
+        if (kt + 1 < kt1) copy(kt + 1, As1, Bs1);
+        gemm_step<T, KB, NT>(As0, Bs0, w, lane, acc);
+        step_sync();
+        if (++kt >= kt1) break;
+        if (kt + 1 < kt1) copy(kt + 1, As0, Bs0);
+        gemm_step<T, KB, NT>(As1, Bs1, w, lane, acc);
+        step_sync();
+        if (++kt >= kt1) break;
     }
 
     // Epilogue: element e of lane l holds row Mfma<T>::row(e, l / 16),
@@ -312,7 +344,7 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) P[(((wn * NT + j) * 2 + wm) * 4 + i) * 64] = acc[i][j];
+            for (int j = 0; j < NT; ++j) P[((wn * NT + j) * 8 + i * 2 + wm) * 64] = acc[i][j];
         return;
     }
 #pragma unroll
@@ -324,7 +356,7 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
             const int2 cm = g.cmap[col];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int64_t row = (int64_t)tm * BM + wm * 64 + i * 16 + Mfma<T>::row(e, lk);
+                const int64_t row = (int64_t)tm * BM + (i * 2 + wm) * 16 + Mfma<T>::row(e, lk);
                 if (row >= g.M) continue;
                 const int2 rm = g.rmap[row];
                 const int64_t bidx = (int64_t)rm.x * g.c_nbc + cm.x;
@@ -486,7 +518,11 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
     const int64_t M = A->rows(), K = A->cols(), N = B->cols();
     if (M == 0 || N == 0 || C->nnzb == 0) return BSMM_OK;
     if (alpha == 0.0 || K == 0) return scale_blocks(C, nullptr, beta, s);
-    const int KB = options().dense_kb == 32 ? 32 : 16;
+    // The FP64 copies add 32-bit offsets of up to seven columns of B with k
+    // step 16 and three with 32 (past the latter's limit, K = 1.7e8, the two
+    // panels would not fit into memory).
+    const bool far = sizeof(T) == 8 && K > (int64_t(1) << 26) - 64;
+    const int KB = options().dense_kb == 32 || far ? 32 : 16;
     const int64_t Mp = ceil_div(M, BM) * BM, Np = ceil_div(N, BN) * BN, Kp = ceil_div(K, KB) * KB;
     const int64_t tiles = (Mp / BM) * (Np / BN);
     if (tiles > kMaxGridBlocks || Mp * Kp > (int64_t(1) << 47) || Kp * Np > (int64_t(1) << 47)) {

@@ -72,3 +72,24 @@ def test_split_k_within_the_scratch_region():
     finally:
         set_path()
     check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("m,n,k", [(130, 250, 33), (64, 40, 2100)])
+def test_k_step_32(m, n, k, dtype):
+    """The longer k step (also the way of FP64 panels whose columns lie too
+    far apart for the short one's offsets), FP64 and FP32, exact."""
+    from tests.helpers import lib
+    from tests.test_gpu_f32 import _as_f32, _f32_multiply
+    rng = rng_of(m * k)
+    rs, ks, ns = (_cover(x, [9, 22, 32], rng) for x in (m, k, n))
+    A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, ns, 1.0, "int")
+    lib().bsmm_set_option("dense_kb", "32")
+    try:
+        if dtype == "f64":
+            X, _ = gpu_multiply(3.0, A, B, 0.0, path="dense")
+        else:
+            X, _ = _f32_multiply(3.0, _as_f32(A), _as_f32(B), 0.0, path="dense")
+    finally:
+        lib().bsmm_set_option("dense_kb", "16")
+    check_against_oracle(X, orc.multiply(3.0, A, B, 0.0), 0.0)
