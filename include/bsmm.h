@@ -215,17 +215,22 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
  *                 "t128" (16x16x64 MFMA, k step 64, one stage) or "t64"
  *                 (64 x 64 tiles); every variant gives the same bits
  *   "stack_kernel" "plain" (default) | "tuned"
- *                 plain: one fixed parameter rule per shape, one launch per
- *                 shape class; tuned: parameters from the tuning database,
- *                 else the learned model, else the plain rule, and all shape
- *                 classes launched together as nodes of one hipGraph
+ *                 plain: one fixed parameter rule per shape; tuned:
+ *                 parameters from the tuning database, else the learned
+ *                 model, else the plain rule.  Classes that "stack_tile"
+ *                 does not gather have a launch each; tuned ones run together
+ *                 as nodes of one hipGraph when a plan is kept or there are
+ *                 more than three
  *   "stack_chunk" maximum products per stack launch, "0" = unlimited
  *                 (paper, Sec. II: batches of at most 30000 products)
- *   "stack_tile"  tuned path: "T" > 0 (default "32") runs every FP64 MFMA
-                 class of blocks up to 32 x 32 whose runs need no splitting
-                 in one launch, its runs ordered by tiles of T x T C blocks
-                 (when those classes hold at least 4096 runs); "0" launches
-                 every class on its own.  Results are the same bits.
+ *   "stack_tile"  "T" > 0 (default "32") runs every MFMA class of blocks up
+                 to 32 x 32 whose runs need no splitting in one launch (when
+                 those classes hold at least 4096 runs), its runs ordered by
+                 tiles of C blocks, T / 8 on a side or, where those would
+                 outnumber the runs, twice, four times, ... that; T on a side
+                 in the allocation-free multiply, which gathers tuned classes
+                 only.  "0" launches every class on its own.  Results are the
+                 same bits.
    "jit"         tuned path: "1" compiles, at run time (hiprtc), an FP64 or
                  FP32 MFMA small-block kernel with m, n and k as compile-time
                  constants for every class whose products share one depth
@@ -249,8 +254,8 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
                  an FP64 launch with many products per block of B reads B's
                  blocks from such copies
    "stack_sched" order in which the scheduled launch's waves take runs:
-                 "dynamic" (default; a run counter, several short runs per
-                 update) or "static" (fixed strides, numbered XCD by XCD)
+                 "dynamic" (default; a run counter per XCD, several short
+                 runs per update) or "static" (fixed strides within the XCD)
    "stack_panel" maximum products held in the stacks at once (default
  *                 "1073741824", 16 GiB of product entries; "0" = no
  *                 limit): a multiply with more products builds and runs

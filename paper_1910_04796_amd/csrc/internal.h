@@ -319,7 +319,9 @@ constexpr int kMaxStackK = 0xFFFF;
 // block row's share of every window found once per multiply.
 constexpr int kMaxStackCols = 8192;
 constexpr int kStackWin = 4096;
-constexpr size_t kSchedCounterBytes = 4 * 256;  // four counters, a line each
+constexpr int kXcds = 8;
+constexpr int kSchedCounterStride = 32;  // in 8-byte words: a line each
+constexpr size_t kSchedCounterBytes = kXcds * kSchedCounterStride * 8;  // one counter per XCD
 // Product stacks of C += A*B, grouped by shape class (m, n).
 struct Stacks {
     int64_t n_runs = 0, n_prod = 0;
@@ -425,12 +427,13 @@ struct SmmArgs {
     void *part;
     // Scheduled MFMA kernel (one launch for every class with blocks up to
     // 32 x 32): entries run << 16 | m << 8 | n in tile order; mode 0 static
-    // XCD-aware striding, 1 run counters (next, zeroed before the launch).
+    // striding, 1 run counters (next, one per XCD, zeroed before the launch).
     const unsigned long long *sched;
     int64_t n_sched;
     unsigned long long *next;
     int sched_mode;
-    int sched_chunk;        // schedule entries taken per wave at a time
+    int sched_chunk;        // schedule entries taken per wave at a time (a power of two)
+    int sched_per_cu;       // most workgroups per CU
     // Scheduled kernel, when the multiply filters: squared Frobenius norm of
     // every finished C block, norm2[run_cblk[r]] (run_cblk: C block of run r).
     double *norm2;

@@ -364,9 +364,8 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
 // order of a schedule that groups the runs by 2-D tiles of C blocks: the
 // waves in flight then work on nearby block rows and block columns and
 // share their A and B blocks in the caches.  Schedule entry: run << 16 |
-// m << 8 | n.  Static mode: wave slots are numbered XCD by XCD (workgroup g
-// runs on XCD g % 8), so each XCD takes a contiguous part of every window
-// of in-flight runs; dynamic mode: waves take the next run from a counter.
+// m << 8 | n.  Static mode: a wave takes every so many-th entry of its XCD;
+// dynamic mode: waves take the next one from the XCD's counter.
 template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, int n) {
     typename Mfma<T>::acc_t acc[MT][NT];
@@ -377,39 +376,36 @@ __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, in
     if (p.norm2 && lane_id() == 0) p.norm2[p.run_cblk[r]] = ss;
 }
 
-constexpr int kXcds = 8;
-// Counters of the dynamic order: counter c hands out every kSchedCounters-th
-// chunk.  Updates of one address follow one another about 15 ns apart, so a
-// single counter bounded launches of many short runs: {5,13,23}-blocks at
-// 25 % (48,000 runs) 505 us with two runs per update, 310 us with four
-// counters and one run; FP32 banded 10 % (1.4 M runs) 11.9 -> 9.4 ms, banded
-// 10 % 69.8 -> 68.0 ms.  Every counter serves workgroups of all XCDs: with a
-// counter per XCD the XCDs drifted apart and the 30 % product lost 5 % (639
-// -> 671 ms); more counters gain nothing (8: the same, 32: 30 % 674 ms).
-constexpr int kSchedCounters = 4;
-constexpr int kSchedCounterStride = 32;  // in 8-byte words: a line each
-static_assert(kSchedCounters * kSchedCounterStride * 8 == kSchedCounterBytes, "counter buffer");
+// Segments of 2^kSegBits schedule entries go to the XCDs in turn (workgroup
+// g runs on XCD g % 8) and each XCD's waves take theirs in order, so that the
+// runs of a tile meet in one L2: banded 30 % 639 -> 611 ms, banded 10 % 67.8 ->
+// 64.9 against one order for all XCDs, with tiles of 32 x 32; segments of 32
+// to 1,024 entries differ by 2 %.  The next entry is taken when the last one is
+// done, not ahead of it: runs taken one after the other also start one after
+// the other, and share operands while they are at the same k (taken ahead:
+// 30 % 563 -> 608 ms).
+//
+// One counter per XCD.  Updates of one address follow one another about 15 ns
+// apart, so a single counter bounded launches of many short runs
+// ({5,13,23}-blocks at 25 %, 48,000 runs: 505 us; four or eight counters 300 us).
+// An XCD that is done does not help the others: reading eight counters in
+// every wave costs 70 us at the end, more than the XCDs differ.
+constexpr int kSegBits = 8;
 // Fewest runs for which the MFMA classes go through the scheduled launch.
 constexpr int64_t kSchedMinRuns = 4096;
 
 template <class T, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     const int wpw = blockDim.x / kWave;
-    const int64_t waves = (int64_t)gridDim.x * wpw;
     // A wave takes `chunk` consecutive entries at a time (short runs: fewer
-    // counter updates), the first ones by its number.
-    const int64_t chunk = p.sched_chunk > 1 ? p.sched_chunk : 1;
-    const int w = uniform(wave_id());
-    int64_t it;
-    if (p.sched_mode == 0) {
-        const int G = gridDim.x, xcd = blockIdx.x % kXcds, loc = blockIdx.x / kXcds;
-        const int before = xcd * (G / kXcds) + min(xcd, G % kXcds);
-        it = ((int64_t)(before + loc) * wpw + w) * chunk;
-    } else {
-        it = ((int64_t)blockIdx.x * wpw + w) * chunk;
-    }
-    const int c = blockIdx.x / kXcds % kSchedCounters;
-    while (it < p.n_sched) {
+    // counter updates), the first ones by its number in its XCD.
+    const int chunk = max(p.sched_chunk, 1);
+    const int x = blockIdx.x % kXcds;
+    const int64_t waves = (int64_t)((gridDim.x - x + kXcds - 1) / kXcds) * wpw;
+    int64_t pos = ((int64_t)(blockIdx.x / kXcds) * wpw + uniform(wave_id())) * chunk;
+    while (true) {
+        const int64_t it = (((pos >> kSegBits) * kXcds + x) << kSegBits) + (pos & ((1 << kSegBits) - 1));
+        if (it >= p.n_sched) break;  // pos only grows, and `it` with it
         const int64_t end = min(it + chunk, p.n_sched);
         for (int64_t i = it; i < end; ++i) {
             const unsigned long long e = scalar_at(p.sched, i);
@@ -424,17 +420,21 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
             }
         }
         if (p.sched_mode == 0) {
-            it += waves * chunk;
+            pos += waves * chunk;
         } else {
             unsigned long long t = 0;
-            if (lane_id() == 0) t = atomicAdd(&p.next[c * kSchedCounterStride], 1ull);
-            it = (waves + uniform((int64_t)t) * kSchedCounters + c) * chunk;
+            if (lane_id() == 0) t = atomicAdd(&p.next[x * kSchedCounterStride], 1ull);
+            pos = (waves + uniform((int64_t)t)) * chunk;
         }
     }
 }
 
+// Six waves per SIMD: each holds one chunk of operands on its way, and the
+// operand stream is bound by the latency of the L2 misses as much as by their
+// rate (banded 30 % at 3 / 4 / 5 / 6 waves: 668 / 589 / 564 / 551 ms).  The
+// registers that do not fit are spilled outside of the loop over products.
 template <class T, OperandLayout LA, OperandLayout LB>
-__global__ __launch_bounds__(256, 4) void k_smm_mfma_sched(SmmArgs p) {
+__global__ __launch_bounds__(256, 6) void k_smm_mfma_sched(SmmArgs p) {
     sched_loop<T, LA, LB>(p);
 }
 
@@ -738,6 +738,7 @@ unsigned smm_grid(const SmmLaunch &L, int64_t nruns) {
             (void)hipGetLastError();
             per_cu = 5;
         }
+        if (L.args.sched_per_cu > 0) per_cu = std::min(per_cu, L.args.sched_per_cu);
         wg_cap = (int64_t)cu_count() * per_cu;
     }
     return grid_of(waves_needed, L.waves, wg_cap);
@@ -761,7 +762,7 @@ int launch_smm(SmmLaunch L, const void *A, const void *B, void *C, const int64_t
         return launch_jit_smm(L.jit_fn, smm_grid(L, re - rb), L.waves, A, B, C, run_coff, run_ptr, prods,
                               rb, re, alpha, beta, s);
     if (is_sched_kernel(L.fn) && a.sched_mode == 1) {
-        hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(kSchedCounters), 0, s, a.next);
+        hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(kXcds), 0, s, a.next);
         BSMM_TRY(launch_check("zero_counters"));
     }
     {
@@ -980,7 +981,10 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         // two products per run: 1.26 / 1.25 / 1.26 / 1.29 / 1.33 ms for 1 / 2
         // / 4 / 8 / 16 runs per update).
         const int64_t mean_len = std::max<int64_t>(1, sched_prods / sched_runs);
-        L.args.sched_chunk = (int)std::max<int64_t>(1, 4 / mean_len);
+        L.args.sched_chunk = mean_len >= 4 ? 1 : mean_len >= 2 ? 2 : 4;
+        // Runs that short gain nothing from more than four waves per SIMD
+        // (banded 1 % at 4 / 5 / 6: 1.19 / 1.26 / 1.37 ms).
+        L.args.sched_per_cu = mean_len < 4 ? 4 : 0;
         L.waves = 4;
         L.lds = 0;
         launches.push_back({L, {0, st.n_sched}});
@@ -1094,7 +1098,7 @@ int build_graph(const LaunchList &launches, const bsmm_matrix_s *A, const bsmm_m
             hipKernelNodeParams zp{};
             zp.func = (void *)k_zero_counters;
             zp.gridDim = dim3(1);
-            zp.blockDim = dim3(kSchedCounters);
+            zp.blockDim = dim3(kXcds);
             zp.sharedMemBytes = 0;
             zp.kernelParams = &zargp;
             zp.extra = nullptr;

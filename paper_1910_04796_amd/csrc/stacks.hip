@@ -575,13 +575,28 @@ __global__ __launch_bounds__(256) void k_sched_scatter(int64_t nruns, const int6
 
 }  // namespace
 
+// Edge of the schedule's tiles for the option's T: T / 8 C blocks.  Waves that
+// start one after the other run side by side and share what the L2 of their
+// XCD can hold of A and B, so few neighbours both ways beat a large tile
+// (scheduled kernel, ms, edges 2 / 4 / 8 / 16 / 32: banded 30 % 576 / 563 /
+// 596 / 631 / 635, banded 10 % 63.4 / 62.6 / 63.2 / 63.7 / 65.7, FP32 banded
+// 10 % 8.34 / 8.41 / 8.58 / 8.68 / 8.85; 1 % and products of a few ms the same
+// for all).  Edges grow until the tiles are no more than the runs or 65,536;
+// on a scratch arena they are T, whose tables are the smallest.
+static int tile_edge(int T, int64_t nbr, int64_t nbc, int64_t runs) {
+    if (scratch_arena()) return std::max(T, 1);
+    int64_t e = std::max(T / 8, 1);
+    while (ceil_div(nbr, e) * ceil_div(nbc, e) > std::max<int64_t>(runs, 65536)) e *= 2;
+    return (int)e;
+}
+
 int build_schedule(const bsmm_matrix_s *C, Stacks &st, const std::vector<char> &eligible, int tile,
                    hipStream_t s) {
     st.n_sched = 0;
     for (int cl = 0; cl < st.n_classes; ++cl)
         if (eligible[cl]) st.n_sched += st.class_begin[cl + 1] - st.class_begin[cl];
     if (st.n_sched == 0) return BSMM_OK;
-    tile = std::max(tile, 1);
+    tile = tile_edge(tile, C->nbr, C->nbc, st.n_sched);
     const int64_t nti = ceil_div(C->nbr, tile), ntj = ceil_div(C->nbc, tile);
     const int64_t ntiles = nti * ntj;
     DevBuf flags, hist, off;

@@ -41,6 +41,30 @@ def test_product_depths(k):
     check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
 
 
+@pytest.mark.parametrize("sched", ["static", "dynamic"])
+@pytest.mark.parametrize("tile", [1, 32, 200])
+@pytest.mark.parametrize("depth,occ", [(1, 1.0), (2, 1.0), (9, 0.8)])
+def test_schedule_segments(depth, occ, tile, sched):
+    """Schedules of several segments per XCD with an incomplete last one,
+    runs taken four, two and one at a time: every C block is written once."""
+    rng = rng_of(depth)
+    rs, ns = (rng.choice([5, 13, 20], size=s).astype(np.int32) for s in (163, 171))
+    A, B = _matrices(depth + 200, rs, np.full(depth, 3, np.int32), ns, occ, "int")
+    Cin = make_matrix(rng, rs, ns, 0.2, "int")
+    b = lib()
+    saved = {k: b.bsmm_get_option(k) for k in ("stack_tile", "stack_sched", "stack_params")}
+    b.bsmm_set_option("stack_tile", str(tile))
+    b.bsmm_set_option("stack_sched", sched)
+    b.bsmm_set_option("stack_params", "16 16 0 4")
+    try:
+        X, st = gpu_multiply(1.0, A, B, -2.0, Cin, path="stack", kernel="tuned")
+    finally:
+        for k, v in saved.items():
+            b.bsmm_set_option(k, v)
+    assert st["n_sched_runs"] > 16 * 256 and st["n_sched_runs"] % 256
+    check_against_oracle(X, orc.multiply(1.0, A, B, -2.0, Cin), 0.0)
+
+
 def test_copied_b_same_bits():
     """Enough products per B block for row-major copies of B: the same bits
     as reading both operands in place (stack_at "1" keeps B in place), and a
