@@ -11,6 +11,12 @@ typedef double v2d_t __attribute__((ext_vector_type(2)));
 typedef float v2f_t __attribute__((ext_vector_type(2)));
 typedef float v4f_t __attribute__((ext_vector_type(4)));
 
+// Buffer of `bytes` bytes at p (both the same on every lane).
+typedef __amdgpu_buffer_rsrc_t BufferRsrc;
+__device__ __forceinline__ BufferRsrc buffer_at(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);  // raw, 32-bit data
+}
+
 // Both instructions take lane l's operands at row (or column) l % 16 and
 // k = l / 16 of the step and return four results per lane.
 template <class T> struct Mfma;
@@ -22,13 +28,21 @@ template <> struct Mfma<double> {
     }
     // Result element e of lane l: row 4 e + l / 16, column l % 16.
     static __device__ __forceinline__ int row(int e, int lk) { return 4 * e + lk; }
-    // Two consecutive values (one 16-byte load at 8-byte alignment: dword
-    // alignment is all the vector loads need), and their store.
-    static __device__ __forceinline__ void load2(const double *p, double &x, double &y) {
-        v2d_t v;
-        __builtin_memcpy(&v, p, sizeof v);
-        x = v[0];
-        y = v[1];
+    // One value, and two consecutive ones (16 bytes at 8-byte alignment:
+    // dword alignment is all the vector loads need), at a byte offset of a
+    // buffer; dwords past the buffer's end read as zero.
+    static __device__ __forceinline__ double load(BufferRsrc r, uint32_t off) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        double x;
+        __builtin_memcpy(&x, &v, sizeof x);
+        return x;
+    }
+    static __device__ __forceinline__ void load2(BufferRsrc r, uint32_t off, double &x, double &y) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+        v2d_t d;
+        __builtin_memcpy(&d, &v, sizeof d);
+        x = d[0];
+        y = d[1];
     }
     static __device__ __forceinline__ void store2(double *p, double x, double y) {
         const v2d_t v = {x, y};
@@ -43,11 +57,18 @@ template <> struct Mfma<float> {
     }
     // Result element e of lane l: row 4 (l / 16) + e, column l % 16.
     static __device__ __forceinline__ int row(int e, int lk) { return 4 * lk + e; }
-    static __device__ __forceinline__ void load2(const float *p, float &x, float &y) {
-        v2f_t v;
-        __builtin_memcpy(&v, p, sizeof v);
-        x = v[0];
-        y = v[1];
+    static __device__ __forceinline__ float load(BufferRsrc r, uint32_t off) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+        float x;
+        __builtin_memcpy(&x, &v, sizeof x);
+        return x;
+    }
+    static __device__ __forceinline__ void load2(BufferRsrc r, uint32_t off, float &x, float &y) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+        v2f_t d;
+        __builtin_memcpy(&d, &v, sizeof d);
+        x = d[0];
+        y = d[1];
     }
     static __device__ __forceinline__ void store2(float *p, float x, float y) {
         const v2f_t v = {x, y};

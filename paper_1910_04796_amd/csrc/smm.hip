@@ -162,79 +162,80 @@ template <int NTILE> __device__ __forceinline__ int tile_row(int t, int r) {
     return (t | 1) < NTILE ? 32 * (t >> 1) + 2 * r + (t & 1) : 16 * t + r;
 }
 
-// Byte offsets of one operand's loads from its chunk of 8 values of k; ext
-// is the block's row (column) count, k the product's depth.  Lane group lk
-// supplies k = 2 lk + s of the chunk to MFMA step s.  (Past the last value
-// of k the offsets repeat it; mfma_chunk zeroes those values.)
-template <class T, int NTILE, OperandLayout LAY> struct OperandOffsets {
-    // kAlongTile: rows of value s = 0; kAlongK: see of_depth.
-    uint32_t at[NTILE];
-    uint32_t step;  // bytes from one value of k to the next
-    __device__ __forceinline__ void init(int ext, int lr, int lk) {
+// One operand's loads, a chunk of 8 values of k at a time: lane group lk
+// supplies k = 2 lk + s of the chunk to MFMA step s.  The chunk is a buffer
+// from its first value to the end of its block, so what lies past the block
+// reads as zero (rows and columns past the block reach results that are not
+// stored) and the lanes' offsets stay the same for all products of a run.
+template <class T, int NTILE, OperandLayout LAY> struct Operand {
+    static constexpr uint32_t kSize = sizeof(T);
+    const char *data;
+    const char *at;   // the chunk
+    uint32_t bytes;   // from there to the end of the block; 0: past the run
+    uint32_t step;    // bytes of a chunk
+    int ext;          // rows (columns) of the block
+    // Byte offsets of the lane: kAlongTile: column s of the first two tiles
+    // (of the only one); kAlongK: row of tile t.
+    uint32_t off[LAY == kAlongTile ? 2 : NTILE];
+
+    __device__ __forceinline__ void init(const void *d, int ext_, int lr, int lk) {
+        data = static_cast<const char *>(d);
+        ext = ext_;
+        step = (LAY == kAlongTile ? 8 * (uint32_t)ext : 8u) * kSize;
         if (LAY == kAlongTile) {
-            step = (uint32_t)ext * sizeof(T);
-#pragma unroll
-            for (int t = 0; t < NTILE; ++t) at[t] = 2 * lk * step + row(t, ext, lr) * (uint32_t)sizeof(T);
-        } else {
-            step = sizeof(T);
-#pragma unroll
-            for (int t = 0; t < NTILE; ++t) at[t] = row(t, ext, lr);  // times the depth, per product
+            off[0] = (2 * lk * (uint32_t)ext + (NTILE > 1 ? 2 * lr : lr)) * kSize;
+            off[1] = off[0] + (uint32_t)ext * kSize;
         }
     }
-    // The row that lane index lr of tile t loads (a pair's first row for
-    // tiles that share their loads), inside the block.
-    static __device__ __forceinline__ uint32_t row(int t, int ext, int lr) {
-        if (LAY == kAlongTile) return min((t | 1) < NTILE ? 16 * (t & ~1) + 2 * lr : 16 * t + lr, ext - 1);
-        return min(tile_row<NTILE>(t, lr), ext - 1);
-    }
-    // base: the block's chunk; left: values of k from the chunk's first one.
-    __device__ __forceinline__ void load(const char *base, int k, int left, int lk, T (&f)[2][NTILE]) const {
-        if (LAY == kAlongTile) {
-            uint32_t back0 = 0, back1 = 0;
-            if (left < 8) {
-                // Steps back from a value past the block to its last one.
-                back0 = (uint32_t)max(2 * lk + 1 - left, 0) * step;
-                back1 = (uint32_t)max(2 * lk + 2 - left, 0) * step;
-            }
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const uint32_t add = s * step - (s ? back1 : back0);
-#pragma unroll
-                for (int t = 0; t + 1 < NTILE; t += 2) {
-                    // The pair may end one past the block: every data buffer
-                    // holds one element more than its blocks.
-                    Mfma<T>::load2(reinterpret_cast<const T *>(base + (at[t] + add)), f[s][t], f[s][t + 1]);
-                }
-                if (NTILE & 1) f[s][NTILE - 1] = *reinterpret_cast<const T *>(base + (at[NTILE - 1] + add));
-            }
-        } else {
-            const uint32_t kk = left < 8 ? min(2 * lk, left - 1) : 2 * lk;
+    __device__ __forceinline__ void block(uint64_t elem, int k, int lr, int lk) {
+        at = data + elem * kSize;
+        bytes = (uint32_t)ext * (uint32_t)k * kSize;
+        if (LAY == kAlongK) {
 #pragma unroll
             for (int t = 0; t < NTILE; ++t)
-                Mfma<T>::load2(reinterpret_cast<const T *>(base + (at[t] * (uint32_t)k + kk) * (uint32_t)sizeof(T)),
-                               f[0][t], f[1][t]);
+                off[t] = ((uint32_t)tile_row<NTILE>(t, lr) * (uint32_t)k + 2 * lk) * kSize;
+        }
+    }
+    __device__ __forceinline__ void next_chunk() {
+        at += step;
+        bytes -= step;
+    }
+    // left: values of k from the chunk's first one.
+    __device__ __forceinline__ void load(int left, int lr, int lk, T (&f)[2][NTILE]) const {
+        const BufferRsrc r = buffer_at(at, bytes);
+        if (LAY == kAlongTile) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+#pragma unroll
+                for (int t = 0; t + 1 < NTILE; t += 2) Mfma<T>::load2(r, off[s] + 16 * t * kSize, f[s][t], f[s][t + 1]);
+                if (NTILE == 1) f[s][0] = Mfma<T>::load(r, off[s]);
+                else if (NTILE & 1) f[s][NTILE - 1] = Mfma<T>::load(r, off[s] + (16 * (NTILE - 1) - lr) * kSize);
+            }
+        } else {
+            // Past the row's last k lies the next row: such lanes read past
+            // the buffer, and half a pair is cleared by mfma_chunk.
+#pragma unroll
+            for (int t = 0; t < NTILE; ++t) Mfma<T>::load2(r, 2 * lk < left ? off[t] : ~0u, f[0][t], f[1][t]);
         }
     }
 };
 
 // One chunk of 8 values of k of a product: its operands, and how many values
-// from the chunk's first one lie inside the block.
+// from the chunk's first one lie inside the block (0: past the run).
 template <class T, int MT, int NT> struct Chunk {
     T a[2][MT], b[2][NT];
     int left;
 };
 
-template <class T, int MT, int NT>
+template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void mfma_chunk(Chunk<T, MT, NT> &c, int lk, typename Mfma<T>::acc_t (&acc)[MT][NT]) {
-    if (c.left < 8) {
+    if (LA == kAlongK) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const bool in = 2 * lk + s < c.left;
+        for (int i = 0; i < MT; ++i) c.a[1][i] = 2 * lk + 1 < c.left ? c.a[1][i] : T(0);
+    }
+    if (LB == kAlongK) {
 #pragma unroll
-            for (int i = 0; i < MT; ++i) c.a[s][i] = in ? c.a[s][i] : T(0);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) c.b[s][j] = in ? c.b[s][j] : T(0);
-        }
+        for (int j = 0; j < NT; ++j) c.b[1][j] = 2 * lk + 1 < c.left ? c.b[1][j] : T(0);
     }
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -246,11 +247,17 @@ __device__ __forceinline__ void mfma_chunk(Chunk<T, MT, NT> &c, int lk, typename
 
 // Products [q0, q1) of one run into the MT x NT accumulator tiles of an
 // m x n C block (q0, q1, m and n the same on every lane: descriptors, depths
-// and block addresses stay on the scalar unit, a lane adds its offset).  The
-// products' chunks follow one another without a break: the operands of the
-// next chunk (of the next product where one ends) are on their way while a
-// chunk is multiplied, the descriptor of the product after it one product
-// earlier.
+// and block addresses stay on the scalar unit).  The products' chunks follow
+// one another without a break: the operands of the next chunk (of the next
+// product where one ends) are on their way while a chunk is multiplied, the
+// descriptor of the product after it one product earlier.
+//
+// Two chunk variables in turn and no vector instruction besides loads and
+// MFMAs: on FP64, whose MFMAs and vector instructions exclude each other, the
+// copies between chunk variables, offsets and tail masks took a quarter of the
+// MFMAs' time.  23-blocks at 20 % 1.75 -> 1.50 ms, {5,13,23} at 25 % 296 -> 241
+// us, uniform 64-blocks at 20 % 1.68 -> 1.30 ms (FP32: 0.69 -> 0.57).  More
+// chunks ahead gain nothing (2, 3, 5: the same within 2 %).
 template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, int64_t q0, int64_t q1,
                                               typename Mfma<T>::acc_t (&acc)[MT][NT]) {
@@ -263,40 +270,44 @@ __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, in
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = Mfma<T>::zero();
     if (q0 >= q1) return;
-    const char *A = static_cast<const char *>(LA == kAlongK ? p.A_t : p.A);
-    const char *B = static_cast<const char *>(LB == kAlongTile ? p.B_t : p.B);
-    OperandOffsets<T, MT, LA> oa;
-    OperandOffsets<T, NT, LB> ob;
-    oa.init(m, lr, lk);
-    ob.init(n, lr, lk);
-    u64x2 pr = scalar_at(prods, q0), nxt = scalar_at(prods, min(q0 + 1, q1 - 1));
-    const char *a = A + (pr.x & ((1ull << 48) - 1)) * sizeof(T), *b = B + pr.y * sizeof(T);
-    int k = (int)(pr.x >> 48), left = k;
+    Operand<T, MT, LA> oa;
+    Operand<T, NT, LB> ob;
+    oa.init(LA == kAlongK ? p.A_t : p.A, m, lr, lk);
+    ob.init(LB == kAlongTile ? p.B_t : p.B, n, lr, lk);
+    u64x2 nxt = scalar_at(prods, q0);
     int64_t q = q0;
+    int left = 0;
+    auto advance = [&] {  // to product q
+        left = (int)(nxt.x >> 48);
+        oa.block(nxt.x & ((1ull << 48) - 1), left, lr, lk);
+        ob.block(nxt.y, left, lr, lk);
+        if (q >= q1) {
+            left = 0;
+            oa.bytes = ob.bytes = 0;
+        }
+        ++q;
+        nxt = scalar_at(prods, min(q, q1 - 1));
+    };
     auto load = [&](Chunk<T, MT, NT> &c) {
-        oa.load(a, k, left, lk, c.a);
-        ob.load(b, k, left, lk, c.b);
+        oa.load(left, lr, lk, c.a);
+        ob.load(left, lr, lk, c.b);
         c.left = left;
         left -= 8;
-        a += 8 * oa.step;
-        b += 8 * ob.step;
-        if (left <= 0) {
-            ++q;
-            a = A + (nxt.x & ((1ull << 48) - 1)) * sizeof(T);
-            b = B + nxt.y * sizeof(T);
-            k = left = (int)(nxt.x >> 48);
-            nxt = scalar_at(prods, min(q + 1, q1 - 1));
-        }
+        oa.next_chunk();
+        ob.next_chunk();
+        if (left <= 0) advance();
     };
-    Chunk<T, MT, NT> cur, next;
-    load(cur);
-    bool more;
+    Chunk<T, MT, NT> c0, c1;
+    advance();
+    load(c0);
+    asm volatile("" : "+s"(c0.left));  // (a known first chunk would get a copy of the loop)
     do {
-        more = q < q1;
-        if (more) load(next);
-        mfma_chunk(cur, lk, acc);
-        cur = next;
-    } while (more);
+        load(c1);
+        mfma_chunk<T, MT, NT, LA, LB>(c0, lk, acc);
+        load(c0);
+        // (A branch around so many accumulators would copy them; zeros add nothing.)
+        if (MT * NT > 8 || c1.left > 0) mfma_chunk<T, MT, NT, LA, LB>(c1, lk, acc);
+    } while (c0.left > 0);
 }
 
 // C block (column-major, ld = m) <- beta C + alpha acc, or the unscaled
@@ -429,12 +440,8 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     }
 }
 
-// Six waves per SIMD: each holds one chunk of operands on its way, and the
-// operand stream is bound by the latency of the L2 misses as much as by their
-// rate (banded 30 % at 3 / 4 / 5 / 6 waves: 668 / 589 / 564 / 551 ms).  The
-// registers that do not fit are spilled outside of the loop over products.
 template <class T, OperandLayout LA, OperandLayout LB>
-__global__ __launch_bounds__(256, 6) void k_smm_mfma_sched(SmmArgs p) {
+__global__ __launch_bounds__(256, 4) void k_smm_mfma_sched(SmmArgs p) {
     sched_loop<T, LA, LB>(p);
 }
 
@@ -982,9 +989,13 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         // / 4 / 8 / 16 runs per update).
         const int64_t mean_len = std::max<int64_t>(1, sched_prods / sched_runs);
         L.args.sched_chunk = mean_len >= 4 ? 1 : mean_len >= 2 ? 2 : 4;
-        // Runs that short gain nothing from more than four waves per SIMD
-        // (banded 1 % at 4 / 5 / 6: 1.19 / 1.26 / 1.37 ms).
-        L.args.sched_per_cu = mean_len < 4 ? 4 : 0;
+        // Waves in flight share what an L2 holds, so fewer of them find more
+        // there: FP64 three waves per SIMD (2 / 3 / 4 / 5: banded 10 % 61.6 / 58.6
+        // / 60.3 / 60.9 ms, 30 % 540 / 537 / 564 / 565, 1 % - / 1.23 / 1.24 / 1.22),
+        // FP32, half the bytes each, four (banded 10 % 8.04 / 7.80 / 7.90 with 3
+        // / 4 / 5); launches of few runs also four, to end together (48,000
+        // runs 251 / 236 / 233 us with 3 / 4 / 5).
+        L.args.sched_per_cu = C->dtype == BSMM_F64 && st.n_sched >= 65536 ? 3 : 4;
         L.waves = 4;
         L.lds = 0;
         launches.push_back({L, {0, st.n_sched}});

@@ -65,6 +65,35 @@ def test_schedule_segments(depth, occ, tile, sched):
     check_against_oracle(X, orc.multiply(1.0, A, B, -2.0, Cin), 0.0)
 
 
+@pytest.mark.parametrize("at", ["auto", "0", "1"])
+@pytest.mark.parametrize("blocks", [70, 20])
+@pytest.mark.parametrize("depths", [[1, 7], [8, 13], [5, 23, 24]])
+def test_infinities_stay_in_their_rows_and_columns(depths, blocks, at):
+    """Infinities anywhere in the blocks reach only the elements of C that
+    their rows and columns stand for: values read past a row, a column or the
+    depth of a block never do.  One launch (70 x 70 C blocks) and one per
+    class, A and B read in place and from row-major copies."""
+    rng = rng_of(blocks + depths[0])
+    rs = rng.choice([9, 16, 17, 23], size=blocks).astype(np.int32)
+    A, B = _matrices(depths[-1], rs, np.asarray(depths, np.int32), rs, 1.0, "int")
+    for M, v in ((A, np.inf), (B, -np.inf)):
+        M.data[rng.random(M.data.size) < 0.003] = v
+    b = lib()
+    saved = {k: b.bsmm_get_option(k) for k in ("stack_at", "stack_params")}
+    b.bsmm_set_option("stack_at", at)
+    b.bsmm_set_option("stack_params", "16 16 0 4")
+    try:
+        X, st = gpu_multiply(1.0, A, B, 0.0, path="stack", kernel="tuned")
+    finally:
+        for k, v in saved.items():
+            b.bsmm_set_option(k, v)
+    assert (st["n_sched_runs"] > 0) == (blocks == 70)
+    with np.errstate(invalid="ignore"):
+        R = orc.multiply(1.0, A, B, 0.0)
+    assert 0.02 < np.isfinite(R.data).mean() < 1.0
+    check_against_oracle(X, R, 0.0)
+
+
 def test_copied_b_same_bits():
     """Enough products per B block for row-major copies of B: the same bits
     as reading both operands in place (stack_at "1" keeps B in place), and a
