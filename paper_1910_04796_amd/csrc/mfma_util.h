@@ -30,7 +30,7 @@ template <> struct Mfma<double> {
     static __device__ __forceinline__ int row(int e, int lk) { return 4 * e + lk; }
     // One value, and two consecutive ones (16 bytes at 8-byte alignment:
     // dword alignment is all the vector loads need), at a byte offset of a
-    // buffer; dwords past the buffer's end read as zero.
+    // buffer; dwords past the buffer's end read as zero (and are not stored).
     static __device__ __forceinline__ double load(BufferRsrc r, uint32_t off) {
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
         double x;
@@ -43,6 +43,12 @@ template <> struct Mfma<double> {
         __builtin_memcpy(&d, &v, sizeof d);
         x = d[0];
         y = d[1];
+    }
+    static __device__ __forceinline__ void store(BufferRsrc r, uint32_t off, double x) {
+        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+        u32x2 v;
+        __builtin_memcpy(&v, &x, sizeof v);
+        __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
     }
     static __device__ __forceinline__ void store2(double *p, double x, double y) {
         const v2d_t v = {x, y};
@@ -69,6 +75,11 @@ template <> struct Mfma<float> {
         __builtin_memcpy(&d, &v, sizeof d);
         x = d[0];
         y = d[1];
+    }
+    static __device__ __forceinline__ void store(BufferRsrc r, uint32_t off, float x) {
+        unsigned int v;
+        __builtin_memcpy(&v, &x, sizeof v);
+        __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, 0);
     }
     static __device__ __forceinline__ void store2(float *p, float x, float y) {
         const v2f_t v = {x, y};

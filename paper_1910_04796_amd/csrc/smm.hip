@@ -314,32 +314,64 @@ __device__ __forceinline__ void mfma_products(const SmmArgs &p, int m, int n, in
 // accumulators into a partial block when alpha is not applied here.  With
 // SUMSQ, returns on every lane the squared Frobenius norm of the stored
 // block (summed in FP64: each lane's elements in order, then across the
-// wave in a fixed order).
+// wave in a fixed order).  The block is a buffer: columns past it lie past
+// the buffer's end, and so do the offsets of rows past it, so all elements
+// are loaded (a tile column's together; one after another, each behind the
+// store before it, they made up a third of a short accumulating launch: 72
+// runs 10.5 -> 9 us) and stored without branches.
 template <class T, int MT, int NT, bool SUMSQ>
 __device__ __forceinline__ double mfma_store(T *c, int m, int n,
                                              const typename Mfma<T>::acc_t (&acc)[MT][NT],
                                              bool partial, T alpha, T beta) {
+    constexpr uint32_t kSize = sizeof(T), kOut = 1u << 31;
     const int lane = lane_id();
     const int lr = lane & 15, lk = lane >> 4;
+    const BufferRsrc r = buffer_at(c, (uint32_t)m * (uint32_t)n * kSize);
+    uint32_t ro[MT][4];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = tile_row<MT>(i, Mfma<T>::row(e, lk));
+            ro[i][e] = row < m ? (uint32_t)row * kSize : kOut;
+        }
     double ss = 0.0;
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int col = tile_row<NT>(j, lr);
-        if (col >= n) continue;
+        const uint32_t co = (uint32_t)col * (uint32_t)m * kSize;
+        T v[MT][4];
+        if (partial) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = acc[i][j][e];
+        } else if (beta == T(0)) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = alpha * acc[i][j][e];
+        } else {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = Mfma<T>::load(r, co + ro[i][e]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const T prod = alpha * acc[i][j][e];
+                    v[i][e] = fma(beta, v[i][e], prod);
+                }
+        }
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int row = tile_row<MT>(i, Mfma<T>::row(e, lk));
-                if (row < m) {
-                    T *dst = c + (int64_t)col * m + row;
-                    T v = acc[i][j][e];
-                    if (!partial) {
-                        const T prod = alpha * v;
-                        v = (beta == T(0)) ? prod : fma(beta, *dst, prod);
-                    }
-                    *dst = v;
-                    if (SUMSQ) ss = fma((double)v, (double)v, ss);
+                Mfma<T>::store(r, co + ro[i][e], v[i][e]);
+                if (SUMSQ) {
+                    const double x = ro[i][e] != kOut && col < n ? (double)v[i][e] : 0.0;
+                    ss = fma(x, x, ss);
                 }
             }
     }
@@ -360,14 +392,10 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
         const int sg = (int)(it % S);
         const int64_t rq0 = scalar_at(p.run_ptr, r), len = scalar_at(p.run_ptr, r + 1) - rq0;
         const int64_t q0 = rq0 + len * sg / S, q1 = rq0 + len * (sg + 1) / S;
+        T *c = S > 1 ? static_cast<T *>(p.part) + it * (int64_t)m * n : static_cast<T *>(p.C) + scalar_at(p.run_coff, r);
         typename Mfma<T>::acc_t acc[MT][NT];
         mfma_products<T, MT, NT, kAlongTile, kAlongK>(p, m, n, q0, q1, acc);
-        if (S > 1)
-            mfma_store<T, MT, NT, false>(static_cast<T *>(p.part) + it * (int64_t)m * n, m, n, acc, true,
-                                         T(0), T(0));
-        else
-            mfma_store<T, MT, NT, false>(static_cast<T *>(p.C) + scalar_at(p.run_coff, r), m, n, acc, false,
-                                         (T)p.alpha, (T)p.beta);
+        mfma_store<T, MT, NT, false>(c, m, n, acc, S > 1, (T)p.alpha, (T)p.beta);
     }
 }
 
@@ -380,10 +408,10 @@ __global__ __launch_bounds__(256) void k_smm_mfma(SmmArgs p) {
 template <class T, int MT, int NT, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, int n) {
     typename Mfma<T>::acc_t acc[MT][NT];
+    T *c = static_cast<T *>(p.C) + scalar_at(p.run_coff, r);
     mfma_products<T, MT, NT, LA, LB>(p, m, n, scalar_at(p.run_ptr, r), scalar_at(p.run_ptr, r + 1), acc);
     // One store path: the norm is summed whether or not the filter wants it.
-    const double ss = mfma_store<T, MT, NT, true>(static_cast<T *>(p.C) + scalar_at(p.run_coff, r), m, n, acc, false,
-                                                  (T)p.alpha, (T)p.beta);
+    const double ss = mfma_store<T, MT, NT, true>(c, m, n, acc, false, (T)p.alpha, (T)p.beta);
     if (p.norm2 && lane_id() == 0) p.norm2[p.run_cblk[r]] = ss;
 }
 
