@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kRowThreads) void k_symbolic_count(
     int32_t nbr, int32_t nbc, const int64_t *a_rp, const int32_t *a_ci, const int64_t *b_rp,
     const int32_t *b_ci, const int64_t *c_rp, const int32_t *c_ci, const int32_t *rbs,
     const int32_t *kbs, const int32_t *cbs, int64_t *row_nnz, int64_t *row_elems,
-    int64_t *row_prod, double *row_flops) {
+    int64_t *row_prod, double *row_flops, RowCounts *rows) {
     extern __shared__ uint32_t bm[];
     __shared__ int64_t red_i[16];
     __shared__ double red_d[16];
@@ -121,6 +121,7 @@ __global__ __launch_bounds__(kRowThreads) void k_symbolic_count(
             row_elems[row] = m * cols;
             row_prod[row] = np;
             row_flops[row] = 2.0 * (double)m * kn;
+            if (rows) rows[row] = RowCounts{cnt, m * cols, np, 2.0 * (double)m * kn};
         }
         __syncthreads();  // the bitmap is cleared for the next row
     }
@@ -455,7 +456,7 @@ static int bitmap_lds_bytes(int32_t nbc, size_t *bytes) {
 
 int symbolic_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix_s *C,
                    int64_t *d_row_nnz, int64_t *d_row_elems, int64_t *d_row_prod,
-                   double *d_row_flops, hipStream_t s) {
+                   double *d_row_flops, RowCounts *d_rows, hipStream_t s) {
     if (A->nbr == 0) return BSMM_OK;
     size_t lds;
     BSMM_TRY(bitmap_lds_bytes(B->nbc, &lds));
@@ -464,7 +465,7 @@ int symbolic_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_ma
                        A->d_row_ptr(), A->d_col_ind(), B->d_row_ptr(), B->d_col_ind(),
                        has_c ? C->d_row_ptr() : nullptr, has_c ? C->d_col_ind() : nullptr,
                        A->d_rbs(), B->d_rbs(), B->d_cbs(), d_row_nnz, d_row_elems, d_row_prod,
-                       d_row_flops);
+                       d_row_flops, d_rows);
     return launch_check("symbolic_count");
 }
 

@@ -292,9 +292,15 @@ int symbolic_count_screen(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const 
                           int64_t *d_row_screened, int64_t *d_row_old_screened, hipStream_t s);
 int symbolic_fill_bits(int32_t nbr, int32_t nbc, const uint32_t *d_bits, const int64_t *d_new_row_ptr,
                        int32_t *d_new_col_ind, hipStream_t s);
+// Counts of one C block row; symbolic_count also writes them to d_rows unless
+// that is null.
+struct RowCounts {
+    int64_t nnz, elems, products;
+    double flops;
+};
 int symbolic_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix_s *C,
                    int64_t *d_row_nnz, int64_t *d_row_elems, int64_t *d_row_prod,
-                   double *d_row_flops, hipStream_t s);
+                   double *d_row_flops, RowCounts *d_rows, hipStream_t s);
 int symbolic_fill(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix_s *C,
                   const int64_t *d_new_row_ptr, int32_t *d_new_col_ind, hipStream_t s);
 // Every block present: row_ptr[i] = i*nbc, col_ind = 0..nbc-1 per row,
@@ -341,7 +347,6 @@ struct Stacks {
     DevBuf run_of_c;   // int64[C.nnzb]   run of every C block in its panel, or -1
     DevBuf d_rsi, d_csi;              // size-class index of rows / columns while a scratch arena is active
     const int32_t *rsi = nullptr, *csi = nullptr;  // ... where it lies (there, or in C)
-    DevBuf missing;                   // pattern flag
     bool screened = false;            // C's pattern came from the screen: products of left-out blocks are skipped
     DevBuf a_t;                       // A's blocks transposed, for the scheduled launch (option stack_at)
     DevBuf b_t;                       // B's blocks transposed, for the scheduled launch

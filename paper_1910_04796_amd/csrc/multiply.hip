@@ -28,6 +28,8 @@ struct RowTotals {
     int64_t nnz, elems, products, screened, old_screened;
     double flops;
 };
+// C block rows whose counts go to the host one by one.
+constexpr int kFewRows = 256;
 __global__ __launch_bounds__(256) void k_row_totals(int32_t nbr, const int64_t *nnz,
                                                     const int64_t *elems, const int64_t *prod,
                                                     const double *flops, const int64_t *scr,
@@ -169,17 +171,34 @@ int symbolic(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, SymbolicTotal
     BSMM_TRY(rnnz.reserve(sizeof(int64_t) * (nbr + 1), s));
     BSMM_TRY(rprod.reserve(sizeof(int64_t) * (nbr + 1), s));
     BSMM_TRY(rflops.reserve(sizeof(double) * (nbr + 1), s));
-    BSMM_TRY(sums.reserve(sizeof(RowTotals), s));
+    // Few rows: the counting kernel hands every row's counts to the host,
+    // which adds them up (in one more launch, 8 of 90 us for 20 rows; exact
+    // either way: all are whole numbers).
+    const bool few = nbr <= kFewRows && !scratch_arena();
+    BSMM_TRY(sums.reserve(few ? sizeof(RowCounts) * nbr : sizeof(RowTotals), s));
     BSMM_TRY(symbolic_count(A, B, C, rnnz.as<int64_t>(), row_elems.as<int64_t>(),
-                            rprod.as<int64_t>(), rflops.as<double>(), s));
-    hipLaunchKernelGGL(k_row_totals, dim3(1), dim3(256), 0, s, nbr,
-                       (const int64_t *)rnnz.as<int64_t>(), (const int64_t *)row_elems.as<int64_t>(),
-                       (const int64_t *)rprod.as<int64_t>(), (const double *)rflops.as<double>(),
-                       (const int64_t *)nullptr, (const int64_t *)nullptr, sums.dev<RowTotals>());
-    BSMM_TRY(launch_check("row_totals"));
+                            rprod.as<int64_t>(), rflops.as<double>(), few ? sums.dev<RowCounts>() : nullptr, s));
+    if (!few) {
+        hipLaunchKernelGGL(k_row_totals, dim3(1), dim3(256), 0, s, nbr,
+                           (const int64_t *)rnnz.as<int64_t>(), (const int64_t *)row_elems.as<int64_t>(),
+                           (const int64_t *)rprod.as<int64_t>(), (const double *)rflops.as<double>(),
+                           (const int64_t *)nullptr, (const int64_t *)nullptr, sums.dev<RowTotals>());
+        BSMM_TRY(launch_check("row_totals"));
+    }
     BSMM_TRY(sums.record());
     BSMM_TRY(sums.wait());
-    const RowTotals h = *sums.host<RowTotals>();
+    RowTotals h{};
+    if (few) {
+        const RowCounts *row = sums.host<RowCounts>();
+        for (int32_t i = 0; i < nbr; ++i) {
+            h.nnz += row[i].nnz;
+            h.elems += row[i].elems;
+            h.products += row[i].products;
+            h.flops += row[i].flops;
+        }
+    } else {
+        h = *sums.host<RowTotals>();
+    }
     tot->nnzb = h.nnz;
     tot->nelems = h.elems;
     tot->nprod = h.products;

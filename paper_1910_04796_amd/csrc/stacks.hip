@@ -53,14 +53,13 @@ __device__ __forceinline__ void a_part(const int64_t *a_rp, int32_t row, int par
 // Workgroup (row, part): products per C block of the row from the part's
 // share of A's block row (P > 1 splits long A rows of few-row products;
 // the part counts go to pcount[c * P + part], else straight to c_count).
-// A product whose C block is not in the pattern sets *missing, unless
-// missing is null (a pattern from the symbolic screen leaves such blocks
-// out on purpose; their products are skipped here and in the fill).
+// Products whose C block is not in the pattern are skipped here and in the
+// fill; the host sees them by the total.
 __global__ __launch_bounds__(256) void k_stack_count(int32_t nbr, int32_t nbc, const int64_t *a_rp,
                                                      const int32_t *a_ci, const int64_t *b_rp,
                                                      const int32_t *b_ci, const int64_t *c_rp,
                                                      const int32_t *c_ci, int64_t *c_count,
-                                                     int32_t *c_row, int32_t *missing, int P,
+                                                     int32_t *c_row, int P,
                                                      int64_t *pcount) {
     extern __shared__ int32_t lds[];
     int32_t *map = lds;          // nbc entries: column -> slot in the C row, or -1
@@ -84,7 +83,6 @@ __global__ __launch_bounds__(256) void k_stack_count(int32_t nbr, int32_t nbc, c
             for (int64_t q = b_rp[kb] + lane_id(); q < b_rp[kb + 1]; q += kWave) {
                 const int32_t s = map[b_ci[q]];
                 if (s >= 0) atomicAdd(&cnt[s], 1);
-                else if (missing) *missing = 1;
             }
         }
         __syncthreads();
@@ -138,7 +136,7 @@ __global__ __launch_bounds__(256) void k_stack_count_win(int32_t nbr, int nwin, 
                                                          const int32_t *a_ci, const int64_t *split,
                                                          const int32_t *b_ci, const int64_t *c_rp,
                                                          const int32_t *c_ci, int64_t *c_count,
-                                                         int32_t *c_row, int32_t *missing, int P,
+                                                         int32_t *c_row, int P,
                                                          int64_t *pcount) {
     __shared__ int32_t map[kStackWin];
     __shared__ int32_t cnt[kStackWin];
@@ -168,7 +166,6 @@ __global__ __launch_bounds__(256) void k_stack_count_win(int32_t nbr, int nwin, 
                 for (int64_t q = sp[0] + lane_id(); q < q1; q += kWave) {
                     const int32_t s = map[b_ci[q] - w0];
                     if (s >= 0) atomicAdd(&cnt[s], 1);
-                    else if (missing) *missing = 1;
                 }
             }
             __syncthreads();
@@ -291,7 +288,7 @@ __global__ __launch_bounds__(256) void k_class_scatter(
 // are scanned class by class, then every wave walks its blocks again.
 __global__ __launch_bounds__(1024) void k_classify_small(
     int64_t c_base, int nblk, const int64_t *c_count, const int32_t *c_row, const int32_t *c_ci,
-    const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi, int ncs, int ncl, const int32_t *missing, int64_t *cb,
+    const int64_t *c_blk_off, const int32_t *rsi, const int32_t *csi, int ncs, int ncl, int64_t *cb,
     int64_t *run_cblk, int32_t *run_class, int64_t *run_coff, int64_t *run_ptr, int64_t *run_of_c) {
     constexpr int W = 16;
     __shared__ unsigned long long s_run[kSmallClasses * W], s_prod[kSmallClasses * W];
@@ -322,7 +319,6 @@ __global__ __launch_bounds__(1024) void k_classify_small(
     if (t == 0) {
         cb[ncl] = runs;
         cb[2 * ncl + 1] = prods;
-        cb[2 * (ncl + 1)] = *missing;
         run_ptr[runs] = prods;
     }
     __syncthreads();
@@ -360,8 +356,6 @@ __global__ __launch_bounds__(1024) void k_classify_small(
     }
 }
 
-__global__ void k_zero_i32(int32_t *p) { *p = 0; }
-
 // out[r] = scan[rp[r]] for r = 0..nbr: products before each C block row.
 __global__ void k_gather_rows(const int64_t *scan, const int64_t *rp, int32_t nbr, int64_t *out) {
     for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= nbr;
@@ -371,8 +365,7 @@ __global__ void k_gather_rows(const int64_t *scan, const int64_t *rp, int32_t nb
 
 // out[0..ncl]: first run of every class; out[ncl+1..2 ncl+1]: its first product.
 __global__ void k_gather_class_begin(const int64_t *hoff, const int64_t *hoff_p, int64_t ntiles,
-                                     int ncl, const int32_t *missing, int64_t *out) {
-    if (threadIdx.x == 0) out[2 * (ncl + 1)] = *missing;
+                                     int ncl, int64_t *out) {
     for (int cl = threadIdx.x; cl <= ncl; cl += blockDim.x) {
         out[cl] = hoff[(int64_t)cl * ntiles];
         out[ncl + 1 + cl] = hoff_p[(int64_t)cl * ntiles];
@@ -689,7 +682,6 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
     st.csi = keep ? C->b_col_size.as<int32_t>() : st.d_csi.as<int32_t>();
     BSMM_TRY(st.c_row.reserve(sizeof(int32_t) * nnzb, s));
     BSMM_TRY(st.c_count.reserve(sizeof(int64_t) * nnzb, s));
-    BSMM_TRY(st.missing.reserve(sizeof(int32_t), s));
     // Few C block rows with long A rows (tall-and-skinny products, or a
     // product whose stacks are built in row panels of few rows each): split
     // every A row into P parts so that about 1024 workgroups count and fill.
@@ -713,8 +705,6 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
         st.kparts = (int)P;
     }
     if (st.kparts > 1) BSMM_TRY(st.pcount.reserve(sizeof(int64_t) * nnzb * st.kparts, s));
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, s, st.missing.as<int32_t>());
-    BSMM_TRY(launch_check("zero_i32"));
     st.nwin = 0;
     if (nbc > kMaxStackCols) {
         st.nwin = (int)ceil_div(nbc, kStackWin);
@@ -726,14 +716,14 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
         hipLaunchKernelGGL(k_stack_count_win, dim3(grid_rows(nbr), st.kparts), dim3(256), 0, s, nbr, st.nwin,
                            A->d_row_ptr(), A->d_col_ind(), (const int64_t *)st.b_split.as<int64_t>(),
                            B->d_col_ind(), C->d_row_ptr(), C->d_col_ind(), st.c_count.as<int64_t>(),
-                           st.c_row.as<int32_t>(), st.screened ? nullptr : st.missing.as<int32_t>(), st.kparts,
+                           st.c_row.as<int32_t>(), st.kparts,
                            st.pcount.as<int64_t>());
     } else {
         const size_t map_lds = sizeof(int32_t) * 2 * (size_t)nbc;
         hipLaunchKernelGGL(k_stack_count, dim3(grid_rows(nbr), st.kparts), dim3(256), map_lds, s, nbr,
                            nbc, A->d_row_ptr(), A->d_col_ind(), B->d_row_ptr(), B->d_col_ind(),
                            C->d_row_ptr(), C->d_col_ind(), st.c_count.as<int64_t>(),
-                           st.c_row.as<int32_t>(), st.screened ? nullptr : st.missing.as<int32_t>(), st.kparts,
+                           st.c_row.as<int32_t>(), st.kparts,
                            st.pcount.as<int64_t>());
     }
     BSMM_TRY(launch_check("stack_count"));
@@ -743,9 +733,10 @@ int stack_count(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matri
     return launch_check("part_offsets");
 }
 
-// The flag of k_stack_count, read after a host synchronisation.
-static int check_missing(int32_t miss) {
-    if (!miss) return BSMM_OK;
+// `counted` products of the `all` that A and B have found their C block (a
+// pattern from the symbolic screen leaves blocks out on purpose).
+static int check_missing(const Stacks &st, int64_t counted, int64_t all) {
+    if (st.screened || counted == all) return BSMM_OK;
     set_error(BSMM_EINDEX, "C pattern does not contain every product block");
     return BSMM_EINDEX;
 }
@@ -767,10 +758,8 @@ int stack_row_bounds(const bsmm_matrix_s *C, const Stacks &st, std::vector<int64
                             hipMemcpyDeviceToHost, s));
     BSMM_HIP(hipMemcpyAsync(blk_before->data(), C->d_row_ptr(), sizeof(int64_t) * (nbr + 1),
                             hipMemcpyDeviceToHost, s));
-    int32_t miss = 0;
-    BSMM_HIP(hipMemcpyAsync(&miss, st.missing.p, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     BSMM_HIP(hipStreamSynchronize(s));
-    return check_missing(miss);
+    return check_missing(st, prod_before->back(), st.n_prod);
 }
 
 namespace {
@@ -796,7 +785,7 @@ int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t 
     BSMM_TRY(h.hoff.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.hist_p.reserve(sizeof(int64_t) * n, s));
     BSMM_TRY(h.hoff_p.reserve(sizeof(int64_t) * n, s));
-    BSMM_TRY(h.cb.reserve(sizeof(int64_t) * (2 * (ncl + 1) + 1), s));
+    BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
     hipLaunchKernelGGL(k_class_hist, dim3(grid_of(h.ntiles, 4)), dim3(256),
                        (sizeof(int32_t) + sizeof(int64_t)) * 4 * ncl, s, c0, nblk, h.ntiles, h.tile,
                        (const int64_t *)st.c_count.as<int64_t>(),
@@ -809,7 +798,7 @@ int class_offsets(const bsmm_matrix_s *C, const Stacks &st, int64_t c0, int64_t 
                                  h.hoff_p.as<int64_t>(), ncl * h.ntiles, s));
     hipLaunchKernelGGL(k_gather_class_begin, dim3(1), dim3(256), 0, s,
                        (const int64_t *)h.hoff.as<int64_t>(), (const int64_t *)h.hoff_p.as<int64_t>(),
-                       h.ntiles, ncl, (const int32_t *)st.missing.as<int32_t>(), h.cb.dev<int64_t>());
+                       h.ntiles, ncl, h.cb.dev<int64_t>());
     return launch_check("gather_class_begin");
 }
 }  // namespace
@@ -853,12 +842,12 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     BSMM_TRY(st.run_ptr.reserve(sizeof(int64_t) * (nblk + 1), s));
     const bool small = nblk <= kSmallBlocks && ncl <= kSmallClasses;
     if (small) {
-        BSMM_TRY(h.cb.reserve(sizeof(int64_t) * (2 * (ncl + 1) + 1), s));
+        BSMM_TRY(h.cb.reserve(sizeof(int64_t) * 2 * (ncl + 1), s));
         hipLaunchKernelGGL(k_classify_small, dim3(1), dim3(1024), 0, s, c0, (int)nblk,
                            (const int64_t *)st.c_count.as<int64_t>(),
                            (const int32_t *)st.c_row.as<int32_t>(), C->d_col_ind(), C->d_blk_off(),
                            st.rsi, st.csi,
-                           st.ncs, ncl, (const int32_t *)st.missing.as<int32_t>(), h.cb.dev<int64_t>(), st.run_cblk.as<int64_t>(),
+                           st.ncs, ncl, h.cb.dev<int64_t>(), st.run_cblk.as<int64_t>(),
                            st.run_class.as<int32_t>(), st.run_coff.as<int64_t>(), st.run_ptr.as<int64_t>(),
                            st.run_of_c.as<int64_t>());
         BSMM_TRY(launch_check("classify_small"));
@@ -906,7 +895,7 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     }
     BSMM_TRY(h.cb.wait());
     const int64_t *both = h.cb.host<int64_t>();
-    BSMM_TRY(check_missing((int32_t)both[2 * (ncl + 1)]));
+    BSMM_TRY(check_missing(st, both[2 * ncl + 1], nprod));
     st.class_begin.assign(both, both + ncl + 1);
     st.class_prod_begin.assign(both + ncl + 1, both + 2 * (ncl + 1));
     st.n_runs = st.class_begin[ncl];
