@@ -166,7 +166,8 @@ struct GemmArgs {
     int32_t c_nbc;
     const int32_t *c_rbs;
     const int2 *rmap, *cmap;
-    // Split k (few output tiles): workgroup (tile, split) sums k tiles
+    int tile0, ntiles;  // tiles of this launch
+    // Split k: workgroup (tile, split) sums k tiles
     // [split * kt_per, (split + 1) * kt_per) into part[split] (unscaled, per
     // tile in the waves' accumulator order); k_splitk_reduce applies the
     // epilogue.
@@ -265,6 +266,18 @@ __device__ __forceinline__ void gemm_step(const T *As, const T *Bs, int w, int l
     }
 }
 
+// Tiles in groups of kGroupM tile rows, the row index fastest: the tiles of an
+// XCD share panels of A and B in its L2.
+__device__ __forceinline__ void tile_at(const GemmArgs &g, int tile, int &tm, int &tn) {
+    const int per_group = kGroupM * g.tiles_n;
+    const int group = tile / per_group;
+    const int first_m = group * kGroupM;
+    const int gsz = min(g.tiles_m - first_m, kGroupM);
+    const int in_group = tile - group * per_group;
+    tm = first_m + in_group % gsz;
+    tn = in_group / gsz;
+}
+
 // KB = 16: 64 KB of LDS, two workgroups per CU; KB = 32: 128 KB, one
 // workgroup per CU with twice the prefetch distance and half the barriers.
 // NT: 16-column tiles per wave.  Bound by the matrix cores.  N = 8192 in
@@ -280,8 +293,8 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
     // and does not end them before every LDS read.
     __shared__ __attribute__((aligned(16))) T As0[KB * BM], As1[KB * BM], Bs0[BN * KB], Bs1[BN * KB];
 
-    // XCD-aware remap, then grouped row-major order inside the XCD's band
-    // (split k: consecutive logical ids walk the tiles of one split).
+    // XCD-aware remap: each XCD takes a band of consecutive tiles (split k:
+    // consecutive logical ids walk the tiles of one split).
     const int nwg = gridDim.x;
     int logical = blockIdx.x;
     {
@@ -290,19 +303,13 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
     }
     int split = 0, kt0 = 0, kt1 = g.ktiles;
     if (SPLIT) {
-        const int tiles = g.tiles_m * g.tiles_n;
-        split = logical / tiles;
-        logical -= split * tiles;
+        split = logical / g.ntiles;
+        logical -= split * g.ntiles;
         kt0 = split * g.kt_per;
         kt1 = min(g.ktiles, kt0 + g.kt_per);
     }
-    const int per_group = kGroupM * g.tiles_n;
-    const int group = logical / per_group;
-    const int first_m = group * kGroupM;
-    const int gsz = min(g.tiles_m - first_m, kGroupM);
-    const int in_group = logical - group * per_group;
-    const int tm = first_m + in_group % gsz;
-    const int tn = in_group / gsz;
+    int tm, tn;
+    tile_at(g, g.tile0 + logical, tm, tn);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -340,7 +347,7 @@ __global__ __launch_bounds__(1024 / NT, MINW) void k_dgemm_mfma(GemmArgs g) {
         // Partial sums in the accumulators' own order: per 16 columns and
         // 64 rows, four consecutive 64-lane vectors.
         typename Mfma<T>::acc_t *P = static_cast<typename Mfma<T>::acc_t *>(g.part) +
-                                     (((int64_t)split * g.tiles_m + tm) * g.tiles_n + tn) * 4096 + lane;
+                                     ((int64_t)split * g.ntiles + logical) * 4096 + lane;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -382,13 +389,14 @@ __global__ __launch_bounds__(64) void k_splitk_reduce(GemmArgs g) {
     __shared__ T s_out[16][65];
     const T alpha = (T)g.alpha, beta = (T)g.beta;
     const int lane = threadIdx.x, l16 = lane & 15, lk = lane >> 4;
-    const int64_t strips = (int64_t)g.tiles_m * g.tiles_n * 16;
-    const int64_t plane = (int64_t)g.tiles_m * g.tiles_n * 4096;
+    const int64_t strips = (int64_t)g.ntiles * 16, plane = (int64_t)g.ntiles * 4096;
     for (int64_t st = blockIdx.x; st < strips; st += gridDim.x) {
         const int64_t tile = st >> 4;
         const int part = (int)st & 15;  // 16 columns (part / 2) of one half of the rows (part % 2)
-        const int64_t row0 = tile / g.tiles_n * BM + (part & 1) * 64;
-        const int64_t col0 = tile % g.tiles_n * BN + (part >> 1) * 16;
+        int tm, tn;
+        tile_at(g, g.tile0 + (int)tile, tm, tn);
+        const int64_t row0 = (int64_t)tm * BM + (part & 1) * 64;
+        const int64_t col0 = (int64_t)tn * BN + (part >> 1) * 16;
         if (row0 >= g.M || col0 >= g.N) continue;
         const V *p = static_cast<const V *>(g.part) + tile * 4096 + part * 256 + lane;
         V v[4];
@@ -485,28 +493,29 @@ int zero_panel(const bsmm_matrix_s *M, T *panel, int64_t ld, int64_t ncols, hipS
     return launch_check("zero_padding");
 }
 
-// Parts of k for an output of `tiles` tiles of `ktiles` k steps on `slots`
+// Parts of k for `tiles` output tiles of `ktiles` k steps on `slots`
 // resident workgroups: the count with the lowest estimated time, in units of
 // one k step of a resident workgroup (4 us in FP64).  All workgroups take
 // ceil(tiles * S / slots) rounds of ceil(ktiles / S) k steps, plus about
 // three for a workgroup's start and end; S > 1 also writes and reads S
-// partial outputs (part_bytes each, 4.5 TB/s).  Each part holds at least
-// eight k steps, the partials at most max_bytes.  Aiming at two rounds whatever
-// the tile count left the last one nearly empty: 1408 x 1408 (121 tiles)
-// with k = 247,808 took 19.0 ms in 9 parts (2.13 rounds, three in effect)
-// and takes 15.0 ms in 21; 210 tiles of k = 2300 took 346 + 86 us in 5
-// parts and 329 + 28 us in 2.
-int64_t gemm_splits(int64_t tiles, int64_t ktiles, int64_t slots, int64_t part_bytes, int64_t max_bytes) {
+// partial outputs (tile_bytes each and tile, 4.5 TB/s).  Each part holds at
+// least eight k steps, the partials at most max_bytes.  Aiming at two rounds
+// whatever the tile count left the last one nearly empty: 1408 x 1408 (121
+// tiles) with k = 247,808 took 19.0 ms in 9 parts (2.13 rounds, three in
+// effect) and takes 15.0 ms in 21; 210 tiles of k = 2300 took 346 + 86 us in
+// 5 parts and 329 + 28 us in 2.
+int64_t gemm_splits(int64_t tiles, int64_t ktiles, int64_t slots, int64_t tile_bytes, int64_t max_bytes,
+                    double *cost) {
+    const int64_t part_bytes = tiles * tile_bytes;
     const int64_t most = std::max<int64_t>(1, std::min<int64_t>({ktiles / 8, 64, max_bytes / part_bytes}));
     int64_t best = 1;
-    double best_cost = 0.0;
     for (int64_t S = 1; S <= most; ++S) {
         const double rounds = (double)ceil_div(tiles * S, slots);
-        double cost = rounds * (double)(ceil_div(ktiles, S) + 3);
-        if (S > 1) cost += 2.0 * (double)(S * part_bytes) / 4.5e12 / 4e-6 + 2.0;
-        if (S == 1 || cost < 0.98 * best_cost) {
+        double c = rounds * (double)(ceil_div(ktiles, S) + 3);
+        if (S > 1) c += 2.0 * (double)(S * part_bytes) / 4.5e12 / 4e-6 + 2.0;
+        if (S == 1 || c < 0.98 * *cost) {
             best = S;
-            best_cost = cost;
+            *cost = c;
         }
     }
     return best;
@@ -576,29 +585,51 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
         part_cap = std::min<int64_t>(part_cap, (int64_t)(ar->cap - ar->used) - 512);
         part_cap = std::max<int64_t>(part_cap, 0);
     }
-    int64_t splits = gemm_splits(tiles, g.ktiles, slots, (int64_t)sizeof(T) * Mp * Np, part_cap);
+    // All tiles in parts of k, or the full rounds' tiles whole and only the
+    // rest in parts (a launch more, about two steps): N = 3000 (576 tiles, 512
+    // slots) 1.11 -> 1.04 ms, N = 6000 (2209) 6.98 -> 6.61, FP32 2900 (529)
+    // 0.59 -> 0.54.  Dealing the k steps evenly to the workgroups instead filled
+    // every round, but put neighbours at different k: 1,408 x 1,408 x 247,808
+    // 13.9 -> 16.3 ms.
+    const int64_t tile_bytes = (int64_t)sizeof(T) * BM * BN;
+    const int64_t rest = tiles % slots;
+    double cost_all = 0.0, cost_rest = 0.0;
+    int64_t splits = gemm_splits(tiles, g.ktiles, slots, tile_bytes, part_cap, &cost_all), whole = 0;
+    if (rest && rest < tiles) {
+        const int64_t r = gemm_splits(rest, g.ktiles, slots, tile_bytes, part_cap, &cost_rest);
+        cost_rest += (double)(tiles / slots) * (double)(g.ktiles + 3) + 2.0;
+        if (r > 1 && cost_rest < 0.98 * cost_all) {
+            splits = r;
+            whole = tiles - rest;
+        }
+    }
+    if (splits == 1) whole = tiles;
     DevBuf part;
     if (splits > 1) {
         g.kt_per = (int)ceil_div(g.ktiles, splits);
         splits = ceil_div(g.ktiles, g.kt_per);  // no empty split
         g.splits = (int)splits;
-        BSMM_TRY(part.reserve(sizeof(T) * splits * Mp * Np, s));
+        BSMM_TRY(part.reserve(tile_bytes * splits * (tiles - whole), s));
         g.part = part.p;
     }
     {
         KernelTimer kt(0, s);
-        const dim3 grid((unsigned)(tiles * splits));
-        if (splits > 1) {
-            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 4, 1, true>), grid, dim3(256), 0, s, g);
-            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, 4, true>), grid, dim3(512), 0, s, g);
-        } else {
+        if (whole) {
+            const dim3 grid((unsigned)whole);
             if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 4, 1, false>), grid, dim3(256), 0, s, g);
             else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, 4, false>), grid, dim3(512), 0, s, g);
+        }
+        g.tile0 = (int)whole;
+        g.ntiles = (int)(tiles - whole);
+        if (splits > 1) {
+            const dim3 grid((unsigned)(g.ntiles * splits));
+            if (KB == 32) hipLaunchKernelGGL((k_dgemm_mfma<T, 32, 4, 1, true>), grid, dim3(256), 0, s, g);
+            else hipLaunchKernelGGL((k_dgemm_mfma<T, 16, 2, 4, true>), grid, dim3(512), 0, s, g);
         }
     }
     BSMM_TRY(launch_check("dgemm_mfma"));
     if (splits == 1) return BSMM_OK;
-    hipLaunchKernelGGL(k_splitk_reduce<T>, dim3(grid_of(tiles * 16, 1)), dim3(64), 0, s, g);
+    hipLaunchKernelGGL(k_splitk_reduce<T>, dim3(grid_of((int64_t)g.ntiles * 16, 1)), dim3(64), 0, s, g);
     return launch_check("splitk_reduce");
 }
 

@@ -44,6 +44,17 @@ def test_split_k_into_blocks(occ):
     check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
 
 
+def test_last_round_in_parts():
+    """529 tiles: 512 of them whole, the last ones in parts of k, into a C
+    that stores every other block."""
+    rng = rng_of(4)
+    rs, ks = _cover(23 * 128, [32], rng), _cover(300, [20], rng)
+    A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
+    C = make_matrix(rng, rs, rs, 0.5, "int")
+    X, _ = gpu_multiply(1.0, A, B, 2.0, C, path="dense")
+    check_against_oracle(X, orc.multiply(1.0, A, B, 2.0, C), 0.0)
+
+
 def test_split_k_f32():
     from tests.test_gpu_f32 import _as_f32, _f32_multiply
     rng = rng_of(9)
