@@ -19,10 +19,11 @@
 //      separately rounded products (native FP64 for the recombination and
 //      beta * C).
 //
-// Layout: A is merged transposed (rows of A contiguous in k) and B column-
-// major (columns contiguous in k); the int8 slices are stored in k panels of
-// 32 bytes ([slice][k / 32][row][k % 32]) so that every k step of a tile
-// reads whole contiguous blocks.
+// Layout: the digits are taken along the rows of A and the columns of B,
+// straight from the blocks when every block is stored, else from a panel into
+// which they are merged; the int8 slices are stored in k panels of 32 bytes
+// ([slice][k / 32][row][k % 32]) so that every k step of a tile reads whole
+// contiguous blocks.
 // GEMM kernels (option "emul_kernel"), all with S INT32 accumulators (one per
 // weight d) per output tile:
 //   t64     64 x 64 outputs per 256-thread workgroup, each wave 2 x 2 tiles of
@@ -40,6 +41,7 @@
 
 #include "dev_util.h"
 #include "internal.h"
+#include "mfma_util.h"
 
 namespace bsmm {
 
@@ -147,6 +149,203 @@ __global__ __launch_bounds__(256) void k_slice(const double *X, int64_t rows, in
             *reinterpret_cast<unsigned long long *>(out + (int64_t)s * rows * ld + p * rows * 32 + r * 32 +
                                                     8 * q) = w;
         }
+    }
+}
+
+// A matrix that stores every block, sliced without a panel: k_block_max takes
+// the largest magnitude of every row of A (COLS: column of B) from the
+// blocks, k_slice_rows / k_slice_cols read the blocks again and write the
+// digits.  Bound by HBM: 8192 x 8192 in 32-blocks 128 + 260 us for A, 117 + 299
+// us for B, against merge, exponents and slices through a panel with 342 + 124
+// + 303 and 224 + 124 + 303 us.
+
+// A wave takes `per` blocks of one block row (COLS: block column); its lanes
+// keep the largest magnitude of the elements lane, lane + 64, ... of every
+// block, as long as those stay in the same row (column), then join them in
+// LDS.  Infinity stands for every value that is not finite.
+constexpr int kMaxSlots = 16, kMaxExt = 256;
+template <bool COLS>
+__global__ __launch_bounds__(256) void k_block_max(int32_t strips, int32_t blocks, int32_t nbc, int per,
+                                                   const int32_t *rbs, const int32_t *cbs, const int64_t *strip_off,
+                                                   const int64_t *blk_off, const double *data,
+                                                   unsigned long long *mx) {
+    __shared__ unsigned long long s_mx[4][kMaxExt];
+    unsigned long long *joined = s_mx[wave_id()];
+    const int lane = lane_id();
+    const int64_t chunks = (blocks + per - 1) / per, items = strips * chunks;
+    for (int64_t it = (int64_t)blockIdx.x * 4 + wave_id(); it < items; it += (int64_t)gridDim.x * 4) {
+        const int32_t strip = uniform((int32_t)(it / chunks));
+        const int32_t b0 = uniform((int32_t)(it % chunks) * per), b1 = min(b0 + per, blocks);
+        const int ext = COLS ? scalar_at(cbs, strip) : scalar_at(rbs, strip);
+        unsigned long long *out = mx + strip_off[strip];
+        const bool lds = ext <= kMaxExt;
+        if (lds)
+            for (int i = lane; i < ext; i += kWave) joined[i] = 0;
+        wave_lds_sync();
+        double big[kMaxSlots] = {};
+        int m = COLS ? 0 : ext;
+        auto join = [&](int s0) {  // elements s0 + lane, s0 + lane + 64, ...
+            const float rcp = 1.0f / (float)m;
+#pragma unroll
+            for (int t = 0; t < kMaxSlots; ++t) {
+                if (big[t] > 0.0) {
+                    const int e = s0 + lane + t * kWave;
+                    int row, col;
+                    if (e < (1 << 20) && m < 4096) {
+                        col = divmod_small(e, m, rcp, &row);
+                    } else {
+                        col = e / m;
+                        row = e - col * m;
+                    }
+                    atomicMax(lds ? &joined[COLS ? col : row] : &out[COLS ? col : row],
+                              (unsigned long long)__double_as_longlong(big[t]));
+                }
+                big[t] = 0.0;
+            }
+        };
+        for (int32_t b = b0; b < b1; ++b) {
+            const int64_t p = COLS ? (int64_t)b * nbc + strip : (int64_t)strip * nbc + b;
+            const int bm = COLS ? scalar_at(rbs, b) : ext;
+            const int len = bm * (COLS ? ext : scalar_at(cbs, b));
+            const double *x = data + scalar_at(blk_off, p);
+            if (COLS && bm != m) {
+                if (m) join(0);
+                m = bm;
+            }
+            for (int s0 = 0; s0 < len; s0 += kMaxSlots * kWave) {
+                if (s0) join(s0 - kMaxSlots * kWave);
+                // A buffer up to the block's end: zeros past it.
+                const int left = min(len - s0, kMaxSlots * kWave);
+                const BufferRsrc r = buffer_at(x + s0, (uint32_t)left * 8);
+                double v[kMaxSlots];
+#pragma unroll
+                for (int t = 0; t < kMaxSlots; ++t) v[t] = fabs(Mfma<double>::load(r, (lane + t * kWave) * 8));
+#pragma unroll
+                for (int t = 0; t < kMaxSlots; ++t)
+                    big[t] = fmax(big[t], v[t] < __builtin_inf() ? v[t] : __builtin_inf());
+            }
+            if (len > kMaxSlots * kWave) join((len - 1) / (kMaxSlots * kWave) * (kMaxSlots * kWave));
+        }
+        if (m == 0) m = 1;
+        join(0);
+        wave_lds_sync();
+        if (lds)
+            for (int i = lane; i < ext; i += kWave)
+                if (joined[i]) atomicMax(&out[i], joined[i]);
+        wave_lds_sync();  // joined is cleared for the next item
+    }
+}
+
+// Row exponents from the magnitudes of k_block_max.
+__global__ __launch_bounds__(256) void k_exp_of_max(const unsigned long long *mx, int64_t n, int *e) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const double x = __longlong_as_double((long long)mx[i]);
+        int ex = 0;
+        if (x > 0.0 && x < __builtin_inf()) (void)frexp(x, &ex);
+        e[i] = x < __builtin_inf() ? ex : kNonFiniteExp;
+    }
+}
+
+// The S digits of N consecutive values of k, 4 to a word.
+template <int N>
+__device__ __forceinline__ void write_digits(double (&v)[N], int S, int64_t slice, signed char *out) {
+    for (int s = 0; s < S; ++s) {
+        v4i w[N / 16];
+#pragma unroll
+        for (int j = 0; j < N; j += 4) {
+            unsigned int x = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const double t = v[j + b] * 128.0, d = trunc(t);
+                v[j + b] = t - d;
+                x |= (unsigned int)(unsigned char)(signed char)(int)d << (8 * b);
+            }
+            w[j / 16][j / 4 % 4] = (int)x;
+        }
+#pragma unroll
+        for (int j = 0; j < N / 16; ++j) *reinterpret_cast<v4i *>(out + s * slice + 16 * j) = w[j];
+    }
+}
+
+// A: a wave takes 64 rows of one k panel, a row per lane (consecutive lanes
+// read consecutive rows of a block), 32 values of k each.
+__global__ __launch_bounds__(256) void k_slice_rows(int64_t rows, int64_t cols, int64_t rows_p, int64_t ld, int32_t nbc,
+                                                    int S, const int2 *rmap, const int2 *cmap, const int32_t *rbs,
+                                                    const int64_t *blk_off, const double *data, const int *e,
+                                                    signed char *out) {
+    const int64_t tiles = rows_p / 64, items = tiles * (ld / 32);
+    for (int64_t it = uniform((int64_t)blockIdx.x * 4 + wave_id()); it < items; it += (int64_t)gridDim.x * 4) {
+        const int64_t p = it / tiles, r = it % tiles * 64 + lane_id();
+        const bool in = r < rows;
+        const int2 rm = in ? rmap[r] : make_int2(0, 0);
+        const int64_t m = in ? rbs[rm.x] : 0;
+        double v[32];
+        int last = -1;
+        int64_t base = 0;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) {
+            const int64_t k = 32 * p + j;
+            v[j] = 0.0;
+            if (k < cols) {
+                const unsigned long long km = scalar_at(reinterpret_cast<const unsigned long long *>(cmap), k);
+                if ((int)km != last) {  // low half: block column; high half: column inside
+                    last = (int)km;
+                    base = blk_off[(int64_t)rm.x * nbc + last] + rm.y;
+                }
+                if (in) v[j] = data[base + (int)(km >> 32) * m];
+            }
+        }
+        const int er = in ? e[r] : 0;
+#pragma unroll
+        for (int j = 0; j < 32; ++j) v[j] = er == kNonFiniteExp ? 0.0 : ldexp(v[j], -er);
+        write_digits<32>(v, S, rows_p * ld, out + p * rows_p * 32 + r * 32);
+    }
+}
+
+// B: a wave takes 16 columns of two k panels; it reads along k, the direction
+// of a block's columns, and turns the tile in LDS, so that a lane has 16
+// values of k of one column.
+__global__ __launch_bounds__(256) void k_slice_cols(int64_t rows, int64_t cols, int64_t cols_p, int64_t ld, int32_t nbc,
+                                                    int S, const int2 *rmap, const int2 *cmap, const int32_t *rbs,
+                                                    const int64_t *blk_off, const double *data, const int *e,
+                                                    signed char *out) {
+    __shared__ double s_tile[4][16][65];
+    double(*tile)[65] = s_tile[wave_id()];
+    const int lane = lane_id();
+    const int64_t tiles = cols_p / 16, items = tiles * (ld / 64);
+    for (int64_t it = uniform((int64_t)blockIdx.x * 4 + wave_id()); it < items; it += (int64_t)gridDim.x * 4) {
+        const int64_t pp = it / tiles, c0 = it % tiles * 16;
+        const int64_t k = 64 * pp + lane;
+        const bool kin = k < rows;
+        const int2 km = kin ? rmap[k] : make_int2(0, 0);
+        const int64_t m = kin ? rbs[km.x] : 0;
+        int last = -1;
+        int64_t base = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            double x = 0.0;
+            if (c0 + i < cols) {
+                const unsigned long long cm = scalar_at(reinterpret_cast<const unsigned long long *>(cmap), c0 + i);
+                if ((int)cm != last) {  // low half: block column; high half: column inside
+                    last = (int)cm;
+                    base = blk_off[(int64_t)km.x * nbc + last] + km.y;
+                }
+                if (kin) x = data[base + (int)(cm >> 32) * m];
+            }
+            tile[i][lane] = x;
+        }
+        wave_lds_sync();
+        const int64_t c = c0 + (lane >> 2);
+        const int q = lane & 3;
+        const int er = c < cols ? e[c] : 0;
+        double v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const double x = tile[lane >> 2][16 * q + j];
+            v[j] = er == kNonFiniteExp ? 0.0 : ldexp(x, -er);
+        }
+        wave_lds_sync();  // the tile has been read before it is replaced
+        write_digits<16>(v, S, cols_p * ld, out + (2 * pp + (q >> 1)) * cols_p * 32 + c * 32 + 16 * (q & 1));
     }
 }
 
@@ -742,6 +941,51 @@ EmulKernel emul_kernel(int S, int variant) {
     }
 }
 
+// Exponents and digit slices of A's rows (COLS: B's columns), n of them with
+// the padding, each Kp long.
+template <bool COLS>
+int slice_operand(const bsmm_matrix_s *M, int64_t n, int64_t Kp, int S, int *e, signed char *slices, hipStream_t s) {
+    if (M->full()) {
+        DevBuf mx;
+        BSMM_TRY(mx.reserve(sizeof(unsigned long long) * n, s));
+        BSMM_TRY(fill_zero(mx.as<double>(), n, s));
+        const int32_t strips = COLS ? M->nbc : M->nbr, blocks = COLS ? M->nbr : M->nbc;
+        // About 16,384 waves, each with at least eight blocks.
+        const int per = (int)std::max<int64_t>(8, ceil_div((int64_t)strips * blocks, 16384));
+        hipLaunchKernelGGL(k_block_max<COLS>, dim3(grid_of(strips * ceil_div(blocks, per), 4)), dim3(256), 0, s, strips,
+                           blocks, M->nbc, per, M->d_rbs(), M->d_cbs(), COLS ? M->d_col_off() : M->d_row_off(),
+                           M->d_blk_off(), M->d_data(), mx.as<unsigned long long>());
+        hipLaunchKernelGGL(k_exp_of_max, dim3(grid_of(n, 256)), dim3(256), 0, s,
+                           (const unsigned long long *)mx.as<unsigned long long>(), n, e);
+        BSMM_TRY(launch_check("emul exponents"));
+        if (COLS)
+            hipLaunchKernelGGL(k_slice_cols, dim3(grid_of(n / 16 * (Kp / 64), 4)), dim3(256), 0, s, M->rows(), M->cols(),
+                               n, Kp, M->nbc, S, M->d_row_map(), M->d_col_map(), M->d_rbs(), M->d_blk_off(), M->d_data(),
+                               (const int *)e, slices);
+        else
+            hipLaunchKernelGGL(k_slice_rows, dim3(grid_of(n / 64 * (Kp / 32), 4)), dim3(256), 0, s, M->rows(), M->cols(),
+                               n, Kp, M->nbc, S, M->d_row_map(), M->d_col_map(), M->d_rbs(), M->d_blk_off(), M->d_data(),
+                               (const int *)e, slices);
+        return launch_check("emul slices");
+    }
+    // Blocks are missing: through a panel of zeros.
+    DevBuf panel;
+    BSMM_TRY(panel.reserve(sizeof(double) * n * Kp, s));
+    BSMM_TRY(fill_zero(panel.as<double>(), n * Kp, s));
+    if (M->nnzb > 0) {
+        hipLaunchKernelGGL((COLS ? k_merge_c : k_merge_t), dim3(grid_of(M->nnzb, 4)), dim3(256), 0, s, M->nbr, M->nnzb,
+                           M->d_rbs(), M->d_cbs(), M->d_row_off(), M->d_col_off(), M->d_row_ptr(), M->d_col_ind(),
+                           M->d_blk_off(), M->d_data(), panel.as<double>(), Kp);
+        BSMM_TRY(launch_check("emul merge"));
+    }
+    hipLaunchKernelGGL(k_row_exp, dim3(grid_of(n, 4)), dim3(256), 0, s, (const double *)panel.as<double>(), n,
+                       COLS ? M->rows() : M->cols(), Kp, e);
+    BSMM_TRY(launch_check("emul exponents"));
+    hipLaunchKernelGGL(k_slice, dim3(grid_of(n * (Kp / 8), 256)), dim3(256), 0, s, (const double *)panel.as<double>(), n,
+                       Kp, S, (const int *)e, slices);
+    return launch_check("emul slices");
+}
+
 }  // namespace
 
 // Largest k chunk (multiple of 64, hence of every variant's k step) with
@@ -766,42 +1010,13 @@ int emul_multiply(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s 
     const int64_t tile_m = wide ? WTM : ET, tile_n = wide ? WTN : ET;
     const int64_t Mp = ceil_div(M, tile_m) * tile_m, Np = ceil_div(N, tile_n) * tile_n;
     const int64_t Kp = ceil_div(K, EK) * EK;
-    DevBuf at, bp, ea, eb, as, bs, V, cmap;
-    BSMM_TRY(at.reserve(sizeof(double) * Mp * Kp, s));
-    BSMM_TRY(bp.reserve(sizeof(double) * Kp * Np, s));
+    DevBuf ea, eb, as, bs, V, cmap;
     BSMM_TRY(ea.reserve(sizeof(int) * Mp, s));
     BSMM_TRY(eb.reserve(sizeof(int) * Np, s));
     BSMM_TRY(as.reserve((size_t)S * Mp * Kp, s));
     BSMM_TRY(bs.reserve((size_t)S * Np * Kp, s));
-    // Panels need zeros where no block lands: padding and missing blocks.
-    if (!(A->full() && Mp == M && Kp == K)) BSMM_TRY(fill_zero(at.as<double>(), Mp * Kp, s));
-    if (!(B->full() && Np == N && Kp == K)) BSMM_TRY(fill_zero(bp.as<double>(), Kp * Np, s));
-    if (A->nnzb > 0) {
-        hipLaunchKernelGGL(k_merge_t, dim3(grid_of(A->nnzb, 4)), dim3(256), 0, s, A->nbr, A->nnzb,
-                           A->d_rbs(), A->d_cbs(),
-                           A->d_row_off(), A->d_col_off(), A->d_row_ptr(), A->d_col_ind(),
-                           A->d_blk_off(), A->d_data(), at.as<double>(), Kp);
-        BSMM_TRY(launch_check("emul merge A"));
-    }
-    if (B->nnzb > 0) {
-        hipLaunchKernelGGL(k_merge_c, dim3(grid_of(B->nnzb, 4)), dim3(256), 0, s, B->nbr, B->nnzb,
-                           B->d_rbs(), B->d_cbs(),
-                           B->d_row_off(), B->d_col_off(), B->d_row_ptr(), B->d_col_ind(),
-                           B->d_blk_off(), B->d_data(), bp.as<double>(), Kp);
-        BSMM_TRY(launch_check("emul merge B"));
-    }
-    hipLaunchKernelGGL(k_row_exp, dim3(grid_of(Mp, 4)), dim3(256), 0, s,
-                       (const double *)at.as<double>(), Mp, K, Kp, ea.as<int>());
-    hipLaunchKernelGGL(k_row_exp, dim3(grid_of(Np, 4)), dim3(256), 0, s,
-                       (const double *)bp.as<double>(), Np, K, Kp, eb.as<int>());
-    BSMM_TRY(launch_check("emul exponents"));
-    hipLaunchKernelGGL(k_slice, dim3(grid_of(Mp * (Kp / 8), 256)), dim3(256), 0, s,
-                       (const double *)at.as<double>(), Mp, Kp, S, (const int *)ea.as<int>(),
-                       as.as<signed char>());
-    hipLaunchKernelGGL(k_slice, dim3(grid_of(Np * (Kp / 8), 256)), dim3(256), 0, s,
-                       (const double *)bp.as<double>(), Np, Kp, S, (const int *)eb.as<int>(),
-                       bs.as<signed char>());
-    BSMM_TRY(launch_check("emul slices"));
+    BSMM_TRY(slice_operand<false>(A, Mp, Kp, S, ea.as<int>(), as.as<signed char>(), s));
+    BSMM_TRY(slice_operand<true>(B, Np, Kp, S, eb.as<int>(), bs.as<signed char>(), s));
     const int32_t *d_cmap = nullptr;
     if (!C->full()) {
         const int64_t cells = (int64_t)C->nbr * C->nbc;

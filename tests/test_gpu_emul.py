@@ -39,6 +39,29 @@ def test_bit_exact_against_reference(S):
         assert len(bad) == 0, f"{len(bad)} mismatches, first {bad[:3].tolist()}: {D[tuple(bad[0])]} vs {R[tuple(bad[0])]}"
 
 
+@pytest.mark.parametrize("rows,ks,cols", [([300, 1, 5], [70, 3], [33, 290]), ([64, 31], [1, 1, 40, 64], [2, 65]),
+                                          ([7], [5, 13, 13, 23, 300], [1, 1, 1, 300])])
+def test_block_shapes_bit_exact(rows, ks, cols):
+    """Blocks beyond the 1,024 elements and 256 rows or columns that one pass
+    over the magnitudes holds, blocks of one row, neighbours of equal and of
+    changing height; every block stored, and one missing (through panels)."""
+    rng = rng_of(sum(rows) + sum(ks))
+    rbs, kbs, cbs = (np.array(x, np.int32) for x in (rows, ks, cols))
+    A = make_matrix(rng, rbs, kbs, 1.0, values="wide")
+    B = make_matrix(rng, kbs, cbs, 1.0, values="wide")
+    Ad, Bd = orc.to_dense(A), orc.to_dense(B)
+    Ad[0, -1], Bd[-1, 0] = -np.inf, np.nan
+    Bd[:, 1] = 0.0
+    A, B = from_dense(Ad, rbs, kbs), from_dense(Bd, kbs, cbs)
+    R = er.emulate(Ad, Bd, 7)
+    D = orc.to_dense(_emul(A, B, 1.0, 0.0, None, 7)[0])
+    assert np.array_equal(D, R, equal_nan=True)
+    # (finite: a block row that A lacks has no blocks in C, NaN or not)
+    A, B = make_matrix(rng, rbs, kbs, 0.6, values="wide"), make_matrix(rng, kbs, cbs, 1.0, values="wide")
+    D = orc.to_dense(_emul(A, B, 1.0, 0.0, None, 7)[0])
+    assert np.array_equal(D, er.emulate(orc.to_dense(A), orc.to_dense(B), 7))
+
+
 def test_multi_chunk_k():
     """K above the INT32-exact chunk of the device (8 slices: 16,640): the
     chunks add their weight sums into exact int64 partials, so the result
