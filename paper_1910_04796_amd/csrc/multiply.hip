@@ -29,7 +29,8 @@ struct RowTotals {
     double flops;
 };
 // C block rows whose counts go to the host one by one.
-constexpr int kFewRows = 256;
+constexpr int kFewRows = 1024;
+static_assert(kFewRows * sizeof(RowCounts) <= Readback::kMaxBytes, "row counts");
 __global__ __launch_bounds__(256) void k_row_totals(int32_t nbr, const int64_t *nnz,
                                                     const int64_t *elems, const int64_t *prod,
                                                     const double *flops, const int64_t *scr,

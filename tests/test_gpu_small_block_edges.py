@@ -94,6 +94,26 @@ def test_infinities_stay_in_their_rows_and_columns(depths, blocks, at):
     check_against_oracle(X, R, 0.0)
 
 
+@pytest.mark.parametrize("nk", [1, 31, 32, 33, 65])
+@pytest.mark.parametrize("nbc", [5, 4000, 4001])
+def test_product_lists(nk, nbc):
+    """Rows of A with as many blocks as one pass over them holds, one less,
+    one more and beyond two passes; C with the most block columns of the
+    list kernel for short rows and one more: exact, and K ascending (with
+    values whose sum depends on the order: the same bits as one product after
+    the other)."""
+    rng = rng_of(nk + nbc)
+    rs, ks, ns = np.array([2, 1, 3], np.int32), np.full(nk, 1, np.int32), np.full(nbc, 1, np.int32)
+    A, B = make_matrix(rng, rs, ks, 1.0), make_matrix(rng, ks, ns, 0.7 if nbc < 100 else 0.02)
+    A.data[:] = 1.0
+    B.data[:] = rng.choice([2.0**53, 1.0, -(2.0**53), 3.0], size=B.data.size)
+    X, _ = gpu_multiply(1.0, A, B, 0.0, path="stack")
+    D, want = orc.to_dense(B), np.zeros(nbc)
+    for k in range(nk):
+        want = want + D[k]
+    assert np.array_equal(orc.to_dense(X), np.tile(want, (6, 1)))
+
+
 def test_copied_b_same_bits():
     """Enough products per B block for row-major copies of B: the same bits
     as reading both operands in place (stack_at "1" keeps B in place), and a
