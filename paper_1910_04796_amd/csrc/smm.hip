@@ -646,11 +646,13 @@ bool is_sched_kernel(const void *fn) {
 // from row-major copies.  A fragment of B in place touches one 64-byte
 // piece of 16 columns, from a copy one 128-byte piece of 4 rows of k: a
 // third fewer cache lines, which the launch feels once each B block is read
-// many times, while the copy costs one read and one write of B.  Measured
-// (kernel plus copy, FP64): banded 30 % (about 800 products per B block)
-// 680 -> 647 ms, 10 % (270) 75.8 -> 73.0 ms, 23-blocks at 20 % (70) 2.23 ->
-// 2.15 ms, banded 1 % (18) 1.46 -> 1.61 ms.  FP32, whose fragments are half
-// as long, gains nothing (10 %, 130 products: 11.9 -> 12.1 ms).
+// many times, while the copy costs one read and one write of B (and a launch).
+// Measured (whole multiply, FP64, in place -> from copies): banded 30 % 664 ->
+// 563 ms, 10 % 82.6 -> 70.1 ms, 5 % 30.4 -> 27.7 ms; 23-blocks at 20 % (70
+// products per B block) 1.95 -> 1.90 ms, at 10 % (35) 0.90 -> 0.85 ms;
+// {5,13,23}-blocks, N = 3000, at 25 % (55) 398 -> 413 us, at 10 % (22) 218 -> 237
+// us; banded 2 % and 1 % the same.  FP32, whose fragments are half as long,
+// gained nothing (10 %: 11.9 -> 12.1 ms).
 constexpr int64_t kCopyBMinUses = 48;
 
 constexpr int kLdsBudget = 64 * 1024;  // bytes of LDS per workgroup
