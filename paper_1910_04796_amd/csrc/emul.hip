@@ -945,13 +945,15 @@ EmulKernel emul_kernel(int S, int variant) {
 // the padding, each Kp long.
 template <bool COLS>
 int slice_operand(const bsmm_matrix_s *M, int64_t n, int64_t Kp, int S, int *e, signed char *slices, hipStream_t s) {
-    if (M->full()) {
+    const int64_t largest = (int64_t)M->max_rbs * M->max_cbs;
+    if (M->full() && largest < (1 << 28)) {  // (k_block_max counts a block's elements in 32 bits)
         DevBuf mx;
         BSMM_TRY(mx.reserve(sizeof(unsigned long long) * n, s));
         BSMM_TRY(fill_zero(mx.as<double>(), n, s));
         const int32_t strips = COLS ? M->nbc : M->nbr, blocks = COLS ? M->nbr : M->nbc;
-        // About 16,384 waves, each with at least eight blocks.
-        const int per = (int)std::max<int64_t>(8, ceil_div((int64_t)strips * blocks, 16384));
+        // About 16,384 waves, each with at least 8,192 elements or one block.
+        const int per = (int)std::min<int64_t>(
+            blocks, std::max<int64_t>({1, 8192 / largest, ceil_div((int64_t)strips * blocks, 16384)}));
         hipLaunchKernelGGL(k_block_max<COLS>, dim3(grid_of(strips * ceil_div(blocks, per), 4)), dim3(256), 0, s, strips,
                            blocks, M->nbc, per, M->d_rbs(), M->d_cbs(), COLS ? M->d_col_off() : M->d_row_off(),
                            M->d_blk_off(), M->d_data(), mx.as<unsigned long long>());
@@ -968,7 +970,7 @@ int slice_operand(const bsmm_matrix_s *M, int64_t n, int64_t Kp, int S, int *e, 
                                (const int *)e, slices);
         return launch_check("emul slices");
     }
-    // Blocks are missing: through a panel of zeros.
+    // Blocks are missing (or huge): through a panel of zeros.
     DevBuf panel;
     BSMM_TRY(panel.reserve(sizeof(double) * n * Kp, s));
     BSMM_TRY(fill_zero(panel.as<double>(), n * Kp, s));
