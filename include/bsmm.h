@@ -250,9 +250,9 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
    "stack_at"    scheduled launch: "1" reads A's blocks from row-major
                  copies made for the multiply, "0" and "auto" (default) read
                  them in place; the same bits either way (not in
-                 bsmm_multiply_noalloc, which makes no copies).  Unless "1",
-                 an FP64 launch with many products per block of B reads B's
-                 blocks from such copies
+                 bsmm_multiply_noalloc, which makes no copies).  Unless "1", a
+                 launch with many products per block of B reads B's blocks
+                 from such copies
    "stack_sched" order in which the scheduled launch's waves take runs:
                  "dynamic" (default; a run counter per XCD, several short
                  runs per update) or "static" (fixed strides within the XCD)
@@ -270,7 +270,8 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
  *   "stack_params" "TM TN KC WAVES": the tuned path uses this parameter
  *                 set for every shape class ("" = select per shape)
  *   "dense_kb"    k step of the dense FP64 GEMM: "16" (default; 64 KB of
- *                 LDS, two workgroups per CU) or "32" (128 KB, one per CU)
+ *                 LDS, two workgroups per CU) or "32" (128 KB, one per CU;
+ *                 always with more than 67 million columns of A)
  *   "plan_cache"  "1": a multiply into C keeps its plan (symbolic totals,
  *                 stacks, launches or instantiated hipGraph); the next
  *                 multiply into C with the same A and B handles, unchanged

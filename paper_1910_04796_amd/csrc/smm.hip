@@ -627,19 +627,19 @@ template <class T> SmmKernel kernel_for(int tm, int tn) {
 thread_local double *t_norm_sink = nullptr;
 
 // The scheduled kernel reading A (or B) from row-major copies.
+template <class T> SmmKernel sched_kernel_t(bool a_rows, bool b_rows) {
+    if (a_rows) return k_smm_mfma_sched<T, kAlongK, kAlongK>;
+    return b_rows ? k_smm_mfma_sched<T, kAlongTile, kAlongTile> : k_smm_mfma_sched<T, kAlongTile, kAlongK>;
+}
 SmmKernel sched_kernel(int dtype, bool a_rows, bool b_rows) {
-    if (dtype == BSMM_F32)
-        return a_rows ? k_smm_mfma_sched<float, kAlongK, kAlongK> : k_smm_mfma_sched<float, kAlongTile, kAlongK>;
-    if (a_rows) return k_smm_mfma_sched<double, kAlongK, kAlongK>;
-    return b_rows ? k_smm_mfma_sched<double, kAlongTile, kAlongTile> : k_smm_mfma_sched<double, kAlongTile, kAlongK>;
+    return dtype == BSMM_F32 ? sched_kernel_t<float>(a_rows, b_rows) : sched_kernel_t<double>(a_rows, b_rows);
 }
 
 bool is_sched_kernel(const void *fn) {
-    return fn == (const void *)sched_kernel(BSMM_F64, false, false) ||
-           fn == (const void *)sched_kernel(BSMM_F64, false, true) ||
-           fn == (const void *)sched_kernel(BSMM_F64, true, false) ||
-           fn == (const void *)sched_kernel(BSMM_F32, false, false) ||
-           fn == (const void *)sched_kernel(BSMM_F32, true, false);
+    for (int dtype : {BSMM_F64, BSMM_F32})
+        for (int rows = 0; rows < 3; ++rows)
+            if (fn == (const void *)sched_kernel(dtype, rows == 1, rows == 2)) return true;
+    return false;
 }
 
 // Fewest products per block of B for which the scheduled launch reads B
@@ -647,12 +647,13 @@ bool is_sched_kernel(const void *fn) {
 // piece of 16 columns, from a copy one 128-byte piece of 4 rows of k: a
 // third fewer cache lines, which the launch feels once each B block is read
 // many times, while the copy costs one read and one write of B (and a launch).
-// Measured (whole multiply, FP64, in place -> from copies): banded 30 % 664 ->
+// Measured (whole multiply, in place -> from copies): FP64 banded 30 % 664 ->
 // 563 ms, 10 % 82.6 -> 70.1 ms, 5 % 30.4 -> 27.7 ms; 23-blocks at 20 % (70
 // products per B block) 1.95 -> 1.90 ms, at 10 % (35) 0.90 -> 0.85 ms;
 // {5,13,23}-blocks, N = 3000, at 25 % (55) 398 -> 413 us, at 10 % (22) 218 -> 237
-// us; banded 2 % and 1 % the same.  FP32, whose fragments are half as long,
-// gained nothing (10 %: 11.9 -> 12.1 ms).
+// us; banded 2 % and 1 % the same.  FP32, which the masks of B in place cost
+// more: banded 10 % 50.7 -> 40.5 ms, N = 24,000 9.89 -> 8.87 ms, 23-blocks at 20
+// % 1.29 -> 1.16 ms, N = 3000 at 25 % 311 -> 314 us.
 constexpr int64_t kCopyBMinUses = 48;
 
 constexpr int kLdsBudget = 64 * 1024;  // bytes of LDS per workgroup
@@ -777,6 +778,7 @@ unsigned smm_grid(const SmmLaunch &L, int64_t nruns) {
         }
         if (L.args.sched_per_cu > 0) per_cu = std::min(per_cu, L.args.sched_per_cu);
         wg_cap = (int64_t)cu_count() * per_cu;
+        return std::max<unsigned>(grid_of(waves_needed, L.waves, wg_cap), kXcds);  // every part has its waves
     }
     return grid_of(waves_needed, L.waves, wg_cap);
 }
@@ -994,7 +996,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         SmmLaunch L;
         // No copies with a scratch arena (they are as large as the operands).
         const bool at = options().stack_at == 1 && !scratch_arena();
-        const bool bt = !at && C->dtype == BSMM_F64 && !scratch_arena() && B->nnzb > 0 &&
+        const bool bt = !at && !scratch_arena() && B->nnzb > 0 &&
                         st.n_prod / B->nnzb >= kCopyBMinUses;
         ex->reads_a_t = at;
         ex->reads_b_t = bt;
@@ -1022,7 +1024,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         // Waves in flight share what an L2 holds, so fewer of them find more
         // there: FP64 three waves per SIMD (2 / 3 / 4 / 5: banded 10 % 61.6 / 58.6
         // / 60.3 / 60.9 ms, 30 % 540 / 537 / 564 / 565, 1 % - / 1.23 / 1.24 / 1.22),
-        // FP32, half the bytes each, four (banded 10 % 8.04 / 7.80 / 7.90 with 3
+        // FP32, half the bytes each, four (banded 10 % 7.25 / 6.75 / 6.75 with 3
         // / 4 / 5); launches of few runs also four, to end together (48,000
         // runs 251 / 236 / 233 us with 3 / 4 / 5).
         L.args.sched_per_cu = C->dtype == BSMM_F64 && st.n_sched >= 65536 ? 3 : 4;

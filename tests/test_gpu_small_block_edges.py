@@ -281,3 +281,26 @@ def test_threads_and_streams_read_back_their_own_counts():
     finally:
         set_path()
     assert not failed, failed
+
+
+@pytest.mark.parametrize("k", [1, 4, 7, 8, 9, 23, 32])
+def test_copied_b_f32(k):
+    """FP32 with enough products per B block for row-major copies of B: the
+    same bits as with both operands in place (stack_at "1"), and the exact
+    product of whole numbers."""
+    from tests.test_gpu_f32 import _as_f32, _f32_multiply
+    rng = rng_of(k)
+    rs = rng.choice([6, 14, 22, 31], size=70).astype(np.int32)
+    A, B = _matrices(k + 300, rs, np.full(7, k, np.int32), rs, 0.9, "int")
+    b = lib()
+    out = {}
+    try:
+        for at in ("0", "1"):
+            b.bsmm_set_option("stack_at", at)
+            out[at] = _f32_multiply(1.0, _as_f32(A), _as_f32(B), 0.0, path="stack", kernel="tuned",
+                                    params="16 16 0 4")
+    finally:
+        b.bsmm_set_option("stack_at", "auto")
+    assert out["0"][1]["n_sched_runs"] > 4096 and out["0"][1]["n_products"] >= 48 * len(B.col_ind)
+    check_against_oracle(out["0"][0], out["1"][0], 0.0)
+    check_against_oracle(out["0"][0], orc.multiply(1.0, A, B, 0.0), 0.0)
