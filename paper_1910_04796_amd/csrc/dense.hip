@@ -435,15 +435,29 @@ __global__ __launch_bounds__(64) void k_splitk_reduce(GemmArgs g) {
         const int2 rm = in ? g.rmap[row] : make_int2(0, 0);
         const int ld = in ? g.c_rbs[rm.x] : 0;
         const int ncol = (int)min((int64_t)16, g.N - col0);
-        for (int c = 0; c < ncol; ++c) {
-            const int2 cm = g.cmap[col0 + c];
+        // All lookups, then all old values, then the stores: one column after
+        // the other made 16 chains of dependent loads (210 tiles of 2 parts
+        // with beta = 1: 28 us, 23 so).
+        T *dst[16];
+        T old[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const int2 cm = g.cmap[col0 + min(c, ncol - 1)];
             const int64_t bidx = (int64_t)rm.x * g.c_nbc + cm.x;
-            const int32_t blk = !in ? -1 : g.c_map ? g.c_map[bidx] : (int32_t)bidx;
-            if (blk < 0) continue;
-            T *dst = static_cast<T *>(g.C) + g.c_blk_off[blk] + rm.y + (int64_t)ld * cm.y;
-            const T prod = alpha * s_out[c][lane];
-            *dst = (beta == T(0)) ? prod : fma(beta, *dst, prod);
+            const int32_t blk = !in || c >= ncol ? -1 : g.c_map ? g.c_map[bidx] : (int32_t)bidx;
+            dst[c] = blk < 0 ? nullptr : static_cast<T *>(g.C) + g.c_blk_off[blk] + rm.y + (int64_t)ld * cm.y;
         }
+        if (beta != T(0)) {
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                if (dst[c]) old[c] = *dst[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            if (dst[c]) {
+                const T prod = alpha * s_out[c][lane];
+                *dst[c] = (beta == T(0)) ? prod : fma(beta, old[c], prod);
+            }
         __syncthreads();  // the strip has been written before s_out is reused
     }
 }
