@@ -236,14 +236,12 @@ __global__ __launch_bounds__(256) void k_block_max(int32_t strips, int32_t block
     }
 }
 
-// Row exponents from the magnitudes of k_block_max.
-__global__ __launch_bounds__(256) void k_exp_of_max(const unsigned long long *mx, int64_t n, int *e) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double x = __longlong_as_double((long long)mx[i]);
-        int ex = 0;
-        if (x > 0.0 && x < __builtin_inf()) (void)frexp(x, &ex);
-        e[i] = x < __builtin_inf() ? ex : kNonFiniteExp;
-    }
+// The exponent of a row from its magnitude of k_block_max.
+__device__ __forceinline__ int exp_of_max(unsigned long long mx) {
+    const double x = __longlong_as_double((long long)mx);
+    int ex = 0;
+    if (x > 0.0 && x < __builtin_inf()) (void)frexp(x, &ex);
+    return x < __builtin_inf() ? ex : kNonFiniteExp;
 }
 
 // The S digits of N consecutive values of k, 4 to a word.
@@ -271,8 +269,8 @@ __device__ __forceinline__ void write_digits(double (&v)[N], int S, int64_t slic
 // read consecutive rows of a block), 32 values of k each.
 __global__ __launch_bounds__(256) void k_slice_rows(int64_t rows, int64_t cols, int64_t rows_p, int64_t ld, int32_t nbc,
                                                     int S, const int2 *rmap, const int2 *cmap, const int32_t *rbs,
-                                                    const int64_t *blk_off, const double *data, const int *e,
-                                                    signed char *out) {
+                                                    const int64_t *blk_off, const double *data,
+                                                    const unsigned long long *mx, int *e, signed char *out) {
     const int64_t tiles = rows_p / 64, items = tiles * (ld / 32);
     for (int64_t it = uniform((int64_t)blockIdx.x * 4 + wave_id()); it < items; it += (int64_t)gridDim.x * 4) {
         const int64_t p = it / tiles, r = it % tiles * 64 + lane_id();
@@ -295,7 +293,8 @@ __global__ __launch_bounds__(256) void k_slice_rows(int64_t rows, int64_t cols, 
                 if (in) v[j] = data[base + (int)(km >> 32) * m];
             }
         }
-        const int er = in ? e[r] : 0;
+        const int er = exp_of_max(mx[r]);  // (0 in the padding)
+        if (p == 0) e[r] = er;
 #pragma unroll
         for (int j = 0; j < 32; ++j) v[j] = er == kNonFiniteExp ? 0.0 : ldexp(v[j], -er);
         write_digits<32>(v, S, rows_p * ld, out + p * rows_p * 32 + r * 32);
@@ -307,8 +306,8 @@ __global__ __launch_bounds__(256) void k_slice_rows(int64_t rows, int64_t cols, 
 // values of k of one column.
 __global__ __launch_bounds__(256) void k_slice_cols(int64_t rows, int64_t cols, int64_t cols_p, int64_t ld, int32_t nbc,
                                                     int S, const int2 *rmap, const int2 *cmap, const int32_t *rbs,
-                                                    const int64_t *blk_off, const double *data, const int *e,
-                                                    signed char *out) {
+                                                    const int64_t *blk_off, const double *data,
+                                                    const unsigned long long *mx, int *e, signed char *out) {
     __shared__ double s_tile[4][16][65];
     double(*tile)[65] = s_tile[wave_id()];
     const int lane = lane_id();
@@ -337,7 +336,8 @@ __global__ __launch_bounds__(256) void k_slice_cols(int64_t rows, int64_t cols, 
         wave_lds_sync();
         const int64_t c = c0 + (lane >> 2);
         const int q = lane & 3;
-        const int er = c < cols ? e[c] : 0;
+        const int er = exp_of_max(mx[c]);  // (0 in the padding)
+        if (pp == 0 && q == 0) e[c] = er;
         double v[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
@@ -941,33 +941,39 @@ EmulKernel emul_kernel(int S, int variant) {
     }
 }
 
+// Whether slice_operand reads the blocks (k_block_max counts a block's
+// elements in 32 bits) or a panel.
+bool sliced_from_blocks(const bsmm_matrix_s *M) {
+    return M->full() && (int64_t)M->max_rbs * M->max_cbs < (1 << 28);
+}
+
 // Exponents and digit slices of A's rows (COLS: B's columns), n of them with
-// the padding, each Kp long.
+// the padding, each Kp long.  mx: n zeros for the magnitudes.
 template <bool COLS>
-int slice_operand(const bsmm_matrix_s *M, int64_t n, int64_t Kp, int S, int *e, signed char *slices, hipStream_t s) {
-    const int64_t largest = (int64_t)M->max_rbs * M->max_cbs;
-    if (M->full() && largest < (1 << 28)) {  // (k_block_max counts a block's elements in 32 bits)
-        DevBuf mx;
-        BSMM_TRY(mx.reserve(sizeof(unsigned long long) * n, s));
-        BSMM_TRY(fill_zero(mx.as<double>(), n, s));
+int slice_operand(const bsmm_matrix_s *M, int64_t n, int64_t Kp, int S, int *e, signed char *slices,
+                  unsigned long long *mx, hipStream_t s) {
+    if (sliced_from_blocks(M)) {
+        const int64_t largest = (int64_t)M->max_rbs * M->max_cbs;
         const int32_t strips = COLS ? M->nbc : M->nbr, blocks = COLS ? M->nbr : M->nbc;
-        // About 16,384 waves, each with at least 8,192 elements or one block.
+        // At most about 16,384 waves, each with at least 8,192 elements or one
+        // block unless that leaves fewer than 2,048: a wave's blocks are a serial
+        // chain of loads (800 x 800 x 800 in 13-blocks, multiply: 118 us, 176 with
+        // chains of 48 blocks on 82 waves).
         const int per = (int)std::min<int64_t>(
-            blocks, std::max<int64_t>({1, 8192 / largest, ceil_div((int64_t)strips * blocks, 16384)}));
+            blocks, std::max<int64_t>({1, std::min<int64_t>(8192 / largest, (int64_t)strips * blocks / 2048),
+                                          ceil_div((int64_t)strips * blocks, 16384)}));
         hipLaunchKernelGGL(k_block_max<COLS>, dim3(grid_of(strips * ceil_div(blocks, per), 4)), dim3(256), 0, s, strips,
                            blocks, M->nbc, per, M->d_rbs(), M->d_cbs(), COLS ? M->d_col_off() : M->d_row_off(),
-                           M->d_blk_off(), M->d_data(), mx.as<unsigned long long>());
-        hipLaunchKernelGGL(k_exp_of_max, dim3(grid_of(n, 256)), dim3(256), 0, s,
-                           (const unsigned long long *)mx.as<unsigned long long>(), n, e);
+                           M->d_blk_off(), M->d_data(), mx);
         BSMM_TRY(launch_check("emul exponents"));
         if (COLS)
             hipLaunchKernelGGL(k_slice_cols, dim3(grid_of(n / 16 * (Kp / 64), 4)), dim3(256), 0, s, M->rows(), M->cols(),
                                n, Kp, M->nbc, S, M->d_row_map(), M->d_col_map(), M->d_rbs(), M->d_blk_off(), M->d_data(),
-                               (const int *)e, slices);
+                               (const unsigned long long *)mx, e, slices);
         else
             hipLaunchKernelGGL(k_slice_rows, dim3(grid_of(n / 64 * (Kp / 32), 4)), dim3(256), 0, s, M->rows(), M->cols(),
                                n, Kp, M->nbc, S, M->d_row_map(), M->d_col_map(), M->d_rbs(), M->d_blk_off(), M->d_data(),
-                               (const int *)e, slices);
+                               (const unsigned long long *)mx, e, slices);
         return launch_check("emul slices");
     }
     // Blocks are missing (or huge): through a panel of zeros.
@@ -1012,13 +1018,18 @@ int emul_multiply(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s 
     const int64_t tile_m = wide ? WTM : ET, tile_n = wide ? WTN : ET;
     const int64_t Mp = ceil_div(M, tile_m) * tile_m, Np = ceil_div(N, tile_n) * tile_n;
     const int64_t Kp = ceil_div(K, EK) * EK;
-    DevBuf ea, eb, as, bs, V, cmap;
+    DevBuf ea, eb, as, bs, V, cmap, mx;
     BSMM_TRY(ea.reserve(sizeof(int) * Mp, s));
     BSMM_TRY(eb.reserve(sizeof(int) * Np, s));
     BSMM_TRY(as.reserve((size_t)S * Mp * Kp, s));
     BSMM_TRY(bs.reserve((size_t)S * Np * Kp, s));
-    BSMM_TRY(slice_operand<false>(A, Mp, Kp, S, ea.as<int>(), as.as<signed char>(), s));
-    BSMM_TRY(slice_operand<true>(B, Np, Kp, S, eb.as<int>(), bs.as<signed char>(), s));
+    if (sliced_from_blocks(A) || sliced_from_blocks(B)) {
+        BSMM_TRY(mx.reserve(sizeof(unsigned long long) * (Mp + Np), s));
+        BSMM_TRY(fill_zero(mx.as<double>(), Mp + Np, s));
+    }
+    unsigned long long *mxa = mx.as<unsigned long long>();
+    BSMM_TRY(slice_operand<false>(A, Mp, Kp, S, ea.as<int>(), as.as<signed char>(), mxa, s));
+    BSMM_TRY(slice_operand<true>(B, Np, Kp, S, eb.as<int>(), bs.as<signed char>(), mxa ? mxa + Mp : nullptr, s));
     const int32_t *d_cmap = nullptr;
     if (!C->full()) {
         const int64_t cells = (int64_t)C->nbr * C->nbc;
