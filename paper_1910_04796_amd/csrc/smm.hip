@@ -430,8 +430,13 @@ __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, in
 // An XCD that is done does not help the others: reading eight counters in
 // every wave costs 70 us at the end, more than the XCDs differ.
 constexpr int kSegBits = 8;
-// Fewest runs for which the MFMA classes go through the scheduled launch.
+// Fewest runs for which the MFMA classes go through the scheduled launch, and
+// the most classes that keep a launch each below that in a plan: a launch takes
+// 6 us, a graph of 9 or 16 of them 95 to 125 us to start, the scheduled launch
+// 35 us (400 x 400 x 400, 3,000 products, 16 classes: tuned 115 -> 36 us, plain
+// 106 -> 36; 9 classes of 200 x 200 x 200, plain: 54 -> 33).
 constexpr int64_t kSchedMinRuns = 4096;
+constexpr int kSchedFewClasses = 6;
 
 template <class T, OperandLayout LA, OperandLayout LB>
 __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
@@ -972,14 +977,18 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         }
     }
     int64_t sched_runs = 0, sched_prods = 0;
+    int sched_classes = 0;
     for (int cl = 0; cl < st.n_classes; ++cl)
         if (eligible[cl]) {
+            ++sched_classes;
             sched_runs += st.class_begin[cl + 1] - st.class_begin[cl];
             sched_prods += st.class_prod_begin[cl + 1] - st.class_prod_begin[cl];
         }
-    if (sched_on && sched_runs > 0 && sched_runs < kSchedMinRuns) {
+    if (sched_on && sched_runs > 0 && sched_runs < kSchedMinRuns &&
+        (sched_classes <= kSchedFewClasses || !options().plan_cache || scratch_arena())) {
         // Too few runs for the scheduling passes to pay off: those classes
-        // take their own launches after all.
+        // take their own launches after all (with a scratch arena always, as
+        // the schedule would need room there).
         for (int cl = 0; cl < st.n_classes; ++cl) {
             if (!eligible[cl]) continue;
             const int m = st.row_sizes[cl / st.ncs], n = st.col_sizes[cl % st.ncs];
@@ -1037,9 +1046,12 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     // does one with run-time compiled kernels (module functions, which a
     // graph kernel node does not take).  Up to three launches that are not
     // kept for a replay go one by one too: instantiating their graph takes
-    // longer than they gain from running side by side.
-    if (tuned && chunk <= 0 && launches.size() > (options().plan_cache ? 1u : 3u) && !scratch_arena() &&
-        st.n_jit == 0) {
+    // longer than they gain from running side by side.  The same holds for any
+    // number of launches of few runs (800 x 800 x 800 in 16 classes: 366 us with
+    // a graph, 199 us one by one).
+    const bool worth_graph = options().plan_cache ? launches.size() > 1
+                                                  : launches.size() > 3 && st.n_runs >= kSchedMinRuns;
+    if (tuned && chunk <= 0 && worth_graph && !scratch_arena() && st.n_jit == 0) {
         BSMM_TRY(build_graph(launches, A, B, C, st, alpha, beta, &ex->exec));
         BSMM_HIP(hipEventCreateWithFlags(&ex->done, hipEventDisableTiming));
     }

@@ -304,3 +304,26 @@ def test_copied_b_f32(k):
     assert out["0"][1]["n_sched_runs"] > 4096 and out["0"][1]["n_products"] >= 48 * len(B.col_ind)
     check_against_oracle(out["0"][0], out["1"][0], 0.0)
     check_against_oracle(out["0"][0], orc.multiply(1.0, A, B, 0.0), 0.0)
+
+
+@pytest.mark.parametrize("kernel", ["plain", "tuned"])
+@pytest.mark.parametrize("nb", [3, 4, 8, 40])
+@pytest.mark.parametrize("sizes,one_launch", [([5, 23], False), ([5, 13, 23], True), ([6, 14, 22, 30], True)])
+def test_few_runs_of_many_classes(sizes, one_launch, nb, kernel):
+    """Fewer runs than the scheduled launch asks for: in a plan it takes them
+    all the same when they are of more than six classes.  Integer values: exact."""
+    nb = max(nb, len(sizes))
+    rs = np.resize(np.array(sizes, np.int32), nb)
+    A, B = _matrices(nb + 300, rs, rs, rs, 1.0 if nb < 8 else 0.4, "int")
+    Cin = make_matrix(rng_of(nb), rs, rs, 0.3, "int")
+    b = lib()
+    saved = {k: b.bsmm_get_option(k) for k in ("stack_params", "plan_cache")}
+    b.bsmm_set_option("stack_params", "16 16 0 4")
+    b.bsmm_set_option("plan_cache", "1")
+    try:
+        X, st = gpu_multiply(2.0, A, B, -1.0, Cin, path="stack", kernel=kernel)
+    finally:
+        for k, v in saved.items():
+            b.bsmm_set_option(k, v)
+    assert (st["n_sched_runs"] > 0) == one_launch
+    check_against_oracle(X, orc.multiply(2.0, A, B, -1.0, Cin), 0.0)
