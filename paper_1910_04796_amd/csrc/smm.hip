@@ -480,9 +480,10 @@ __global__ __launch_bounds__(256, 4) void k_smm_mfma_sched(SmmArgs p) {
 
 // Row-major copies of a matrix's blocks at the blocks' own offsets: a wave
 // takes kTurnBlocks consecutive blocks of a block row (their lookups side by
-// side, one per lane) and turns each through LDS (blocks of up to about
-// kTurnElems elements), so that reads and writes are both contiguous; the
-// next block's elements are read while this one is written.  Bound by HBM
+// side, one per lane) and turns each through LDS (blocks of up to kTurnElems
+// elements, what a wave's registers read ahead, whose columns fit with an odd
+// stride), so that reads and writes are both contiguous; the next block's
+// elements are read while this one is written.  Bound by HBM
 // (16 bytes per FP64 element); 1.44 GB of 5-to-32-sided blocks 1,146 us with
 // one lookup per block and no read ahead, 642 us so (4.5 TB/s).
 constexpr int kTurnElems = 1024;
@@ -510,10 +511,11 @@ __global__ __launch_bounds__(256) void k_transpose_blocks(int32_t nbr, const int
                 my_k = cbs[ci[p0 + lane]];
             }
             T v[kRegs];
+            auto turned = [&](int k) { return (int64_t)m * k <= kTurnElems && (int64_t)ld * k <= kTurnElems + 64; };
             auto fetch = [&](int b) {
                 const T *sb = src + __shfl(my_off, b, kWave);
                 const int k = __shfl(my_k, b, kWave);
-                if ((int64_t)ld * k > kTurnElems + 64) return;
+                if (!turned(k)) return;
                 const int len = m * k;
 #pragma unroll
                 for (int u = 0; u < kRegs; ++u)
@@ -525,7 +527,7 @@ __global__ __launch_bounds__(256) void k_transpose_blocks(int32_t nbr, const int
                 const T *sb = src + __shfl(my_off, b, kWave);
                 T *db = dst + __shfl(my_off, b, kWave);
                 const int64_t len = (int64_t)m * k;
-                if ((int64_t)ld * k <= kTurnElems + 64) {
+                if (turned(k)) {
 #pragma unroll
                     for (int u = 0; u < kRegs; ++u) {
                         const int e = u * kWave + lane;

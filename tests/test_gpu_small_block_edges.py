@@ -306,6 +306,34 @@ def test_copied_b_f32(k):
     check_against_oracle(out["0"][0], orc.multiply(1.0, A, B, 0.0), 0.0)
 
 
+# (C block side, depth of the products): blocks of A and B on both sides of
+# the 1,024 elements that one turn through LDS holds, with an odd and an even
+# number of rows.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,k", [(32, 32), (32, 33), (31, 33), (31, 35), (23, 44), (23, 45), (23, 46), (22, 47),
+                                 (16, 64), (16, 65), (13, 79), (13, 80), (13, 200)])
+def test_copied_blocks_of_any_size(n, k, dtype):
+    """Row-major copies of blocks deeper than wide, of B (the rule on products
+    per B block) and of A (option "stack_at"): the exact product of whole
+    numbers."""
+    from tests.test_gpu_f32 import _as_f32, _f32_multiply
+    rs = np.full(70, n, np.int32)
+    A, B = _matrices(n * k, rs, np.full(2, k, np.int32), rs, 0.97, "int")
+    R = orc.multiply(1.0, A, B, 0.0)
+    b = lib()
+    try:
+        for at in ("auto", "1"):
+            b.bsmm_set_option("stack_at", at)
+            if dtype == "f64":
+                X, st = gpu_multiply(1.0, A, B, 0.0, path="stack")
+            else:
+                X, st = _f32_multiply(1.0, _as_f32(A), _as_f32(B), 0.0, path="stack")
+            assert st["n_sched_runs"] > 4096 and st["n_products"] >= 48 * len(B.col_ind)
+            check_against_oracle(X, R, 0.0)
+    finally:
+        b.bsmm_set_option("stack_at", "auto")
+
+
 @pytest.mark.parametrize("kernel", ["plain", "tuned"])
 @pytest.mark.parametrize("nb", [3, 4, 8, 40])
 @pytest.mark.parametrize("sizes,one_launch", [([5, 23], False), ([5, 13, 23], True), ([6, 14, 22, 30], True)])
