@@ -28,6 +28,7 @@
 #include "dev_util.h"
 #include "internal.h"
 #include "mfma_util.h"
+#include "split_rule.h"
 
 namespace bsmm {
 
@@ -540,34 +541,6 @@ int merge_panels(const bsmm_matrix_s *A, const bsmm_matrix_s *B, MergeArgs<T> a,
     return launch_check("merge_block");
 }
 
-// Parts of k for `tiles` output tiles of `ktiles` k steps on `slots`
-// resident workgroups: the count with the lowest estimated time, in units of
-// one k step of a resident workgroup (4 us in FP64).  All workgroups take
-// ceil(tiles * S / slots) rounds of ceil(ktiles / S) k steps, plus about
-// three for a workgroup's start and end; S > 1 also writes and reads S
-// partial outputs (tile_bytes each and tile, 4.5 TB/s).  Each part holds at
-// least eight k steps, the partials at most max_bytes.  Aiming at two rounds
-// whatever the tile count left the last one nearly empty: 1408 x 1408 (121
-// tiles) with k = 247,808 took 19.0 ms in 9 parts (2.13 rounds, three in
-// effect) and takes 15.0 ms in 21; 210 tiles of k = 2300 took 346 + 86 us in
-// 5 parts and 329 + 28 us in 2.
-int64_t gemm_splits(int64_t tiles, int64_t ktiles, int64_t slots, int64_t tile_bytes, int64_t max_bytes,
-                    double *cost) {
-    const int64_t part_bytes = tiles * tile_bytes;
-    const int64_t most = std::max<int64_t>(1, std::min<int64_t>({ktiles / 8, 64, max_bytes / part_bytes}));
-    int64_t best = 1;
-    for (int64_t S = 1; S <= most; ++S) {
-        const double rounds = (double)ceil_div(tiles * S, slots);
-        double c = rounds * (double)(ceil_div(ktiles, S) + 3);
-        if (S > 1) c += 2.0 * (double)(S * part_bytes) / 4.5e12 / 4e-6 + 2.0;
-        if (S == 1 || c < 0.98 * *cost) {
-            best = S;
-            *cost = c;
-        }
-    }
-    return best;
-}
-
 template <class T>
 int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
                      double alpha, double beta, hipStream_t s) {
@@ -628,29 +601,12 @@ int dense_multiply_t(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix
         part_cap = std::min<int64_t>(part_cap, (int64_t)(ar->cap - ar->used) - 512);
         part_cap = std::max<int64_t>(part_cap, 0);
     }
-    // All tiles in parts of k, or the full rounds' tiles whole and only the
-    // rest in parts (a launch more, about two steps): N = 3000 (576 tiles, 512
-    // slots) 1.11 -> 1.04 ms, N = 6000 (2209) 6.98 -> 6.61, FP32 2900 (529)
-    // 0.59 -> 0.54.  Dealing the k steps evenly to the workgroups instead filled
-    // every round, but put neighbours at different k: 1,408 x 1,408 x 247,808
-    // 13.9 -> 16.3 ms.
     const int64_t tile_bytes = (int64_t)sizeof(T) * BM * BN;
-    const int64_t rest = tiles % slots;
-    double cost_all = 0.0, cost_rest = 0.0;
-    int64_t splits = gemm_splits(tiles, g.ktiles, slots, tile_bytes, part_cap, &cost_all), whole = 0;
-    if (rest && rest < tiles) {
-        const int64_t r = gemm_splits(rest, g.ktiles, slots, tile_bytes, part_cap, &cost_rest);
-        cost_rest += (double)(tiles / slots) * (double)(g.ktiles + 3) + 2.0;
-        if (r > 1 && cost_rest < 0.98 * cost_all) {
-            splits = r;
-            whole = tiles - rest;
-        }
-    }
-    if (splits == 1) whole = tiles;
+    const DenseParts d = dense_parts(tiles, g.ktiles, slots, tile_bytes, part_cap, sizeof(T) == 8 ? 4.0 : 2.0);
+    const int64_t splits = d.splits, whole = d.whole;
     DevBuf part;
     if (splits > 1) {
-        g.kt_per = (int)ceil_div(g.ktiles, splits);
-        splits = ceil_div(g.ktiles, g.kt_per);  // no empty split
+        g.kt_per = (int)d.kt_per;
         g.splits = (int)splits;
         BSMM_TRY(part.reserve(tile_bytes * splits * (tiles - whole), s));
         g.part = part.p;
