@@ -219,8 +219,8 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
  *                 parameters from the tuning database, else the learned
  *                 model, else the plain rule.  Classes that "stack_tile"
  *                 does not gather have a launch each; tuned ones run together
- *                 as nodes of one hipGraph when a plan is kept or there are
- *                 more than three
+ *                 as nodes of one hipGraph when a plan is kept or their
+ *                 launches are long or many enough to gain by it
  *   "stack_chunk" maximum products per stack launch, "0" = unlimited
  *                 (paper, Sec. II: batches of at most 30000 products)
  *   "stack_tile"  "T" > 0 (default "32") runs every MFMA class of blocks up

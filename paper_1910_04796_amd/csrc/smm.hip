@@ -22,6 +22,7 @@
 //
 // The epilogue applies C = beta*C + alpha*acc (beta == 0 overwrites).
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "dev_util.h"
@@ -894,6 +895,21 @@ static int copy_rows(const bsmm_matrix_s *M, DevBuf &buf, hipStream_t s) {
     return launch_check("transpose_blocks");
 }
 
+// Estimated time (us) that the launch of class cl needs when few of its runs
+// fill the GPU: one run's products one after the other.  A wave takes 9.3
+// GFLOP/s on the register-tile kernel, 36 (FP32 twice that) on the MFMA kernel
+// and there at least 0.28 us per 8 values of k.
+static double launch_chain_us(const Stacks &st, int cl, const SmmLaunch &L, double k) {
+    if ((int)st.class_prod_begin.size() != st.n_classes + 1) return 0.0;
+    const double runs = (double)(st.class_begin[cl + 1] - st.class_begin[cl]);
+    const double prods = (double)(st.class_prod_begin[cl + 1] - st.class_prod_begin[cl]);
+    const double flops = 2.0 * st.row_sizes[cl / st.ncs] * st.col_sizes[cl % st.ncs] * k;
+    const bool mfma = L.args.kc_max == 0;  // (no k chunks in LDS)
+    const double us = mfma ? std::max(0.28 * std::ceil(k / 8.0), flops / (L.dtype == BSMM_F32 ? 72e3 : 36e3))
+                           : flops / 9.3e3;
+    return prods / std::max(runs, 1.0) / std::max(L.args.split, 1) * us;
+}
+
 int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C, Stacks &st,
                double alpha, double beta, hipStream_t s, StackExec *ex) {
     ex->launches.clear();
@@ -932,6 +948,14 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     const bool sched_on = (tuned || !scratch_arena()) && chunk <= 0 && options().stack_tile > 0 &&
                           (int)st.class_prod_begin.size() == st.n_classes + 1;
     std::vector<char> eligible(st.n_classes, 0);
+    const double mean_k = (double)A->cols() / std::max(A->nbc, 1);
+    double sum_us = 0.0, longest_us = 0.0;  // of the classes' own launches
+    auto own_launch = [&](int cl, const SmmLaunch &L) {
+        launches.push_back({L, {st.class_begin[cl], st.class_begin[cl + 1]}});
+        const double us = launch_chain_us(st, cl, L, mean_k);
+        sum_us += us;
+        longest_us = std::max(longest_us, us);
+    };
     for (int cl = 0; cl < st.n_classes; ++cl) {
         const int64_t rb = st.class_begin[cl], re = st.class_begin[cl + 1];
         if (re <= rb) continue;
@@ -966,7 +990,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
             }
         }
         if (chunk <= 0) {
-            launches.push_back({L, {rb, re}});
+            own_launch(cl, L);
             continue;
         }
         // Batches of at most `chunk` products; a run is never split.
@@ -997,7 +1021,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
             SmmLaunch L;
             BSMM_TRY(plan_smm(tuned ? select_params(m, n, krep, rlen[cl]) : plain_launch(m, n, krep), m, n, kmax,
                               C->dtype, &L));
-            launches.push_back({L, {st.class_begin[cl], st.class_begin[cl + 1]}});
+            own_launch(cl, L);
             eligible[cl] = 0;
         }
         sched_runs = 0;
@@ -1046,13 +1070,18 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     // Instantiating a graph may allocate device memory: a multiply running
     // on a scratch arena launches its classes one by one instead, and so
     // does one with run-time compiled kernels (module functions, which a
-    // graph kernel node does not take).  Up to three launches that are not
-    // kept for a replay go one by one too: instantiating their graph takes
-    // longer than they gain from running side by side.  The same holds for any
-    // number of launches of few runs (800 x 800 x 800 in 16 classes: 366 us with
-    // a graph, 199 us one by one).
-    const bool worth_graph = options().plan_cache ? launches.size() > 1
-                                                  : launches.size() > 3 && st.n_runs >= kSchedMinRuns;
+    // graph kernel node does not take).  Without a plan a graph is built for one
+    // use, about 190 us, which its launches have to save by running side by
+    // side: it is worth it when they take some 300 us longer one behind the
+    // other than the longest one alone (tuned, graph and one by one, us: 8 x 8
+    // blocks of 65 and 70, 6 products a run 478 and 997, 2 products 329 and 416;
+    // 8 x 8 blocks of 33 to 64, 40 products 669 and 1345, 5 products 363 and 424,
+    // 2 products 329 and 209; 12 x 12 blocks of 5 to 32, 40 products 458 and 500,
+    // 13 products 344 and 340, 5 products 360 and 206).  More than three launches
+    // of many runs gain by it whatever their length.
+    const bool worth_graph =
+        launches.size() > 1 && (options().plan_cache || sum_us - longest_us > 300.0 ||
+                                (launches.size() > 3 && st.n_runs >= kSchedMinRuns));
     if (tuned && chunk <= 0 && worth_graph && !scratch_arena() && st.n_jit == 0) {
         BSMM_TRY(build_graph(launches, A, B, C, st, alpha, beta, &ex->exec));
         BSMM_HIP(hipEventCreateWithFlags(&ex->done, hipEventDisableTiming));
