@@ -252,7 +252,8 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
                  them in place; the same bits either way (not in
                  bsmm_multiply_noalloc, which makes no copies).  Unless "1", a
                  launch with many products per block of B reads B's blocks
-                 from such copies
+                 from such copies, as large as B (a kept plan holds them), if
+                 there is memory for them, else in place
    "stack_sched" order in which the scheduled launch's waves take runs:
                  "dynamic" (default; a run counter per XCD, several short
                  runs per update) or "static" (fixed strides within the XCD)

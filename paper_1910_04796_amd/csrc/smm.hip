@@ -1031,12 +1031,17 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         SmmLaunch L;
         // No copies with a scratch arena (they are as large as the operands).
         const bool at = options().stack_at == 1 && !scratch_arena();
-        const bool bt = !at && !scratch_arena() && B->nnzb > 0 &&
-                        st.n_prod / B->nnzb >= kCopyBMinUses;
+        bool bt = !at && !scratch_arena() && B->nnzb > 0 &&
+                  st.n_prod / B->nnzb >= kCopyBMinUses;
+        if (at) BSMM_TRY(st.a_t.reserve(A->esize() * (size_t)(A->storage + 1), s));
+        // Without room for the copy B is read in place (the same bits): C may
+        // be grown already and earlier row panels written.
+        if (bt && st.b_t.reserve(B->esize() * (size_t)(B->storage + 1), s) != BSMM_OK) {
+            clear_error();
+            bt = false;
+        }
         ex->reads_a_t = at;
         ex->reads_b_t = bt;
-        if (at) BSMM_TRY(st.a_t.reserve(A->esize() * (size_t)(A->storage + 1), s));
-        if (bt) BSMM_TRY(st.b_t.reserve(B->esize() * (size_t)(B->storage + 1), s));
         L.fn = (void *)sched_kernel(C->dtype, at, bt);
         L.args.A_t = at ? st.a_t.p : nullptr;
         L.args.B_t = bt ? st.b_t.p : nullptr;

@@ -355,3 +355,60 @@ def test_few_runs_of_many_classes(sizes, one_launch, nb, kernel):
             b.bsmm_set_option(k, v)
     assert (st["n_sched_runs"] > 0) == one_launch
     check_against_oracle(X, orc.multiply(2.0, A, B, -1.0, Cin), 0.0)
+
+
+class RefusingAllocator:
+    """Device memory from torch's caching allocator, except requests of
+    `least` bytes up to an eighth more (the library rounds sizes up)."""
+
+    def __init__(self):
+        import torch
+        self.dev = torch.cuda.current_device()
+        self.least, self.refused, self.sizes = None, 0, []
+
+    def alloc(self, nbytes, stream):
+        import torch
+        if self.least and self.least <= nbytes <= self.least + self.least // 8 + 4096:
+            self.refused += 1
+            return 0
+        self.sizes.append(nbytes)
+        return torch.cuda.caching_allocator_alloc(nbytes, self.dev, stream if stream else None)
+
+    def dealloc(self, ptr, nbytes, stream):
+        import torch
+        torch.cuda.caching_allocator_delete(ptr)
+
+
+@pytest.mark.parametrize("panels", [False, True])
+@pytest.mark.parametrize("plan", ["0", "1"])
+def test_no_room_for_the_copy_of_b(plan, panels):
+    """A product whose copy of B finds no memory reads B in place: the same
+    blocks, whether C grows in the call, a plan is kept or C is made in
+    several row panels."""
+    rng = rng_of(91)
+    rs = np.full(70 if not panels else 210, 13, np.int32)
+    A, B = _matrices(92, rs, np.full(2, 200, np.int32), rs, 0.97, "int")
+    R = orc.multiply(1.0, A, B, 0.0)
+    b, ra = lib(), RefusingAllocator()
+    b.bsmm_set_allocator(ra.alloc, ra.dealloc)
+    saved = {k: b.bsmm_get_option(k) for k in ("plan_cache", "stack_panel")}
+    set_path("stack")
+    try:
+        b.bsmm_set_option("plan_cache", plan)
+        if panels:
+            b.bsmm_set_option("stack_panel", str(len(R.col_ind)))  # of two products per C block
+        MA, MB, MC = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B), b.Matrix.empty(A.rbs, B.cbs)
+        ra.least = 8 * (B.data.size + 1)
+        for _ in range(2):
+            b.multiply(1.0, MA, MB, 0.0, MC)
+            st = b.bsmm_last_stats()
+            check_against_oracle(MC.to_host(), R, 0.0)
+        for M in (MA, MB, MC):
+            M.close()
+    finally:
+        for k, v in saved.items():
+            b.bsmm_set_option(k, v)
+        set_path()
+        b.bsmm_set_allocator()
+    assert st["n_sched_runs"] > 4096 and ra.refused > 0
+    assert (st["n_row_panels"] > 1) == panels
