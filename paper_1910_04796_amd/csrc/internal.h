@@ -384,11 +384,11 @@ int stack_class_run_lengths(const bsmm_matrix_s *C, const Stacks &st, std::vecto
 int build_schedule(const bsmm_matrix_s *C, Stacks &st, const std::vector<char> &eligible, int tile,
                    hipStream_t s);
 // After stack_count: the runs and products of C block rows [r0, r1) (C
-// blocks [c0, c1), at most nprod products), replacing the previous panel's;
-// st.n_prod is set to the count held.
+// blocks [c0, c1)), replacing the previous panel's.  They have nprod products
+// (bound: at most so many); st.n_prod is set to the count held.
 int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix_s *C,
                Stacks &st, int32_t r0, int32_t r1, int64_t c0, int64_t c1, int64_t nprod,
-               hipStream_t s);
+               bool bound, hipStream_t s);
 
 // --------------------------------------------------------- small blocks
 // Parameters of the small-block kernel (the tuning space): register tile

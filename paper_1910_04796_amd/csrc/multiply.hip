@@ -347,7 +347,7 @@ int stacks_by_panels(bsmm_matrix_s *A, bsmm_matrix_s *B, bsmm_matrix_s *C, doubl
         int32_t r1 = r0 + 1;
         while (r1 < C->nbr && pb[r1 + 1] - pb[r0] <= cap) ++r1;
         if (pb[r1] > pb[r0]) {
-            BSMM_TRY(stack_rows(A, B, C, st, r0, r1, cb[r0], cb[r1], pb[r1] - pb[r0], s));
+            BSMM_TRY(stack_rows(A, B, C, st, r0, r1, cb[r0], cb[r1], pb[r1] - pb[r0], false, s));
             StackExec ex;  // a graph is retired only after its launch has completed
             BSMM_TRY(run_stacks(A, B, C, st, alpha, beta, s, &ex));
             runs += st.n_runs;

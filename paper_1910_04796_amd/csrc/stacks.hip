@@ -893,7 +893,7 @@ int stack_class_run_lengths(const bsmm_matrix_s *C, const Stacks &st, std::vecto
 
 int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix_s *C,
                Stacks &st, int32_t r0, int32_t r1, int64_t c0, int64_t c1, int64_t nprod,
-               hipStream_t s) {
+               bool bound, hipStream_t s) {
     const int32_t nbc = C->nbc;
     const int ncl = st.n_classes;
     const int64_t nblk = c1 - c0;
@@ -937,8 +937,13 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     BSMM_TRY(h.cb.record());
     // The rest is queued ahead of the host's wait, by what is known before
     // it: at most nblk runs (the scan's values past the runs are not used)
-    // and nprod products.
+    // and nprod products.  Where that is only a bound (the screen left blocks
+    // out, a third of the products at 1 %), the list waits for its own count.
     if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), nblk, s));
+    if (bound) {
+        BSMM_TRY(h.cb.wait());
+        nprod = h.cb.host<int64_t>()[2 * ncl + 1];
+    }
     if (nprod > 0 && nbc > kMaxStackCols) {
         BSMM_TRY(st.prods.reserve(sizeof(ulonglong2) * nprod, s));
         hipLaunchKernelGGL(k_stack_fill_win, dim3(grid_rows(r1 - r0), st.kparts), dim3(256), 0, s, r0, r1,
@@ -971,7 +976,7 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
                            (const int64_t *)st.run_ptr.as<int64_t>(), st.prods.as<ulonglong2>());
         BSMM_TRY(launch_check("stack_fill"));
     }
-    BSMM_TRY(h.cb.wait());
+    if (!bound) BSMM_TRY(h.cb.wait());
     const int64_t *both = h.cb.host<int64_t>();
     BSMM_TRY(check_missing(st, both[2 * ncl + 1], nprod));
     st.class_begin.assign(both, both + ncl + 1);
@@ -988,7 +993,7 @@ int build_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matr
                  Stacks &st, hipStream_t s) {
     const int64_t nprod = st.n_prod;
     BSMM_TRY(stack_count(A, B, C, st, s));
-    return stack_rows(A, B, C, st, 0, C->nbr, 0, C->nnzb, nprod, s);
+    return stack_rows(A, B, C, st, 0, C->nbr, 0, C->nnzb, nprod, st.screened, s);
 }
 
 }  // namespace bsmm

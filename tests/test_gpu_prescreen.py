@@ -248,3 +248,33 @@ def test_screen_plain_with_beta():
     assert st1["n_screened"] > 0
     check_against_oracle(X1, X0, 0.0)
     check_against_oracle(X1, orc.multiply(2.0, A, B, -0.5, Cin, filter_eps=1e-10), TOL)
+
+
+def test_screened_lists_hold_what_is_computed():
+    """Device memory of the product list: 16 bytes for each product that is
+    computed, not for those of blocks that the screen left out."""
+    import torch
+    A, B = _steep(75, target=4000)
+    b = lib()
+    dev, sizes = torch.cuda.current_device(), []
+
+    def alloc(nbytes, stream):
+        sizes.append(nbytes)
+        return torch.cuda.caching_allocator_alloc(nbytes, dev, stream if stream else None)
+
+    b.bsmm_set_allocator(alloc, lambda ptr, nbytes, stream: torch.cuda.caching_allocator_delete(ptr))
+    try:
+        MA, MB, MC = b.Matrix.from_blocks(A), b.Matrix.from_blocks(B), b.Matrix.empty(A.rbs, B.cbs)
+        del sizes[:]
+        b.bsmm_set_option("path", "stack")
+        b.multiply(1.0, MA, MB, 0.0, MC, 1e-2)
+        st = b.bsmm_last_stats()
+        for M in (MA, MB, MC):
+            M.close()
+    finally:
+        b.bsmm_set_option("path", "auto")
+        b.bsmm_set_allocator()
+    run, all_ = 16 * st["n_products_run"], 16 * st["n_products"]
+    assert 1.2 * run < all_, (run, all_)
+    up = run + run // 8 + 4096  # (sizes are rounded up by at most an eighth)
+    assert any(run <= x <= up for x in sizes) and not any(all_ <= x <= all_ + all_ // 8 + 4096 for x in sizes)
