@@ -144,86 +144,87 @@ struct Readback::Slot {
     }
 };
 static std::mutex g_readback_mu;
-std::vector<Readback::Slot *> &Readback::idle_slots() {
-    static auto *v = new std::vector<Slot *>();  // outlives the runtime's own teardown
-    return *v;
-}
+static Readback::Slot *g_idle[16];
+static int g_n_idle = 0;
 
 void release_readback_slots() {
     std::lock_guard<std::mutex> lk(g_readback_mu);
-    for (Readback::Slot *x : Readback::idle_slots()) delete x;
-    Readback::idle_slots().clear();
+    while (g_n_idle > 0) delete g_idle[--g_n_idle];
+}
+
+// An idle buffer of the current device or a new one; null when page-locked
+// memory or an event is not to be had.
+static Readback::Slot *take_slot(int device) {
+    {
+        std::lock_guard<std::mutex> lk(g_readback_mu);
+        for (int i = g_n_idle; i-- > 0;)
+            if (g_idle[i]->device == device) {
+                Readback::Slot *x = g_idle[i];
+                g_idle[i] = g_idle[--g_n_idle];
+                return x;
+            }
+    }
+    auto *x = new (std::nothrow) Readback::Slot();
+    if (!x) return nullptr;
+    x->device = device;
+    if (hipHostMalloc(&x->p, Readback::kMaxBytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
+        x->p = nullptr;
+    } else if (hipEventCreateWithFlags(&x->ev, hipEventDisableTiming) != hipSuccess) {
+        x->ev = nullptr;
+    } else {
+        return x;
+    }
+    (void)hipGetLastError();
+    delete x;
+    return nullptr;
 }
 
 int Readback::reserve(size_t bytes, hipStream_t s) {
     s_ = s;
     bytes_ = bytes;
-    if (scratch_arena()) {
-        BSMM_TRY(tmp_.reserve(bytes, s));
-        dev_ = tmp_.p;
-        return BSMM_OK;
-    }
     if (bytes > kMaxBytes) {
         set_error(BSMM_ERANGE, "%zu bytes to read back at once", bytes);
         return BSMM_ERANGE;
     }
-    int device = 0;
-    BSMM_HIP(hipGetDevice(&device));
-    {
-        std::lock_guard<std::mutex> lk(g_readback_mu);
-        auto &idle = idle_slots();
-        for (size_t i = idle.size(); i-- > 0;)
-            if (idle[i]->device == device) {
-                slot_ = idle[i];
-                idle.erase(idle.begin() + (long)i);
-                break;
-            }
+    if (!scratch_arena()) {
+        int device = 0;
+        BSMM_HIP(hipGetDevice(&device));
+        slot_ = take_slot(device);
     }
-    if (!slot_) {
-        auto *x = new (std::nothrow) Slot();
-        if (!x || hipHostMalloc(&x->p, kMaxBytes, hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess ||
-            hipEventCreateWithFlags(&x->ev, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            delete x;
-            set_error(BSMM_ENOMEM, "page-locked host memory is not available");
-            return BSMM_ENOMEM;
-        }
-        x->device = device;
-        slot_ = x;
+    if (slot_) {
+        dev_ = slot_->p;
+        return BSMM_OK;
     }
-    dev_ = slot_->p;
+    BSMM_TRY(tmp_.reserve(bytes, s));
+    dev_ = tmp_.p;
+    copy_.reset(new (std::nothrow) char[bytes]);
+    if (!copy_) {
+        set_error(BSMM_ENOMEM, "host allocation failed");
+        return BSMM_ENOMEM;
+    }
     return BSMM_OK;
 }
 
 int Readback::record() {
-    if (!slot_) {
-        copy_.resize(bytes_);
-        BSMM_HIP(hipMemcpyAsync(copy_.data(), dev_, bytes_, hipMemcpyDeviceToHost, s_));
-        return BSMM_OK;
-    }
-    BSMM_HIP(hipEventRecord(slot_->ev, s_));
-    recorded_ = true;
+    if (slot_) BSMM_HIP(hipEventRecord(slot_->ev, s_));
+    else BSMM_HIP(hipMemcpyAsync(copy_.get(), dev_, bytes_, hipMemcpyDeviceToHost, s_));
     return BSMM_OK;
 }
 
 int Readback::wait() {
-    if (!slot_) {
-        BSMM_HIP(hipStreamSynchronize(s_));
-        host_ = copy_.data();
-        return BSMM_OK;
-    }
-    BSMM_HIP(hipEventSynchronize(slot_->ev));
+    if (slot_) BSMM_HIP(hipEventSynchronize(slot_->ev));
+    else BSMM_HIP(hipStreamSynchronize(s_));
     waited_ = true;
-    host_ = slot_->p;
+    host_ = slot_ ? slot_->p : copy_.get();
     return BSMM_OK;
 }
 
 Readback::~Readback() {
+    // Kernels and copies may still write when the multiply ended early.
+    if (dev_ && !waited_) (void)hipStreamSynchronize(s_);
     if (!slot_) return;
-    // Kernels may still write when the multiply ended early.
-    if (!waited_) (void)hipStreamSynchronize(s_);
     std::lock_guard<std::mutex> lk(g_readback_mu);
-    if (idle_slots().size() < 16) idle_slots().push_back(slot_);
+    if (g_n_idle < 16) g_idle[g_n_idle++] = slot_;
     else delete slot_;
 }
 

@@ -13,6 +13,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -159,10 +160,12 @@ struct DevBuf {
 // event behind them, so that work queued after record() runs on.  Buffers
 // and events come from a small pool (at most 16 idle) that
 // bsmm_set_allocator(NULL) gives back.
-// While a scratch arena is active (nothing may be allocated) the values go
-// through device memory and a copy instead.
+// While a scratch arena is active (nothing may be allocated), and where
+// page-locked memory is short, the values go through device memory and a copy
+// instead.
 class Readback {
   public:
+    struct Slot;
     Readback() = default;
     Readback(const Readback &) = delete;
     Readback &operator=(const Readback &) = delete;
@@ -175,17 +178,14 @@ class Readback {
     static constexpr size_t kMaxBytes = 32768;
 
   private:
-    struct Slot;
-    friend void release_readback_slots();
-    static std::vector<Slot *> &idle_slots();
     Slot *slot_ = nullptr;
     void *dev_ = nullptr;
     const void *host_ = nullptr;
     hipStream_t s_ = nullptr;
-    bool recorded_ = false, waited_ = false;
+    bool waited_ = false;
     size_t bytes_ = 0;
     DevBuf tmp_;
-    std::vector<char> copy_;
+    std::unique_ptr<char[]> copy_;
 };
 void release_readback_slots();
 
