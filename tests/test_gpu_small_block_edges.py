@@ -412,3 +412,23 @@ def test_no_room_for_the_copy_of_b(plan, panels):
         b.bsmm_set_allocator()
     assert st["n_sched_runs"] > 4096 and ra.refused > 0
     assert (st["n_row_panels"] > 1) == panels
+
+
+@pytest.mark.parametrize("nk", [4, 12])
+@pytest.mark.parametrize("nbc", [8160, 8161, 8192, 8193, 32736, 32737, 40000])
+def test_counts_of_wide_rows(nbc, nk):
+    """C rows whose bitmap has fewer words than a workgroup has threads, as
+    many and more (256 threads, 1,024 for a few long rows of A), with blocks of
+    different widths: blocks, elements, products and flops counted right."""
+    rng = rng_of(nbc + nk)
+    rs, ks = np.array([2, 1, 3], np.int32), np.full(nk, 2, np.int32)
+    ns = rng.choice([1, 2, 5], size=nbc).astype(np.int32)
+    A, B = _matrices(nbc, rs, ks, ns, 1.0, "int")
+    keep = rng.random(len(B.col_ind)) < 0.01
+    keep[[0, nbc - 1]] = True
+    rows = np.repeat(np.arange(nk), np.diff(B.row_ptr))
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=nk))]).astype(np.int64)
+    B = BlockCSR(B.rbs, B.cbs, rp, B.col_ind[keep], B.data[np.repeat(keep, 2 * ns[B.col_ind])])
+    X, st = gpu_multiply(1.0, A, B, 0.0, path="stack")
+    check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
+    assert st["n_products"] == 3 * len(B.col_ind) and st["flops"] == 2.0 * 6 * 2 * ns[B.col_ind].sum()
