@@ -27,8 +27,8 @@
 
 #include "dev_util.h"
 #include "internal.h"
+#include "launch_rules.h"
 #include "mfma_util.h"
-#include "split_rule.h"
 
 namespace bsmm {
 

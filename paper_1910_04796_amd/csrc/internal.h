@@ -438,6 +438,7 @@ struct SmmArgs {
     unsigned long long *next;
     int sched_mode;
     int sched_chunk;        // schedule entries taken per wave at a time (a power of two)
+    int sched_seg_bits;     // log2 of the entries that go to one XCD in a row (at least sched_chunk)
     int sched_per_cu;       // most workgroups per CU
     // Scheduled kernel, when the multiply filters: squared Frobenius norm of
     // every finished C block, norm2[run_cblk[r]] (run_cblk: C block of run r).

@@ -1,4 +1,5 @@
-// split_rule.h -- into how many parts the dense GEMM cuts k (host code only).
+// launch_rules.h -- how work is cut into launches and workgroups, by sizes
+// alone (host code only).
 #pragma once
 #include <algorithm>
 #include <cstdint>
@@ -78,6 +79,21 @@ inline DenseParts dense_parts(int64_t tiles, int64_t ktiles, int64_t slots, int6
     d.kt_per = (ktiles + d.splits - 1) / d.splits;
     d.splits = (ktiles + d.kt_per - 1) / d.kt_per;  // no empty part
     return d;
+}
+
+// log2 of the entries of a schedule of n runs that go to one XCD in a row: 256
+// entries from 16,384 runs on, below that as many as leave each XCD eight
+// segments, at least four entries (the largest piece that a wave takes).  With
+// 256 always, up to 256 runs all lay on one XCD, and of 4,225 some XCDs had three
+// segments and the others two (plans of nine classes, with 256 and so):
+//   16 runs of 8 products   49 and 30 us       900 runs of 24      73 and 50 us
+//   144 runs of 8           70 and 31          900 runs of 81     195 and 107
+//   196 runs of 81         365 and 100       4,225 runs of 32     141 and 130
+//   196 runs of 324       1458 and 326       4,225 runs of 81     278 and 240
+inline int schedule_segment_bits(int64_t n, int xcds) {
+    int bits = 2;
+    while (bits < 8 && n >> (bits + 1) >= 8 * xcds) ++bits;
+    return bits;
 }
 
 }  // namespace bsmm

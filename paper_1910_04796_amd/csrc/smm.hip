@@ -27,6 +27,7 @@
 
 #include "dev_util.h"
 #include "internal.h"
+#include "launch_rules.h"
 #include "mfma_util.h"
 
 namespace bsmm {
@@ -416,26 +417,26 @@ __device__ __forceinline__ void sched_run(const SmmArgs &p, int64_t r, int m, in
     if (p.norm2 && lane_id() == 0) p.norm2[p.run_cblk[r]] = ss;
 }
 
-// Segments of 2^kSegBits schedule entries go to the XCDs in turn (workgroup
-// g runs on XCD g % 8) and each XCD's waves take theirs in order, so that the
-// runs of a tile meet in one L2: banded 30 % 639 -> 611 ms, banded 10 % 67.8 ->
-// 64.9 against one order for all XCDs, with tiles of 32 x 32; segments of 32
-// to 1,024 entries differ by 2 %.  The next entry is taken when the last one is
-// done, not ahead of it: runs taken one after the other also start one after
-// the other, and share operands while they are at the same k (taken ahead:
-// 30 % 563 -> 608 ms).
+// Segments of 2^sched_seg_bits schedule entries go to the XCDs in turn
+// (workgroup g runs on XCD g % 8) and each XCD's waves take theirs in order, so
+// that the runs of a tile meet in one L2: banded 30 % 639 -> 611 ms, banded 10 %
+// 67.8 -> 64.9 against one order for all XCDs, with tiles of 32 x 32; segments
+// of 32 to 1,024 entries differ by 2 %.  The next entry is taken when the last
+// one is done, not ahead of it: runs taken one after the other also start one
+// after the other, and share operands while they are at the same k (taken
+// ahead: 30 % 563 -> 608 ms).
 //
 // One counter per XCD.  Updates of one address follow one another about 15 ns
 // apart, so a single counter bounded launches of many short runs
 // ({5,13,23}-blocks at 25 %, 48,000 runs: 505 us; four or eight counters 300 us).
 // An XCD that is done does not help the others: reading eight counters in
-// every wave costs 70 us at the end, more than the XCDs differ.
-constexpr int kSegBits = 8;
+// every wave costs 70 us at the end, more than the XCDs differ.  So a short
+// schedule has shorter segments, eight or more for each XCD (schedule_segment_bits).
 // Fewest runs for which the MFMA classes go through the scheduled launch, and
 // the most classes that keep a launch each below that in a plan: a launch takes
-// 6 us, a graph of 9 or 16 of them 95 to 125 us to start, the scheduled launch
-// 35 us (400 x 400 x 400, 3,000 products, 16 classes: tuned 115 -> 36 us, plain
-// 106 -> 36; 9 classes of 200 x 200 x 200, plain: 54 -> 33).
+// 6 us, a graph of 9 or 16 of them 95 to 125 us to start, a scheduled replay
+// 31 us (9 classes, plan, as a graph and so: 12 x 12 blocks, 8 products a run 96
+// and 31 us, 4 x 4 blocks 95 and 30; 16 classes of 400 x 400 x 400 as a graph 115).
 constexpr int64_t kSchedMinRuns = 4096;
 constexpr int kSchedFewClasses = 6;
 
@@ -444,12 +445,12 @@ __device__ __forceinline__ void sched_loop(const SmmArgs &p) {
     const int wpw = blockDim.x / kWave;
     // A wave takes `chunk` consecutive entries at a time (short runs: fewer
     // counter updates), the first ones by its number in its XCD.
-    const int chunk = max(p.sched_chunk, 1);
+    const int chunk = max(p.sched_chunk, 1), seg = p.sched_seg_bits;
     const int x = blockIdx.x % kXcds;
     const int64_t waves = (int64_t)((gridDim.x - x + kXcds - 1) / kXcds) * wpw;
     int64_t pos = ((int64_t)(blockIdx.x / kXcds) * wpw + uniform(wave_id())) * chunk;
     while (true) {
-        const int64_t it = (((pos >> kSegBits) * kXcds + x) << kSegBits) + (pos & ((1 << kSegBits) - 1));
+        const int64_t it = (((pos >> seg) * kXcds + x) << seg) + (pos & ((1 << seg) - 1));
         if (it >= p.n_sched) break;  // pos only grows, and `it` with it
         const int64_t end = min(it + chunk, p.n_sched);
         for (int64_t i = it; i < end; ++i) {
@@ -1061,6 +1062,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
         // / 4 / 8 / 16 runs per update).
         const int64_t mean_len = std::max<int64_t>(1, sched_prods / sched_runs);
         L.args.sched_chunk = mean_len >= 4 ? 1 : mean_len >= 2 ? 2 : 4;
+        L.args.sched_seg_bits = schedule_segment_bits(st.n_sched, kXcds);
         // Waves in flight share what an L2 holds, so fewer of them find more
         // there: FP64 three waves per SIMD (2 / 3 / 4 / 5: banded 10 % 61.6 / 58.6
         // / 60.3 / 60.9 ms, 30 % 540 / 537 / 564 / 565, 1 % - / 1.23 / 1.24 / 1.22),

@@ -1,6 +1,7 @@
-"""The rule that cuts k of a dense product into parts (host code, compiled here
-with the host compiler): every k step in one part, partial sums within their
-bound, and no chain of sums longer than about two rounds of workgroups make it."""
+"""Rules of the launches (host code, compiled here with the host compiler).
+Parts of k of a dense product: every k step in one part, partial sums within
+their bound, and no chain of sums longer than about two rounds of workgroups
+make it.  Segments of a schedule: every XCD a like share of the runs."""
 import ctypes
 import os
 import random
@@ -9,7 +10,7 @@ import subprocess
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = """#include "split_rule.h"
+SRC = """#include "launch_rules.h"
 extern "C" void parts(int64_t tiles, int64_t ktiles, int64_t slots, int64_t tile_bytes, int64_t max_bytes,
                       double step_us, int64_t *out) {
     const bsmm::DenseParts d = bsmm::dense_parts(tiles, ktiles, slots, tile_bytes, max_bytes, step_us);
@@ -17,18 +18,24 @@ extern "C" void parts(int64_t tiles, int64_t ktiles, int64_t slots, int64_t tile
     out[1] = d.splits;
     out[2] = d.kt_per;
 }
+extern "C" int segment_bits(int64_t n) { return bsmm::schedule_segment_bits(n, 8); }
 """
 
 
 @pytest.fixture(scope="module")
-def parts(tmp_path_factory):
-    d = tmp_path_factory.mktemp("split_rule")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launch_rules")
     (d / "rule.cpp").write_text(SRC)
     so = str(d / "rule.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC",
                     "-I" + os.path.join(ROOT, "paper_1910_04796_amd", "csrc"), str(d / "rule.cpp"), "-o", so],
                    check=True)
-    fn = ctypes.CDLL(so).parts
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def parts(rules):
+    fn = rules.parts
     fn.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_double, ctypes.POINTER(ctypes.c_int64)]
 
     def call(tiles, ktiles, slots, tile_bytes, max_bytes, step_us):
@@ -66,3 +73,20 @@ def test_parts_cover_k_and_are_never_too_long(parts, max_bytes, tile_bytes, step
         if tiles < slots:
             want = max(1, min(-(-2 * slots // tiles), ktiles // 16, max_bytes // (tiles * tile_bytes)))
             assert (ktiles if whole else per) <= -(-ktiles // want), case
+
+
+def test_segments_share_the_runs(rules):
+    """Segment after segment goes to the next XCD: no XCD has more than an
+    eighth of the runs and one segment, and a segment is a small part of that
+    share unless it is the smallest there is."""
+    rules.segment_bits.argtypes = [ctypes.c_int64]
+    rng = random.Random(8)
+    sizes = [1, 3, 4, 5, 9, 31, 32, 33, 144, 196, 255, 256, 257, 900, 4096, 4225, 16383, 16384, 10**6, 10**9]
+    for n in sizes + [int(2 ** rng.uniform(0, 30)) for _ in range(300)]:
+        seg = 1 << rules.segment_bits(n)
+        assert 4 <= seg <= 256, n
+        assert seg == 4 or n // seg >= 64, n
+        assert seg == 256 or n // seg < 130, n
+        full, last = divmod(n, seg)
+        share = [((full - x + 7) // 8) * seg + (last if full % 8 == x else 0) for x in range(8)]
+        assert sum(share) == n and max(share) <= n // 8 + seg, n
