@@ -40,14 +40,15 @@ def test_transposed_a_same_bits(dtype):
 
 
 def test_transposed_a_replay_sees_new_values():
-    """FP32 (copies by default) with the plan cache: the second multiply
-    replays the plan after A was doubled in place (same pattern and
-    buffers, so the plan still holds) and must use the doubled values."""
+    """A read from copies with the plan cache: the second multiply replays the
+    plan after A was doubled in place (same pattern and buffers, so the plan
+    still holds) and must use the doubled values."""
     from tests.test_gpu_f32 import TOL32, _as_f32
     A, B = _case(102)
     A, B = _as_f32(A), _as_f32(B)
     b = lib()
     b.bsmm_set_option("plan_cache", "1")
+    b.bsmm_set_option("stack_at", "1")
     set_path("stack", "tuned")
     try:
         MA, MB = b.Matrix.from_blocks(A, dtype="f32"), b.Matrix.from_blocks(B, dtype="f32")
@@ -69,6 +70,7 @@ def test_transposed_a_replay_sees_new_values():
             M.close()
     finally:
         b.bsmm_set_option("plan_cache", "0")
+        b.bsmm_set_option("stack_at", "auto")
         set_path()
     assert st["n_sched_runs"] > 4096
     check_against_oracle(X2, orc.multiply(2.0, A, B, 0.0), TOL32)
