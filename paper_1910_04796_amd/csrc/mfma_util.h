@@ -16,6 +16,9 @@ typedef __amdgpu_buffer_rsrc_t BufferRsrc;
 __device__ __forceinline__ BufferRsrc buffer_at(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);  // raw, 32-bit data
 }
+// An offset past the end of any buffer of less than 2 GB, all 16 bytes from it too
+// (an offset near 2^32 would wrap to the buffer's first bytes).
+constexpr uint32_t kPastBuffer = 1u << 31;
 
 // Both instructions take lane l's operands at row (or column) l % 16 and
 // k = l / 16 of the step and return four results per lane.

@@ -217,7 +217,7 @@ template <class T, int NTILE, OperandLayout LAY> struct Operand {
             // Past the row's last k lies the next row: such lanes read past
             // the buffer, and half a pair is cleared by mfma_chunk.
 #pragma unroll
-            for (int t = 0; t < NTILE; ++t) Mfma<T>::load2(r, 2 * lk < left ? off[t] : ~0u, f[0][t], f[1][t]);
+            for (int t = 0; t < NTILE; ++t) Mfma<T>::load2(r, 2 * lk < left ? off[t] : kPastBuffer, f[0][t], f[1][t]);
         }
     }
 };
@@ -325,7 +325,7 @@ template <class T, int MT, int NT, bool SUMSQ>
 __device__ __forceinline__ double mfma_store(T *c, int m, int n,
                                              const typename Mfma<T>::acc_t (&acc)[MT][NT],
                                              bool partial, T alpha, T beta) {
-    constexpr uint32_t kSize = sizeof(T), kOut = 1u << 31;
+    constexpr uint32_t kSize = sizeof(T);
     const int lane = lane_id();
     const int lr = lane & 15, lk = lane >> 4;
     const BufferRsrc r = buffer_at(c, (uint32_t)m * (uint32_t)n * kSize);
@@ -335,7 +335,7 @@ __device__ __forceinline__ double mfma_store(T *c, int m, int n,
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int row = tile_row<MT>(i, Mfma<T>::row(e, lk));
-            ro[i][e] = row < m ? (uint32_t)row * kSize : kOut;
+            ro[i][e] = row < m ? (uint32_t)row * kSize : kPastBuffer;
         }
     double ss = 0.0;
 #pragma unroll
@@ -372,7 +372,7 @@ __device__ __forceinline__ double mfma_store(T *c, int m, int n,
             for (int e = 0; e < 4; ++e) {
                 Mfma<T>::store(r, co + ro[i][e], v[i][e]);
                 if (SUMSQ) {
-                    const double x = ro[i][e] != kOut && col < n ? (double)v[i][e] : 0.0;
+                    const double x = ro[i][e] != kPastBuffer && col < n ? (double)v[i][e] : 0.0;
                     ss = fma(x, x, ss);
                 }
             }

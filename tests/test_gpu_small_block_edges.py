@@ -94,6 +94,44 @@ def test_infinities_stay_in_their_rows_and_columns(depths, blocks, at):
     check_against_oracle(X, R, 0.0)
 
 
+@pytest.mark.parametrize("at", ["0", "1"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("k", [1, 3, 5, 7, 9])
+def test_first_values_stay_in_their_row_and_column(k, dtype, at):
+    """Infinities in the first values of every block of A (the row-major copy
+    then begins with row 0) and of B (column 0): lanes whose values of k lie
+    past a product's depth must not read them, so only row 0 and column 0 of
+    every block of C are not finite."""
+    from tests.test_gpu_f32 import _as_f32, _f32_multiply
+    rng = rng_of(k)
+    rs = rng.choice([9, 16, 17, 23], size=70).astype(np.int32)
+    A, B = _matrices(k + 400, rs, np.array([k], np.int32), rs, 1.0, "int")
+    A.data[np.cumsum(rs * k) - rs * k] = np.inf
+    B.data[np.cumsum(rs * k) - rs * k] = np.inf
+    A.data[A.data == 0.0] = 1.0  # (0 x infinity)
+    B.data[B.data == 0.0] = 1.0
+    b = lib()
+    saved = {k: b.bsmm_get_option(k) for k in ("stack_at", "stack_params")}
+    b.bsmm_set_option("stack_at", at)
+    b.bsmm_set_option("stack_params", "16 16 0 4")
+    try:
+        if dtype == "f64":
+            X, st = gpu_multiply(1.0, A, B, 0.0, path="stack", kernel="tuned")
+        else:
+            X, st = _f32_multiply(1.0, _as_f32(A), _as_f32(B), 0.0, path="stack", kernel="tuned",
+                                 params="16 16 0 4")
+    finally:
+        for key, v in saved.items():
+            b.bsmm_set_option(key, v)
+    assert st["n_sched_runs"] > 4096
+    with np.errstate(invalid="ignore"):
+        R = orc.multiply(1.0, A, B, 0.0)
+    first = np.cumsum(rs) - rs
+    inner = np.setdiff1d(np.arange(rs.sum()), first)
+    assert np.isfinite(orc.to_dense(X)[np.ix_(inner, inner)]).all()
+    check_against_oracle(X, R, 0.0)
+
+
 @pytest.mark.parametrize("nk", [1, 31, 32, 33, 65])
 @pytest.mark.parametrize("nbc", [5, 4000, 4001])
 def test_product_lists(nk, nbc):
