@@ -225,8 +225,9 @@ int bsmm_set_allocator(bsmm_alloc_fn alloc, bsmm_dealloc_fn dealloc, void *ctx);
  *                 (paper, Sec. II: batches of at most 30000 products)
  *   "stack_tile"  "T" > 0 (default "32") runs every MFMA class of blocks up
                  to 32 x 32 whose runs need no splitting in one launch (when
-                 those classes hold at least 4096 runs), its runs ordered by
-                 tiles of C blocks, T / 8 on a side or, where those would
+                 those classes hold at least 4096 runs, or are more than six
+                 and a plan is kept), its runs ordered by tiles of C blocks,
+                 T / 8 on a side or, where those would
                  outnumber the runs, twice, four times, ... that; T on a side
                  in the allocation-free multiply, which gathers tuned classes
                  only.  "0" launches every class on its own.  Results are the

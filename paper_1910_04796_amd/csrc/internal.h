@@ -61,7 +61,7 @@ struct Options {
     std::string mlp_weights;
     int forced[4] = {0, 0, 0, 0};  // "stack_params": tm tn kc waves for every class
     int jit = 0;           // tuned path: run-time compiled kernels for classes of one product depth
-    int stack_tile = 32;   // tuned path: > 0 runs MFMA classes in one launch, tiles of this many blocks
+    int stack_tile = 32;   // T > 0 runs MFMA classes up to 32 x 32 in one launch, by tiles of T / 8 C blocks
     int stack_sched = 1;   // scheduled kernel: 0 static XCD-aware striding, 1 dynamic run counter
     int prescreen = 1;     // stack path with eps > 0: leave out C blocks whose norm bound is below eps
     int stack_at = -1;     // scheduled launch reads A's blocks transposed: 1 on, 0 and -1 (auto) off

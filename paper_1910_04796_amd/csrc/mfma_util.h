@@ -53,10 +53,6 @@ template <> struct Mfma<double> {
         __builtin_memcpy(&v, &x, sizeof v);
         __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
     }
-    static __device__ __forceinline__ void store2(double *p, double x, double y) {
-        const v2d_t v = {x, y};
-        __builtin_memcpy(p, &v, sizeof v);
-    }
 };
 template <> struct Mfma<float> {
     typedef v4f_t acc_t;
@@ -83,10 +79,6 @@ template <> struct Mfma<float> {
         unsigned int v;
         __builtin_memcpy(&v, &x, sizeof v);
         __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, 0);
-    }
-    static __device__ __forceinline__ void store2(float *p, float x, float y) {
-        const v2f_t v = {x, y};
-        __builtin_memcpy(p, &v, sizeof v);
     }
 };
 

@@ -155,8 +155,8 @@ extern "C" int bsmm_tune_shape(int32_t m, int32_t n, int32_t k, int64_t n_runs, 
     const int64_t na = pool * m * (int64_t)k, nb = pool * (int64_t)k * n, nc = n_runs * m * (int64_t)n;
     const int64_t np = n_runs * run_len;
     DevBuf A, B, C, coff, rptr, prods;
-    BSMM_TRY(A.reserve(sizeof(double) * (na + 1), s));  // a pair load may end one past the last block
-    BSMM_TRY(B.reserve(sizeof(double) * (nb + 1), s));
+    BSMM_TRY(A.reserve(sizeof(double) * na, s));
+    BSMM_TRY(B.reserve(sizeof(double) * nb, s));
     BSMM_TRY(C.reserve(sizeof(double) * nc, s));
     BSMM_TRY(coff.reserve(sizeof(int64_t) * n_runs, s));
     BSMM_TRY(rptr.reserve(sizeof(int64_t) * (n_runs + 1), s));

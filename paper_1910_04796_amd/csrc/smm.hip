@@ -1,4 +1,4 @@
-// smm.hip -- batched small-block GEMM over the product stacks (FP64).
+// smm.hip -- batched small-block GEMM over the product stacks.
 //
 // Paper, Sec. II: the stacks of small block products are processed by
 // dedicated small-matrix kernels (LIBCUSMM on NVIDIA GPUs, parametrised by
@@ -17,8 +17,9 @@
 //    of one row;
 //  * long k is split into chunks that fit the region; tile sets larger than
 //    one wavefront are covered in passes;
-//  * for blocks of about 16 x 16 and more, a variant runs each C block on
-//    FP64 matrix cores (register tile "16 x 16" in the parameter space).
+//  * a variant runs each C block on matrix cores (register tile "16 x 16" in
+//    the parameter space; the plain rule takes it for blocks of 25 elements
+//    up to 64 x 64).
 //
 // The epilogue applies C = beta*C + alpha*acc (beta == 0 overwrites).
 #include <algorithm>
@@ -140,14 +141,15 @@ __global__ __launch_bounds__(256) void k_smm_valu(SmmArgs p) {
     }
 }
 
-// MFMA variant for blocks of at least about 16 x 16 (parameter set
-// tm = tn = 16): one wave owns one run at a time and keeps the C block as
-// MT x NT tiles of 16 x 16 x 4 MFMA accumulators (m <= 16 MT, n <= 16 NT):
-// v_mfma_f64_16x16x4 for FP64, v_mfma_f32_16x16x4 for FP32.  Operands come
-// straight from the contiguous A and B blocks; rows and columns past the
-// block repeat its last one (they only reach results that are not stored),
-// and k past the block is zero on both sides.  Both instructions take lane
-// l's operands at row (or column) l % 16 and k = l / 16 of the step.
+// MFMA variant (parameter set tm = tn = 16): one wave owns one run at a time
+// and keeps the C block as MT x NT tiles of 16 x 16 x 4 MFMA accumulators
+// (m <= 16 MT, n <= 16 NT): v_mfma_f64_16x16x4 for FP64, v_mfma_f32_16x16x4 for
+// FP32.  Operands come straight from the contiguous A and B blocks; lanes past a
+// block's rows or columns read what follows in the block, or zero past its end
+// (they only reach results that are not stored), and k past the block is zero
+// on both sides.
+// Both instructions take lane l's operands at row (or column) l % 16 and
+// k = l / 16 of the step.
 
 // Where an operand's values lie.
 enum OperandLayout {
