@@ -5,9 +5,10 @@ import numpy as np
 import pytest
 
 from oracle import oracle as orc
-from synth import make_matrix, rng_of
+from synth import BlockCSR, make_matrix, rng_of
 
 from tests.helpers import check_against_oracle, gpu_multiply
+from tests.test_launch_rules import dense_parts, rules  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -17,6 +18,15 @@ def _cover(total, sizes, rng):
     while sum(out) < total:
         out.append(min(int(rng.choice(sizes)), total - sum(out)))
     return np.asarray(out, np.int32)
+
+
+def _parts(rules, m, n, k, dtype="f64", max_bytes=1 << 31):  # noqa: F811
+    """What the library's rule makes of a product: (tiles in one piece, parts
+    of k of the others)."""
+    import torch
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    size, us = (8, 4.0) if dtype == "f64" else (4, 2.0)
+    return dense_parts(rules, -(-m // 128) * -(-n // 128), -(-k // 16), slots, size * 128 * 128, max_bytes, us)[:2]
 
 
 @pytest.mark.parametrize("beta", [0.0, -2.0])
@@ -34,43 +44,67 @@ def test_tile_edges_exact(m, n, k, beta):
 
 
 @pytest.mark.parametrize("occ", [0.4, 1.0])
-def test_split_k_into_blocks(occ):
+def test_split_k_into_blocks(rules, occ):  # noqa: F811
     """Nine tiles with a long k (split), absent blocks of A and B read as
     zero and a C that stores only the product's blocks."""
     rng = rng_of(int(10 * occ))
     rs, ks, ns = _cover(300, [5, 13, 23], rng), _cover(5000, [23, 32], rng), _cover(333, [5, 13, 23], rng)
     A, B = make_matrix(rng, rs, ks, occ * 0.05, "int"), make_matrix(rng, ks, ns, occ, "int")
     X, _ = gpu_multiply(1.0, A, B, 0.0, path="dense")
+    assert _parts(rules, 300, 333, 5000)[1] >= 19  # (at least 16 k steps of 16 each)
+    assert (len(X.col_ind) == len(rs) * len(ns)) == (occ == 1.0)
     check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)
 
 
-def test_last_round_in_parts():
-    """529 tiles: 512 of them whole, the last ones in parts of k, into a C
-    that stores every other block."""
+@pytest.mark.parametrize("full", [True, False])
+def test_last_round_in_parts(rules, full):  # noqa: F811
+    """529 tiles: 512 of them whole, the last ones in parts of k.  A full C,
+    and one that lacks blocks of the rows (columns) that A (B) stores nothing
+    of, found through the map of its blocks."""
     rng = rng_of(4)
     rs, ks = _cover(23 * 128, [32], rng), _cover(300, [20], rng)
     A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
     C = make_matrix(rng, rs, rs, 0.5, "int")
-    X, _ = gpu_multiply(1.0, A, B, 2.0, C, path="dense")
+    if not full:
+        nb, nk = len(rs), len(ks)
+        rows, cols = np.arange(nb) % 3 != 1, np.arange(nb) % 4 != 2
+        A = _only(A, np.repeat(rows, nk))
+        B = _only(B, np.tile(cols, nk))
+    X, st = gpu_multiply(1.0, A, B, 2.0, C, path="dense")
+    whole, splits = _parts(rules, 23 * 128, 23 * 128, 300)
+    assert st["path"] == 2 and whole == 512 and splits == 2
+    assert (len(X.col_ind) == len(rs) ** 2) == full
     check_against_oracle(X, orc.multiply(1.0, A, B, 2.0, C), 0.0)
 
 
-def test_split_k_f32():
+def _only(M, keep):
+    """M with the stored blocks of `keep` alone."""
+    rows = np.repeat(np.arange(len(M.rbs)), np.diff(M.row_ptr))
+    sizes = np.asarray(M.rbs, np.int64)[rows] * np.asarray(M.cbs, np.int64)[M.col_ind]
+    rp = np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=len(M.rbs)))]).astype(np.int64)
+    return BlockCSR(M.rbs, M.cbs, rp, M.col_ind[keep], M.data[np.repeat(keep, sizes)])
+
+
+def test_split_k_f32(rules):  # noqa: F811
     from tests.test_gpu_f32 import _as_f32, _f32_multiply
     rng = rng_of(9)
     rs, ks = _cover(200, [22], rng), _cover(4000, [22], rng)
     A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
     X, _ = _f32_multiply(1.0, _as_f32(A), _as_f32(B), 0.0, path="dense")
+    assert _parts(rules, 200, 200, 4000, "f32")[1] >= 15
     check_against_oracle(X, orc.multiply(1.0, A, B, 0.0), 0.0)  # sums below 2^24: exact in FP32
 
 
-def test_split_k_within_the_scratch_region():
+def test_split_k_within_the_scratch_region(rules):  # noqa: F811
     """The allocation-free multiply of a long k: the parts of k shrink to
-    what the scratch region holds beside the panels."""
+    what the scratch region of 64 MiB holds beside the panels."""
     from tests.helpers import lib, set_path
     rng = rng_of(12)
-    rs, ks = _cover(640, [32], rng), _cover(6000, [32], rng)
+    rs, ks = _cover(256, [32], rng), _cover(14000, [32], rng)
     A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
+    left = (64 << 20) - 2 * 8 * 256 * 14000  # at most; the index arrays take some of it
+    assert 2 < _parts(rules, 256, 256, 14000, max_bytes=left - (1 << 20))[1]
+    assert _parts(rules, 256, 256, 14000, max_bytes=left)[1] < _parts(rules, 256, 256, 14000)[1]
     b = lib()
     set_path("dense")
     try:
@@ -107,7 +141,7 @@ def test_k_step_32(m, n, k, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-def test_error_of_split_sums(dtype):
+def test_error_of_split_sums(rules, dtype):  # noqa: F811
     """210 tiles of 128 x 128: an element's sums are cut into parts of k no
     longer than two rounds of workgroups make them.  A chain of L sums of
     random terms, S of them added up, has the relative error
@@ -126,7 +160,7 @@ def test_error_of_split_sums(dtype):
         X, st = _f32_multiply(1.0, A, B, 0.0, path="dense")
     else:
         X, st = gpu_multiply(1.0, A, B, 0.0, path="dense")
-    assert st["path"] == 2
+    assert st["path"] == 2 and _parts(rules, m, n, k, dtype)[1] >= 5
     slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
     steps = k // 16
     S = min(-(-2 * slots // 210), steps // 16)

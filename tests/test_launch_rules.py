@@ -22,28 +22,28 @@ extern "C" int segment_bits(int64_t n) { return bsmm::schedule_segment_bits(n, 8
 """
 
 
-@pytest.fixture(scope="module")
-def rules(tmp_path_factory):
-    d = tmp_path_factory.mktemp("launch_rules")
+def build_rules(d):
     (d / "rule.cpp").write_text(SRC)
     so = str(d / "rule.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC",
                     "-I" + os.path.join(ROOT, "paper_1910_04796_amd", "csrc"), str(d / "rule.cpp"), "-o", so],
                    check=True)
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    lib.parts.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_double, ctypes.POINTER(ctypes.c_int64)]
+    lib.segment_bits.argtypes = [ctypes.c_int64]
+    return lib
+
+
+def dense_parts(rules, tiles, ktiles, slots, tile_bytes, max_bytes, step_us):
+    """(tiles in one piece, parts of k of the others, k steps of a part)"""
+    out = (ctypes.c_int64 * 3)()
+    rules.parts(tiles, ktiles, slots, tile_bytes, max_bytes, step_us, out)
+    return tuple(out)
 
 
 @pytest.fixture(scope="module")
-def parts(rules):
-    fn = rules.parts
-    fn.argtypes = [ctypes.c_int64] * 5 + [ctypes.c_double, ctypes.POINTER(ctypes.c_int64)]
-
-    def call(tiles, ktiles, slots, tile_bytes, max_bytes, step_us):
-        out = (ctypes.c_int64 * 3)()
-        fn(tiles, ktiles, slots, tile_bytes, max_bytes, step_us, out)
-        return tuple(out)
-
-    return call
+def rules(tmp_path_factory):
+    return build_rules(tmp_path_factory.mktemp("launch_rules"))
 
 
 def _cases():
@@ -56,9 +56,9 @@ def _cases():
 
 @pytest.mark.parametrize("tile_bytes,step_us,slots", [(131072, 4.0, 512), (65536, 2.0, 512), (131072, 4.0, 256)])
 @pytest.mark.parametrize("max_bytes", [0, 64 << 20, 1 << 31])
-def test_parts_cover_k_and_are_never_too_long(parts, max_bytes, tile_bytes, step_us, slots):
+def test_parts_cover_k_and_are_never_too_long(rules, max_bytes, tile_bytes, step_us, slots):
     for tiles, ktiles in _cases():
-        whole, splits, per = parts(tiles, ktiles, slots, tile_bytes, max_bytes, step_us)
+        whole, splits, per = dense_parts(rules, tiles, ktiles, slots, tile_bytes, max_bytes, step_us)
         case = (tiles, ktiles, whole, splits, per)
         assert 0 <= whole <= tiles and splits >= 1, case
         assert (whole == tiles) == (splits == 1), case
@@ -79,7 +79,6 @@ def test_segments_share_the_runs(rules):
     """Segment after segment goes to the next XCD: no XCD has more than an
     eighth of the runs and one segment, and a segment is a small part of that
     share unless it is the smallest there is."""
-    rules.segment_bits.argtypes = [ctypes.c_int64]
     rng = random.Random(8)
     sizes = [1, 3, 4, 5, 9, 31, 32, 33, 144, 196, 255, 256, 257, 900, 4096, 4225, 16383, 16384, 10**6, 10**9]
     for n in sizes + [int(2 ** rng.uniform(0, 30)) for _ in range(300)]:
