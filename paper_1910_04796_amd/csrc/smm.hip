@@ -898,19 +898,22 @@ static int copy_rows(const bsmm_matrix_s *M, DevBuf &buf, hipStream_t s) {
     return launch_check("transpose_blocks");
 }
 
-// Estimated time (us) that the launch of class cl needs when few of its runs
-// fill the GPU: one run's products one after the other.  A wave takes 9.3
-// GFLOP/s on the register-tile kernel, 36 (FP32 twice that) on the MFMA kernel
-// and there at least 0.28 us per 8 values of k.
-static double launch_chain_us(const Stacks &st, int cl, const SmmLaunch &L, double k) {
+// What the launch of class cl would gain (us, estimated) from others beside it
+// when its runs are few: the time of one run's products one after the other,
+// beyond the 5 us that any launch takes to start.  A wave takes 7.5 GFLOP/s on
+// the register-tile kernel, 36 (FP32 twice that) on the MFMA kernel and there at
+// least 0.28 us per 8 values of k; a wave of that kernel on every SIMD leaves
+// nothing to gain.
+static double launch_gain_us(const Stacks &st, int cl, const SmmLaunch &L, double k) {
     if ((int)st.class_prod_begin.size() != st.n_classes + 1) return 0.0;
     const double runs = (double)(st.class_begin[cl + 1] - st.class_begin[cl]);
     const double prods = (double)(st.class_prod_begin[cl + 1] - st.class_prod_begin[cl]);
     const double flops = 2.0 * st.row_sizes[cl / st.ncs] * st.col_sizes[cl % st.ncs] * k;
-    const bool mfma = L.args.kc_max == 0;  // (no k chunks in LDS)
-    const double us = mfma ? std::max(0.28 * std::ceil(k / 8.0), flops / (L.dtype == BSMM_F32 ? 72e3 : 36e3))
-                           : flops / 9.3e3;
-    return prods / std::max(runs, 1.0) / std::max(L.args.split, 1) * us;
+    const int split = std::max(L.args.split, 1);
+    const double chain = prods / std::max(runs, 1.0) / split;
+    if (L.args.kc_max > 0) return std::max(chain * flops / 7.5e3 - 5.0, 0.0);  // k chunks in LDS: register tiles
+    const double us = std::max(0.28 * std::ceil(k / 8.0), flops / (L.dtype == BSMM_F32 ? 72e3 : 36e3));
+    return std::max(chain * us - 5.0, 0.0) * std::max(1.0 - runs * split / (4.0 * cu_count()), 0.0);
 }
 
 int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C, Stacks &st,
@@ -952,10 +955,10 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
                           (int)st.class_prod_begin.size() == st.n_classes + 1;
     std::vector<char> eligible(st.n_classes, 0);
     const double mean_k = (double)A->cols() / std::max(A->nbc, 1);
-    double sum_us = 0.0, longest_us = 0.0;  // of the classes' own launches
+    double sum_us = 0.0, longest_us = 0.0;  // of launch_gain_us over the classes' own launches
     auto own_launch = [&](int cl, const SmmLaunch &L) {
         launches.push_back({L, {st.class_begin[cl], st.class_begin[cl + 1]}});
-        const double us = launch_chain_us(st, cl, L, mean_k);
+        const double us = launch_gain_us(st, cl, L, mean_k);
         sum_us += us;
         longest_us = std::max(longest_us, us);
     };
@@ -1080,16 +1083,16 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     // on a scratch arena launches its classes one by one instead, and so
     // does one with run-time compiled kernels (module functions, which a
     // graph kernel node does not take).  Without a plan a graph is built for one
-    // use, about 190 us, which its launches have to save by running side by
-    // side: it is worth it when they take some 300 us longer one behind the
-    // other than the longest one alone (tuned, graph and one by one, us: 8 x 8
-    // blocks of 65 and 70, 6 products a run 478 and 997, 2 products 329 and 416;
-    // 8 x 8 blocks of 33 to 64, 40 products 669 and 1345, 5 products 363 and 424,
-    // 2 products 329 and 209; 12 x 12 blocks of 5 to 32, 40 products 458 and 500,
-    // 13 products 344 and 340, 5 products 360 and 206).  More than three launches
-    // of many runs gain by it whatever their length.
+    // use, 150 to 190 us, which its launches have to save by running side by
+    // side: it is worth it when all but the longest gain 160 us so.  Tuned, graph
+    // and one by one, us: 8 x 8 blocks of 65 and 70, 6 products a run 478 and 997;
+    // of 33 to 64, 40 products 669 and 1345, 5 products 363 and 424, 2 products
+    // 329 and 209; 12 x 12 blocks of 5 to 32, 40 products 458 and 500, 13 products
+    // 344 and 340, 5 products 360 and 206; 40 x 40 blocks of 40 and 64, 40 products
+    // 632 and 564; 630 classes of one short product a run 3.97 and 3.20 ms.  More
+    // than three launches of many runs gain by it whatever their length.
     const bool worth_graph =
-        launches.size() > 1 && (options().plan_cache || sum_us - longest_us > 300.0 ||
+        launches.size() > 1 && (options().plan_cache || sum_us - longest_us > 160.0 ||
                                 (launches.size() > 3 && st.n_runs >= kSchedMinRuns));
     if (tuned && chunk <= 0 && worth_graph && !scratch_arena() && st.n_jit == 0) {
         BSMM_TRY(build_graph(launches, A, B, C, st, alpha, beta, &ex->exec));

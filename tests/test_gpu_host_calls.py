@@ -59,7 +59,7 @@ def test_graph_without_a_plan_for_long_launches_only(tmp_path):
     by one; the product is exact either way."""
     _run(tmp_path, """
 for sizes, nk, nb, graph in (([65, 70], 12, 8, 1), ([65, 70], 1, 8, 0), ([65], 12, 8, 0), ([5, 13], 12, 8, 0),
-                             ([33, 40, 48, 64], 40, 8, 1), ([33, 40, 48, 64], 2, 8, 0)):
+                             ([33, 40, 48, 64], 40, 8, 1), ([33, 40, 48, 64], 2, 8, 0), (list(range(1, 25)), 1, 24, 0)):
     rs, ks = np.resize(np.array(sizes, np.int32), nb), np.full(nk, 32, np.int32)
     rng = rng_of(nk + nb)
     A, B = make_matrix(rng, rs, ks, 1.0, "int"), make_matrix(rng, ks, rs, 1.0, "int")
