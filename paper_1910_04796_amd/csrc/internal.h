@@ -326,7 +326,7 @@ constexpr int kMaxStackK = 0xFFFF;
 constexpr int kMaxStackCols = 8192;
 constexpr int kStackWin = 4096;
 constexpr int kXcds = 8;
-constexpr int kSchedCounterStride = 32;  // in 8-byte words: a line each
+constexpr int kSchedCounterStride = 8;  // in 8-byte words (16 and 32 are no faster; the scratch region holds them too)
 constexpr size_t kSchedCounterBytes = kXcds * kSchedCounterStride * 8;  // one counter per XCD
 // Product stacks of C += A*B, grouped by shape class (m, n).
 struct Stacks {
