@@ -900,10 +900,10 @@ static int copy_rows(const bsmm_matrix_s *M, DevBuf &buf, hipStream_t s) {
 
 // What the launch of class cl would gain (us, estimated) from others beside it
 // when its runs are few: the time of one run's products one after the other,
-// beyond the 5 us that any launch takes to start.  A wave takes 7.5 GFLOP/s on
+// less the 1 us that the host's 5 us for a launch hide beside the kernel's start.  A wave takes 7.5 GFLOP/s on
 // the register-tile kernel, 36 (FP32 twice that) on the MFMA kernel and there at
-// least 0.28 us per 8 values of k; a wave of that kernel on every SIMD leaves
-// nothing to gain.
+// least 0.25 us for a product and 0.14 for each 8 values of k; a wave of that
+// kernel on every SIMD leaves nothing to gain.
 static double launch_gain_us(const Stacks &st, int cl, const SmmLaunch &L, double k) {
     if ((int)st.class_prod_begin.size() != st.n_classes + 1) return 0.0;
     const double runs = (double)(st.class_begin[cl + 1] - st.class_begin[cl]);
@@ -911,9 +911,9 @@ static double launch_gain_us(const Stacks &st, int cl, const SmmLaunch &L, doubl
     const double flops = 2.0 * st.row_sizes[cl / st.ncs] * st.col_sizes[cl % st.ncs] * k;
     const int split = std::max(L.args.split, 1);
     const double chain = prods / std::max(runs, 1.0) / split;
-    if (L.args.kc_max > 0) return std::max(chain * flops / 7.5e3 - 5.0, 0.0);  // k chunks in LDS: register tiles
-    const double us = std::max(0.28 * std::ceil(k / 8.0), flops / (L.dtype == BSMM_F32 ? 72e3 : 36e3));
-    return std::max(chain * us - 5.0, 0.0) * std::max(1.0 - runs * split / (4.0 * cu_count()), 0.0);
+    if (L.args.kc_max > 0) return std::max(chain * flops / 7.5e3 - 1.0, 0.0);  // k chunks in LDS: register tiles
+    const double us = std::max(0.25 + 0.14 * std::ceil(k / 8.0), flops / (L.dtype == BSMM_F32 ? 72e3 : 36e3));
+    return std::max(chain * us - 1.0, 0.0) * std::max(1.0 - runs * split / (4.0 * cu_count()), 0.0);
 }
 
 int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C, Stacks &st,
@@ -1089,8 +1089,9 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     // of 33 to 64, 40 products 669 and 1345, 5 products 363 and 424, 2 products
     // 329 and 209; 12 x 12 blocks of 5 to 32, 40 products 458 and 500, 13 products
     // 344 and 340, 5 products 360 and 206; 40 x 40 blocks of 40 and 64, 40 products
-    // 632 and 564; 630 classes of one short product a run 3.97 and 3.20 ms.  More
-    // than three launches of many runs gain by it whatever their length.
+    // 632 and 564; 398 classes of 3.3 short products a run 2.08 and 2.69 ms, 630 of
+    // one product 3.97 and 3.20.  More than three launches of many runs gain by it
+    // whatever their length.
     const bool worth_graph =
         launches.size() > 1 && (options().plan_cache || sum_us - longest_us > 160.0 ||
                                 (launches.size() > 3 && st.n_runs >= kSchedMinRuns));
