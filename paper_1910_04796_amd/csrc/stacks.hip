@@ -940,6 +940,9 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     // and nprod products.  Where that is only a bound (the screen left blocks
     // out, a third of the products at 1 %), the list waits for its own count.
     if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), nblk, s));
+    // (In the scratch region, where nothing is freed, the schedule's run counters
+    // take the place of the run lengths.)
+    if (scratch_arena()) st.sched_next = std::move(run_cnt);
     if (bound) {
         BSMM_TRY(h.cb.wait());
         nprod = h.cb.host<int64_t>()[2 * ncl + 1];
