@@ -938,12 +938,14 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
     // The rest is queued ahead of the host's wait, by what is known before
     // it: at most nblk runs (the scan's values past the runs are not used)
     // and nprod products.  Where that is only a bound (the screen left blocks
-    // out, a third of the products at 1 %), the list waits for its own count.
+    // out, a third of the products at 1 %), a list of more than 2 MB waits for
+    // its own count (4 us; of 180 us with a few thousand products).
     if (!small) BSMM_TRY(scan_exclusive_i64(run_cnt.as<int64_t>(), st.run_ptr.as<int64_t>(), nblk, s));
     // (In the scratch region, where nothing is freed, the schedule's run counters
     // take the place of the run lengths.)
     if (scratch_arena()) st.sched_next = std::move(run_cnt);
-    if (bound) {
+    const bool counted = bound && nprod > (1 << 17);
+    if (counted) {
         BSMM_TRY(h.cb.wait());
         nprod = h.cb.host<int64_t>()[2 * ncl + 1];
     }
@@ -979,7 +981,7 @@ int stack_rows(const bsmm_matrix_s *A, const bsmm_matrix_s *B, const bsmm_matrix
                            (const int64_t *)st.run_ptr.as<int64_t>(), st.prods.as<ulonglong2>());
         BSMM_TRY(launch_check("stack_fill"));
     }
-    if (!bound) BSMM_TRY(h.cb.wait());
+    if (!counted) BSMM_TRY(h.cb.wait());
     const int64_t *both = h.cb.host<int64_t>();
     BSMM_TRY(check_missing(st, both[2 * ncl + 1], nprod));
     st.class_begin.assign(both, both + ncl + 1);
