@@ -958,6 +958,7 @@ int run_stacks(const bsmm_matrix_s *A, const bsmm_matrix_s *B, bsmm_matrix_s *C,
     double sum_us = 0.0, longest_us = 0.0;  // of launch_gain_us over the classes' own launches
     auto own_launch = [&](int cl, const SmmLaunch &L) {
         launches.push_back({L, {st.class_begin[cl], st.class_begin[cl + 1]}});
+        if (!tuned || options().plan_cache) return;  // never or always a graph
         const double us = launch_gain_us(st, cl, L, mean_k);
         sum_us += us;
         longest_us = std::max(longest_us, us);
