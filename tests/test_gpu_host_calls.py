@@ -49,7 +49,8 @@ def _run(tmp_path, body):
     subprocess.run(["gcc", "-shared", "-fPIC", "-O1", str(tmp_path / "hook.c"), "-o", so, "-ldl"], check=True)
     (tmp_path / "child.py").write_text(CHILD + body)
     r = subprocess.run([sys.executable, str(tmp_path / "child.py"), so], cwd=ROOT, capture_output=True, text=True,
-                       timeout=100, env=dict(os.environ, PYTHONPATH=ROOT))
+                       timeout=100, env=dict(os.environ, PYTHONPATH=os.pathsep.join(filter(None, (
+                           ROOT, os.environ.get("PYTHONPATH"))))))
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
 
 
